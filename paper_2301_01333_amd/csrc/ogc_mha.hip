@@ -2,25 +2,27 @@
 // matmuls, the scalar, the mask and the softmax in one kernel, scores never leaving the compute unit.
 //
 // One workgroup = 4 wavefronts = 128 queries of one (batch, head); a wavefront owns 32 queries (64, as two
-// groups of 32, in the bf16 variant for head dimensions up to 64).  Keys and
-// values stream through LDS in blocks of KB keys (bf16: 64, fp32: 32), prefetched one block ahead in
-// registers.  Both products are computed TRANSPOSED so that a lane owns one query:
+// groups of 32, in the bf16 variant for head dimensions up to 64).  Keys and values stream through LDS 32 at a time
+// (bf16: straight from global memory, see ogc_mha_bf16.h; fp32: prefetched one block ahead in registers).  Both products
+// are computed TRANSPOSED so that a lane owns one query:
 //
 //   S^T[key][query] = K * Q^T     first MFMA operand = 32 keys x k from LDS, second = Q^T, held in registers
-//   O^T[c][query]   = V^T * P^T   first operand = 32 channels x keys from LDS (V is transposed on its way into
-//                                 LDS), second = the softmax weights exactly where the first product left them
+//   O^T[c][query]   = V^T * P^T   first operand = 32 channels x keys from LDS (V is transposed on its way into LDS,
+//                                 or out of it), second = the softmax weights exactly where the first product left them
 //
 // In the 32x32 accumulator layout lane l holds column (query) l%32 and rows 8g + 4(l/32) + e, g,e = 0..3.  The
 // softmax reductions of a query are therefore 16 values inside a lane plus one exchange with lane l^32, the
 // running maximum / sum / rescale factors are per-lane scalars, and the weights feed the second product without
 // any data movement: the reduction axis of that product (keys) may be summed in any order, so V^T is simply
-// written to LDS with its key index permuted to the order in which the accumulator registers hold the keys.
+// taken with its key index permuted to the order in which the accumulator registers hold the keys.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <atomic>
+#include <type_traits>
 
 #include "ogc_mha.h"
 
@@ -42,7 +44,10 @@ struct MhaArgs {
     int batch, heads, seq;
     int q_tiles;       // ceil(seq / queries per workgroup)
     int xcd_order;     // 1: workgroups of one (batch, head) are placed on one XCD
+    uint32_t tiles_magic, heads_magic;  // bf16: reciprocals of q_tiles and heads for div_magic
     float scale_log2;  // scale * log2(e)
+    float inv_scale;   // bf16, mask in LDS: 1 / scale, and the bound its quotient is held to
+    float addend_max;
 };
 
 constexpr float LOG2E = 1.44269504088896340736f;
@@ -63,27 +68,22 @@ MHA_DEV uint32_t pack_bf16(float lo, float hi) {  // round to nearest even, two 
     return __builtin_bit_cast(uint32_t, r);
 }
 
-template <int DT> struct MhaCfg;
-template <> struct MhaCfg<OGC_BF16> {
-    static constexpr int E = 2, KB = 64;
-};
-template <> struct MhaCfg<OGC_F32> {
-    static constexpr int E = 4, KB = 32;
-};
+// n / d; m = floor(2^32 / d) + 1 where that is exact for every n in use (n * d < 2^32, and d > 1), else 0
+MHA_DEV uint32_t div_magic(uint32_t n, uint32_t d, uint32_t m) { return m ? __umulhi(n, m) : n / d; }
 
-// DT: OGC_F32 / OGC_BF16.  D32 = head_dim / 32.  FAST: softmax without the running maximum.  PLAIN: no mask, the
-// sequence is a whole number of key blocks and the scalar is positive, so no key needs an addend.
-// QS: 32-query groups per wavefront (1 or 2).  With 2, every key / value operand read from LDS feeds two matrix
-// instructions (one per group): the bf16 kernel is bound by LDS reads, one KiB per instruction, otherwise.
-template <int DT, int D32, int FAST, int PLAIN, int QS> __global__ __launch_bounds__(256, 2) void ogc_mha_kernel(MhaArgs a) {
-    constexpr int E = MhaCfg<DT>::E, KB = MhaCfg<DT>::KB, D = D32 * 32;
-    constexpr int SB = KB / 32;                 // 32-key sub-blocks per block
-    constexpr int KSTR = D * E + 16;            // bytes per key row of K in LDS (padded)
-    constexpr int VSTR = KB * E + 16;           // bytes per channel row of V^T in LDS (padded)
-    constexpr int CH = D * E / 16;              // 16-byte chunks per token row
-    constexpr int KU = KB * CH / 256;                          // 16-byte chunks of K per thread
-    constexpr int KP = KB / 2;                                 // bf16: key pairs per block
-    constexpr int VU = DT == OGC_BF16 ? (KP * CH + 255) / 256 : D32;  // V units per thread (bf16: a unit is two keys)
+#include "ogc_mha_bf16.h"
+
+constexpr int MHA_F32_KEYS = 32;    // keys per block of the fp32 body
+constexpr int MHA_BF16_WHOLE = 64;  // a bf16 sequence of whole blocks of this many keys without a mask needs no addend
+
+// The fp32 body.  PLAIN: no mask, whole key blocks and a positive scalar, so no key needs an addend.
+template <int D32, int FAST, int PLAIN> MHA_DEV void mha_f32_body(const MhaArgs& a) {
+    constexpr int KB = MHA_F32_KEYS, D = D32 * 32;
+    constexpr int KSTR = D * 4 + 16;   // bytes per key row of K in LDS (padded)
+    constexpr int VSTR = KB * 4 + 16;  // bytes per channel row of V^T in LDS (padded)
+    constexpr int CH = D * 4 / 16;     // 16-byte chunks per token row
+    constexpr int KU = KB * CH / 256;  // 16-byte chunks of K per thread
+    constexpr int VU = D32;            // chunks of V per thread
     __shared__ __attribute__((aligned(16))) uint8_t k_lds[KB * KSTR];
     __shared__ __attribute__((aligned(16))) uint8_t vt_lds[D * VSTR];
     __shared__ __attribute__((aligned(16))) float m_lds[KB];
@@ -99,33 +99,29 @@ template <int DT, int D32, int FAST, int PLAIN, int QS> __global__ __launch_boun
         qt = blockIdx.x % a.q_tiles;
     }
     const int b = bh / a.heads, hd = bh % a.heads, S = a.seq;
-    const uint8_t* kbase = a.k + (b * a.sk[0] + hd * a.sk[1]) * E;
-    const uint8_t* vbase = a.v + (b * a.sv[0] + hd * a.sv[1]) * E;
-    const long long kss = a.sk[2] * E, vss = a.sv[2] * E;
+    const uint8_t* kbase = a.k + (b * a.sk[0] + hd * a.sk[1]) * 4;
+    const uint8_t* vbase = a.v + (b * a.sv[0] + hd * a.sv[1]) * 4;
+    const long long kss = a.sk[2] * 4, vss = a.sv[2] * 4;
 
     // ---- this lane's query row as the second MFMA operand, resident for the whole kernel
-    constexpr int QN = DT == OGC_BF16 ? D / 16 : D / 8;
-    int query[QS];
-    v4i qreg[QS][QN];
-    v16f oacc[QS][D32];
-    float run_max[QS], run_sum[QS];  // run_sum: this lane's keys only, halves are added at the end
+    constexpr int QN = D / 8;
+    const int query = (qt * 4 + wave) * 32 + col;
+    v4i qreg[QN];
+    v16f oacc[D32];
+    float run_max = -INFINITY, run_sum = 0.0f;  // run_sum: this lane's keys only, halves are added at the end
+    {
+        const int qrow = query < S ? query : S - 1;
+        const uint8_t* qp = a.q + (b * a.sq[0] + hd * a.sq[1] + qrow * a.sq[2]) * 4;
 #pragma unroll
-    for (int qs = 0; qs < QS; ++qs) {
-        query[qs] = (qt * 4 + wave) * (32 * QS) + qs * 32 + col;
-        const int qrow = query[qs] < S ? query[qs] : S - 1;
-        const uint8_t* qp = a.q + (b * a.sq[0] + hd * a.sq[1] + qrow * a.sq[2]) * E;
-#pragma unroll
-        for (int i = 0; i < QN; ++i) qreg[qs][i] = *(const v4i*)(qp + i * 32 + h * 16);
+        for (int i = 0; i < QN; ++i) qreg[i] = *(const v4i*)(qp + i * 32 + h * 16);
 #pragma unroll
         for (int d = 0; d < D32; ++d)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[qs][d][r] = 0.0f;
-        run_max[qs] = -INFINITY;
-        run_sum[qs] = 0.0f;
+            for (int r = 0; r < 16; ++r) oacc[d][r] = 0.0f;
     }
 
     // ---- prefetch registers for one block of keys / values / mask
-    v4i kreg[KU], vreg[VU][DT == OGC_BF16 ? 2 : 1];
+    v4i kreg[KU], vreg[VU];
     float mreg = 0.0f;   // the mask value as loaded; scaled when it is written to LDS (scaling here would wait for the load,
                          // and with it for every key / value load issued just before)
     bool mpad = false;   // the key lies beyond the sequence
@@ -136,20 +132,10 @@ template <int DT, int D32, int FAST, int PLAIN, int QS> __global__ __launch_boun
             const int u = tid + 256 * i, key = key0 + u / CH, part = u % CH;
             kreg[i] = (full || key < S) ? *(const v4i*)(kbase + key * kss + part * 16) : (v4i){0, 0, 0, 0};
         }
-        if constexpr (DT == OGC_BF16) {
 #pragma unroll
-            for (int i = 0; i < VU; ++i) {
-                const int u = tid + 256 * i, kp = u % KP, c = u / KP, key = key0 + 2 * kp;
-                const bool on = (KP * CH) % 256 == 0 || 256 * (i + 1) <= KP * CH || c < CH;
-                vreg[i][0] = (on && (full || key < S)) ? *(const v4i*)(vbase + key * vss + c * 16) : (v4i){0, 0, 0, 0};
-                vreg[i][1] = (on && (full || key + 1 < S)) ? *(const v4i*)(vbase + (key + 1) * vss + c * 16) : (v4i){0, 0, 0, 0};
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < VU; ++i) {
-                const int u = tid + 256 * i, key = key0 + (u & 31), c = u >> 5;
-                vreg[i][0] = (full || key < S) ? *(const v4i*)(vbase + key * vss + c * 16) : (v4i){0, 0, 0, 0};
-            }
+        for (int i = 0; i < VU; ++i) {
+            const int u = tid + 256 * i, key = key0 + (u & 31), c = u >> 5;
+            vreg[i] = (full || key < S) ? *(const v4i*)(vbase + key * vss + c * 16) : (v4i){0, 0, 0, 0};
         }
         if (tid < KB) {
             const int key = key0 + tid;
@@ -164,29 +150,11 @@ template <int DT, int D32, int FAST, int PLAIN, int QS> __global__ __launch_boun
             const int u = tid + 256 * i;
             *(v4i*)(k_lds + (u / CH) * KSTR + (u % CH) * 16) = kreg[i];
         }
-        if constexpr (DT == OGC_BF16) {
-            // two keys x eight channels per unit -> eight dwords (key, key+1) at the permuted key position:
-            // within a group of 16 keys, key offset 8*gg + 4*hh + e sits at 8*hh + 4*gg + e
 #pragma unroll
-            for (int i = 0; i < VU; ++i) {
-                const int u = tid + 256 * i, kp = u % KP, c = u / KP, o = (2 * kp) & 15;
-                const int pos = ((2 * kp) & ~15) + ((o & 3) | ((o & 8) >> 1) | ((o & 4) << 1));
-                if (c < CH) {
+        for (int i = 0; i < VU; ++i) {
+            const int u = tid + 256 * i, kl = u & 31, c = u >> 5;
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const uint32_t lo = (uint32_t)vreg[i][0][j >> 1], hi = (uint32_t)vreg[i][1][j >> 1];
-                        const uint32_t w = __builtin_amdgcn_perm(hi, lo, (j & 1) ? 0x07060302u : 0x05040100u);
-                        *(uint32_t*)(vt_lds + (8 * c + j) * VSTR + pos * 2) = w;
-                    }
-                }
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < VU; ++i) {
-                const int u = tid + 256 * i, kl = u & 31, c = u >> 5;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) *(int*)(vt_lds + (4 * c + j) * VSTR + kl * 4) = vreg[i][0][j];
-            }
+            for (int j = 0; j < 4; ++j) *(int*)(vt_lds + (4 * c + j) * VSTR + kl * 4) = vreg[i][j];
         }
         if (tid < KB) m_lds[tid] = mpad ? -INFINITY : mreg * LOG2E;
     };
@@ -200,203 +168,162 @@ template <int DT, int D32, int FAST, int PLAIN, int QS> __global__ __launch_boun
         if (kb + 1 < nkb) prefetch((kb + 1) * KB);
 
         // ---- scores, transposed: rows = keys, columns = queries
-        v16f sacc[QS][SB];
+        v16f sacc;
         {
-            // bf16: the operand reads of a 32-key group go out before its first matrix instruction (the compiler
-            // would otherwise issue each read just ahead of its use and wait for it)
             const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+            const uint8_t* krow = k_lds + col * KSTR + h * 16;
 #pragma unroll
-            for (int sb = 0; sb < SB; ++sb) {
-                const uint8_t* krow = k_lds + (sb * 32 + col) * KSTR + h * 16;
-                v4i kfrag[QN];
-                if constexpr (DT == OGC_BF16) {
-#pragma unroll
-                    for (int i = 0; i < QN; ++i) kfrag[i] = *(const v4i*)(krow + i * 32);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-#pragma unroll
-                for (int i = 0; i < QN; ++i)
-#pragma unroll
-                    for (int qs = 0; qs < QS; ++qs) {
-                        const v4i kv = DT == OGC_BF16 ? kfrag[i] : *(const v4i*)(krow + i * 32);
-                        if constexpr (DT == OGC_BF16) {
-                            sacc[qs][sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                __builtin_bit_cast(v8bf, kv), __builtin_bit_cast(v8bf, qreg[qs][i]), i ? sacc[qs][sb] : zero, 0, 0, 0);
-                        } else {
-                            const v4f kf = __builtin_bit_cast(v4f, kv), qf = __builtin_bit_cast(v4f, qreg[qs][i]);
-                            sacc[qs][sb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, qf.x, i ? sacc[qs][sb] : zero, 0, 0, 0);
-                            sacc[qs][sb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, qf.y, sacc[qs][sb], 0, 0, 0);
-                            sacc[qs][sb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, qf.z, sacc[qs][sb], 0, 0, 0);
-                            sacc[qs][sb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, qf.w, sacc[qs][sb], 0, 0, 0);
-                        }
-                    }
+            for (int i = 0; i < QN; ++i) {
+                const v4f kf = *(const v4f*)(krow + i * 32), qf = __builtin_bit_cast(v4f, qreg[i]);
+                sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, qf.x, i ? sacc : zero, 0, 0, 0);
+                sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, qf.y, sacc, 0, 0, 0);
+                sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, qf.z, sacc, 0, 0, 0);
+                sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, qf.w, sacc, 0, 0, 0);
             }
         }
         // ---- scalar, mask, running maximum (base-2 logarithm domain; a key beyond the sequence carries
         // -infinity).  A block of valid keys without a mask needs no per-key addend: the maximum is taken on
         // the raw products and the scalar rides in the exponent's multiply-add.
         const float c = a.scale_log2;
-#pragma unroll
-        for (int qs = 0; qs < QS; ++qs) {
-            float cand = -INFINITY;
-            if constexpr (PLAIN) {
-                if constexpr (!FAST) {
-#pragma unroll
-                    for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) cand = fmaxf(cand, sacc[qs][sb][r]);
-                    cand *= c;
-                }
-            } else {
-#pragma unroll
-                for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const v4f mk = *(const v4f*)(m_lds + sb * 32 + 8 * g + 4 * h);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float t = __builtin_fmaf(sacc[qs][sb][4 * g + e], c, mk[e]);
-                            sacc[qs][sb][4 * g + e] = t;
-                            if constexpr (!FAST) cand = fmaxf(cand, t);
-                        }
-                    }
-            }
-            float off = 0.0f;
+        float cand = -INFINITY;
+        if constexpr (PLAIN) {
             if constexpr (!FAST) {
-                // The reference point of the exponentials only has to be NEAR the maximum: it moves when a block
-                // exceeds it by more than 2^8, so most blocks skip the rescaling of the output accumulators.  The
-                // result is the same function (numerator and denominator carry the same factor); weights reach
-                // 256 at most, far from any overflow.  Key 0 of block 0 is always valid: the first block sets it.
-                cand = fmaxf(cand, other_half(cand));
-                const bool need = cand > run_max[qs] + 8.0f;
-                if (__builtin_amdgcn_ballot_w64(need) != 0) {
-                    const float new_max = need ? cand : run_max[qs];
-                    const float alpha = __builtin_amdgcn_exp2f(run_max[qs] - new_max);
-                    run_max[qs] = new_max;
-                    run_sum[qs] *= alpha;
 #pragma unroll
-                    for (int d = 0; d < D32; ++d)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) oacc[qs][d][r] *= alpha;
-                }
-                off = -run_max[qs];
+                for (int r = 0; r < 16; ++r) cand = fmaxf(cand, sacc[r]);
+                cand *= c;
             }
-#pragma unroll
-            for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    float x;
-                    if constexpr (PLAIN) x = __builtin_fmaf(sacc[qs][sb][r], c, off);
-                    else x = FAST ? sacc[qs][sb][r] : sacc[qs][sb][r] + off;
-                    sacc[qs][sb][r] = __builtin_amdgcn_exp2f(x);
-                }
-        }
-        // ---- O^T += V^T P^T
-        if constexpr (DT == OGC_BF16) {
-#pragma unroll
-            for (int sb = 0; sb < SB; ++sb)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    // the row sum takes the weights as rounded, the values the second product multiplies
-                    v4i pw[QS];
-#pragma unroll
-                    for (int qs = 0; qs < QS; ++qs) {
-                        const v16f& p = sacc[qs][sb];
-                        uint32_t w[4];
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) {
-                            const v2bf pr = {(__bf16)p[8 * j + 2 * t], (__bf16)p[8 * j + 2 * t + 1]};
-                            run_sum[qs] = __builtin_amdgcn_fdot2_f32_bf16(pr, (v2bf){(__bf16)1.0f, (__bf16)1.0f}, run_sum[qs], false);
-                            w[t] = __builtin_bit_cast(uint32_t, pr);
-                        }
-                        pw[qs] = (v4i){(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-                    }
-#pragma unroll
-                    for (int d = 0; d < D32; ++d) {
-                        const v4i vv = *(const v4i*)(vt_lds + (d * 32 + col) * VSTR + (sb * 32 + 16 * j + 8 * h) * 2);
-#pragma unroll
-                        for (int qs = 0; qs < QS; ++qs)
-                            oacc[qs][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, vv),
-                                                                                  __builtin_bit_cast(v8bf, pw[qs]), oacc[qs][d], 0, 0, 0);
-                    }
-                }
         } else {
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
+            for (int g = 0; g < 4; ++g) {
+                const v4f mk = *(const v4f*)(m_lds + 8 * g + 4 * h);
 #pragma unroll
-                for (int qs = 0; qs < QS; ++qs) run_sum[qs] += sacc[qs][0][r];
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-#pragma unroll
-                for (int d = 0; d < D32; ++d) {
-                    const v4f vv = *(const v4f*)(vt_lds + (d * 32 + col) * VSTR + (8 * g + 4 * h) * 4);
-#pragma unroll
-                    for (int qs = 0; qs < QS; ++qs) {
-                        oacc[qs][d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.x, sacc[qs][0][4 * g], oacc[qs][d], 0, 0, 0);
-                        oacc[qs][d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.y, sacc[qs][0][4 * g + 1], oacc[qs][d], 0, 0, 0);
-                        oacc[qs][d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.z, sacc[qs][0][4 * g + 2], oacc[qs][d], 0, 0, 0);
-                        oacc[qs][d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.w, sacc[qs][0][4 * g + 3], oacc[qs][d], 0, 0, 0);
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    const float t = __builtin_fmaf(sacc[4 * g + e], c, mk[e]);
+                    sacc[4 * g + e] = t;
+                    if constexpr (!FAST) cand = fmaxf(cand, t);
                 }
+            }
         }
+        float off = 0.0f;
+        if constexpr (!FAST) {
+            // The reference point of the exponentials only has to be NEAR the maximum: it moves when a block
+            // exceeds it by more than 2^8, so most blocks skip the rescaling of the output accumulators.  The
+            // result is the same function (numerator and denominator carry the same factor); weights reach
+            // 256 at most, far from any overflow.  Key 0 of block 0 is always valid: the first block sets it.
+            cand = fmaxf(cand, other_half(cand));
+            const bool need = cand > run_max + 8.0f;
+            if (__builtin_amdgcn_ballot_w64(need) != 0) {
+                const float new_max = need ? cand : run_max;
+                const float alpha = __builtin_amdgcn_exp2f(run_max - new_max);
+                run_max = new_max;
+                run_sum *= alpha;
+#pragma unroll
+                for (int d = 0; d < D32; ++d)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) oacc[d][r] *= alpha;
+            }
+            off = -run_max;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            float x;
+            if constexpr (PLAIN) x = __builtin_fmaf(sacc[r], c, off);
+            else x = FAST ? sacc[r] : sacc[r] + off;
+            sacc[r] = __builtin_amdgcn_exp2f(x);
+        }
+        // ---- O^T += V^T P^T
+#pragma unroll
+        for (int r = 0; r < 16; ++r) run_sum += sacc[r];
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int d = 0; d < D32; ++d) {
+                const v4f vv = *(const v4f*)(vt_lds + (d * 32 + col) * VSTR + (8 * g + 4 * h) * 4);
+                oacc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.x, sacc[4 * g], oacc[d], 0, 0, 0);
+                oacc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.y, sacc[4 * g + 1], oacc[d], 0, 0, 0);
+                oacc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.z, sacc[4 * g + 2], oacc[d], 0, 0, 0);
+                oacc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.w, sacc[4 * g + 3], oacc[d], 0, 0, 0);
+            }
     }
 
     // ---- normalise and store: after the half exchange a lane holds 16 consecutive channels of its query
+    const float total = run_sum + other_half(run_sum);
+    const float inv = 1.0f / total;
+    uint8_t* op = a.o + (b * a.so[0] + hd * a.so[1] + (long long)query * a.so[2]) * 4;
 #pragma unroll
-    for (int qs = 0; qs < QS; ++qs) {
-        const float total = run_sum[qs] + other_half(run_sum[qs]);
-        const float inv = 1.0f / total;
-        uint8_t* op = a.o + (b * a.so[0] + hd * a.so[1] + (long long)query[qs] * a.so[2]) * E;
+    for (int d = 0; d < D32; ++d) {
+        uint32_t dw[4][4];
 #pragma unroll
-        for (int d = 0; d < D32; ++d) {
-            if constexpr (DT == OGC_BF16) {
-                uint32_t dw[4][2];
+        for (int g = 0; g < 4; ++g)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    dw[g][0] = pack_bf16(oacc[qs][d][4 * g] * inv, oacc[qs][d][4 * g + 1] * inv);
-                    dw[g][1] = pack_bf16(oacc[qs][d][4 * g + 2] * inv, oacc[qs][d][4 * g + 3] * inv);
-                }
+            for (int e = 0; e < 4; ++e) dw[g][e] = __builtin_bit_cast(uint32_t, oacc[d][4 * g + e] * inv);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    swap32(dw[0][j], dw[2][j]);
-                    swap32(dw[1][j], dw[3][j]);
-                }
-                if (query[qs] < S) {
-                    uint8_t* dst = op + (d * 32 + 16 * h) * 2;
-                    *(v4i*)dst = (v4i){(int)dw[0][0], (int)dw[0][1], (int)dw[2][0], (int)dw[2][1]};
-                    *(v4i*)(dst + 16) = (v4i){(int)dw[1][0], (int)dw[1][1], (int)dw[3][0], (int)dw[3][1]};
-                }
-            } else {
-                uint32_t dw[4][4];
+        for (int e = 0; e < 4; ++e) {
+            swap32(dw[0][e], dw[2][e]);
+            swap32(dw[1][e], dw[3][e]);
+        }
+        if (query < S) {
+            uint8_t* dst = op + (d * 32 + 16 * h) * 4;
+            const int order[4] = {0, 2, 1, 3};
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) dw[g][e] = __builtin_bit_cast(uint32_t, oacc[qs][d][4 * g + e] * inv);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    swap32(dw[0][e], dw[2][e]);
-                    swap32(dw[1][e], dw[3][e]);
-                }
-                if (query[qs] < S) {
-                    uint8_t* dst = op + (d * 32 + 16 * h) * 4;
-                    const int order[4] = {0, 2, 1, 3};
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        *(v4i*)(dst + 16 * g) = (v4i){(int)dw[order[g]][0], (int)dw[order[g]][1], (int)dw[order[g]][2], (int)dw[order[g]][3]};
-                }
-            }
+            for (int g = 0; g < 4; ++g)
+                *(v4i*)(dst + 16 * g) = (v4i){(int)dw[order[g]][0], (int)dw[order[g]][1], (int)dw[order[g]][2], (int)dw[order[g]][3]};
         }
     }
 }
 
+// Wavefronts per SIMD the registers are held to: one 32-query group with head_dim <= 64 fits three.
+constexpr int mha_waves(int dt, int d32, int qs) { return dt == OGC_BF16 && qs == 1 && d32 <= 2 ? 3 : 2; }
+
+// DT: OGC_F32 / OGC_BF16.  D32 = head_dim / 32.  FAST: softmax without the running maximum.  PLAIN: no mask, the
+// sequence is a whole number of key blocks and the scalar is positive, so no key needs an addend.
+// QS: 32-query groups per wavefront (1 or 2).  With 2, every key / value operand read from LDS feeds two matrix
+// instructions (one per group).
+template <int DT, int D32, int FAST, int PLAIN, int QS>
+__global__ __launch_bounds__(256, mha_waves(DT, D32, QS)) void ogc_mha_kernel(MhaArgs a) {
+    if constexpr (DT == OGC_BF16) {
+        extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+        mha_bf16_body<D32, FAST, PLAIN ? MHA_NO_ADDEND : MHA_ADDEND_IN_LDS, QS>(a, (mha_lds_u8*)smem);
+    } else {
+        mha_f32_body<D32, FAST, PLAIN>(a);
+    }
+}
+
+// bf16 calls that do not fit the other forms: scalars that are not positive or have no fp32 reciprocal, token strides
+// beyond 32 bits of byte offset.
+template <int D32, int FAST> __global__ __launch_bounds__(256, 2) void ogc_mha_general_kernel(MhaArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    mha_bf16_body<D32, FAST, MHA_ADDEND_GENERAL, 1>(a, (mha_lds_u8*)smem);
+}
+
 namespace {
 
-template <int DT, int D32, int QS> hipError_t launch_fast(int fast, int plain, const MhaArgs& a, dim3 grid, hipStream_t st) {
-    if (fast && plain) hipLaunchKernelGGL((ogc_mha_kernel<DT, D32, 1, 1, QS>), grid, dim3(256), 0, st, a);
-    else if (fast) hipLaunchKernelGGL((ogc_mha_kernel<DT, D32, 1, 0, QS>), grid, dim3(256), 0, st, a);
-    else if (plain) hipLaunchKernelGGL((ogc_mha_kernel<DT, D32, 0, 1, QS>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((ogc_mha_kernel<DT, D32, 0, 0, QS>), grid, dim3(256), 0, st, a);
+// Bytes of LDS of a bf16 launch: the ring, and the addends where the mode keeps them there.
+size_t bf16_lds(int d32, int seq, int plain) {
+    const int keys = seq <= MHA_UNIT ? 2 * MHA_UNIT : (seq + MHA_UNIT - 1) / MHA_UNIT * MHA_UNIT;  // at least two units
+    return (size_t)2 * 4 * MHA_UNIT * d32 * 64 + (plain ? 0 : (size_t)(keys < MHA_LDS_KEYS ? keys : MHA_LDS_KEYS) * 4);
+}
+
+// One launch with dynamic LDS; the limit is raised once per kernel that can ask for more than 64 KiB (head_dim 128: up to
+// 80 KiB).  Two threads at once only repeat it.
+template <int DT, int D32, int FAST, int PLAIN, int QS> hipError_t launch_one(const MhaArgs& a, dim3 grid, hipStream_t st) {
+    auto kern = ogc_mha_kernel<DT, D32, FAST, PLAIN, QS>;
+    const size_t lds = DT == OGC_BF16 ? bf16_lds(D32, a.seq, PLAIN) : 0;
+    static std::atomic<bool> raised{false};
+    if (lds > 65536 && !raised.load(std::memory_order_acquire)) {
+        const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)bf16_lds(D32, MHA_LDS_KEYS, PLAIN));
+        if (e != hipSuccess) return e;
+        raised.store(true, std::memory_order_release);
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a);
     return hipGetLastError();
+}
+template <int DT, int D32, int QS> hipError_t launch_fast(int fast, int plain, const MhaArgs& a, dim3 grid, hipStream_t st) {
+    if (fast && plain) return launch_one<DT, D32, 1, 1, QS>(a, grid, st);
+    if (fast) return launch_one<DT, D32, 1, 0, QS>(a, grid, st);
+    if (plain) return launch_one<DT, D32, 0, 1, QS>(a, grid, st);
+    return launch_one<DT, D32, 0, 0, QS>(a, grid, st);
 }
 template <int DT> hipError_t launch_dim(int d32, int qs, int fast, int plain, const MhaArgs& a, dim3 grid, hipStream_t st) {
     if (qs == 2) {  // bf16 with head_dim <= 64 only (query_groups)
@@ -409,6 +336,35 @@ template <int DT> hipError_t launch_dim(int d32, int qs, int fast, int plain, co
     default: return launch_fast<DT, 4, 1>(fast, plain, a, grid, st);
     }
 }
+template <int D32> void launch_general_dim(int fast, const MhaArgs& a, dim3 grid, hipStream_t st) {
+    if (fast) hipLaunchKernelGGL((ogc_mha_general_kernel<D32, 1>), grid, dim3(256), bf16_lds(D32, a.seq, 1), st, a);
+    else hipLaunchKernelGGL((ogc_mha_general_kernel<D32, 0>), grid, dim3(256), bf16_lds(D32, a.seq, 1), st, a);
+}
+hipError_t launch_general(int d32, int fast, const MhaArgs& a, dim3 grid, hipStream_t st) {
+    switch (d32) {
+    case 1: launch_general_dim<1>(fast, a, grid, st); break;
+    case 2: launch_general_dim<2>(fast, a, grid, st); break;
+    case 3: launch_general_dim<3>(fast, a, grid, st); break;
+    default: launch_general_dim<4>(fast, a, grid, st); break;
+    }
+    return hipGetLastError();
+}
+
+// no mask, whole key blocks only, positive scalar
+bool plain_case(const ogc_mha_desc* d, const float* mask) {
+    const int kb = d->dtype == OGC_BF16 ? MHA_BF16_WHOLE : MHA_F32_KEYS;
+    return mask == nullptr && d->seq % kb == 0 && d->scale > 0.0f;
+}
+
+// bf16 calls that take the general kernel.  A lane's piece is addressed by 32 bits of byte offset from its unit's first
+// row; the addend in LDS is the mask divided by the scalar.
+bool general_case(const ogc_mha_desc* d, const float* mask) {
+    if (d->dtype != OGC_BF16) return false;
+    const int64_t most = (int64_t)1 << 31;
+    if (d->k_stride[2] * 2 > most / MHA_UNIT || d->v_stride[2] * 2 > most / MHA_UNIT) return true;
+    if (plain_case(d, mask)) return false;
+    return !(d->scale >= 1e-30f && d->scale <= 1e30f);
+}
 
 // 32-query groups per wavefront.  Two where the registers allow it (bf16, head_dim <= 64) and the sequence is long
 // enough to keep the four wavefronts of a workgroup busy: the bf16 kernel is then no longer bound by LDS reads.
@@ -416,12 +372,6 @@ int query_groups(const ogc_mha_desc* d) {
     const bool can = d->dtype == OGC_BF16 && d->head_dim <= 64;
     if (d->query_groups != 0) return (d->query_groups == 2 && can) ? 2 : 1;
     return (can && d->seq >= 256) ? 2 : 1;
-}
-
-// no mask, whole key blocks only, positive scalar
-bool plain_case(const ogc_mha_desc* d, const float* mask) {
-    const int kb = d->dtype == OGC_BF16 ? MhaCfg<OGC_BF16>::KB : MhaCfg<OGC_F32>::KB;
-    return mask == nullptr && d->seq % kb == 0 && d->scale > 0.0f;
 }
 
 bool stride_ok(const int64_t s[3], int elt) {
@@ -472,21 +422,33 @@ ogc_status ogc_mha_run(const ogc_mha_desc* d, const void* q, const void* k, cons
     a.batch = d->batch;
     a.heads = d->heads;
     a.seq = d->seq;
-    const int qs = query_groups(d);
+    const bool general = general_case(d, mask);
+    const int qs = general ? 1 : query_groups(d);
     a.q_tiles = (d->seq + 128 * qs - 1) / (128 * qs);
     const int bh = d->batch * d->heads;
+    auto magic = [](uint64_t n, uint64_t v) { return v == 1 || n * v >= 1ull << 32 ? 0u : (uint32_t)((1ull << 32) / v + 1); };
+    a.tiles_magic = magic((uint64_t)bh * a.q_tiles, a.q_tiles);
+    a.heads_magic = magic(bh, d->heads);
     a.xcd_order = (bh % 8 == 0) ? 1 : 0;
     a.scale_log2 = d->scale * 1.44269504088896340736f;
+    a.inv_scale = 1.0f / d->scale;
+    a.addend_max = 3.0e38f / fmaxf(1.0f, a.scale_log2);
     const dim3 grid((unsigned)(bh * a.q_tiles));
     const int plain = plain_case(d, mask);
-    const hipError_t e = d->dtype == OGC_F32 ? launch_dim<OGC_F32>(d->head_dim / 32, qs, d->softmax, plain, a, grid, (hipStream_t)stream)
+    const hipError_t e = general ? launch_general(d->head_dim / 32, d->softmax, a, grid, (hipStream_t)stream)
+                       : d->dtype == OGC_F32 ? launch_dim<OGC_F32>(d->head_dim / 32, qs, d->softmax, plain, a, grid, (hipStream_t)stream)
                                              : launch_dim<OGC_BF16>(d->head_dim / 32, qs, d->softmax, plain, a, grid, (hipStream_t)stream);
     return e == hipSuccess ? OGC_OK : OGC_ERR_DEVICE;
 }
 
 const char* ogc_mha_kernel_name(const ogc_mha_desc* d, int32_t has_mask) {
     if (ogc_mha_validate(d) != OGC_OK) return nullptr;
-    static char names[2][4][2][2][2][48];
+    static char names[2][4][2][2][2][48], general[4][2][48];
+    if (general_case(d, has_mask ? (const float*)d : nullptr)) {
+        char* g = general[d->head_dim / 32 - 1][d->softmax];
+        if (!g[0]) snprintf(g, 48, "ogc_mha_general_kernel<%d, %d>", d->head_dim / 32, d->softmax);
+        return g;
+    }
     const int plain = plain_case(d, has_mask ? (const float*)d : nullptr), qs = query_groups(d);
     char* s = names[d->dtype == OGC_BF16][d->head_dim / 32 - 1][d->softmax][plain][qs - 1];
     if (!s[0]) snprintf(s, 48, "ogc_mha_kernel<%d, %d, %d, %d, %d>", d->dtype, d->head_dim / 32, d->softmax, plain, qs);
