@@ -842,36 +842,78 @@ ogc_prepack_params_kernel(int dtype, const int8_t* __restrict__ wq, const float*
     if (dtype == OGC_I8 || dtype == OGC_F8) scale_out[n] = valid ? in_scale * w_scale[n] : 0.0f;
 }
 
-// Quantize / dequantize nodes of the low-precision graph (Section V) for E4M3 tensors at the boundary: elementwise,
-// four elements per thread, the same reciprocal multiply, rounding and saturation as a layer's requantized output.
-__global__ void ogc_quantize_e4m3_kernel(const float* __restrict__ x, uint8_t* __restrict__ out, size_t n, float inv_scale) {
-    const size_t i = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-    if (i >= n) return;
-    float v[4];
+// Quantize / dequantize nodes of the low-precision graph (Section V) for E4M3 tensors at the boundary: elementwise, the
+// same reciprocal multiply, rounding and saturation as a layer's requantized output.  Bound by HBM: five bytes an element.
+// A workgroup takes 4096 elements, a thread four groups of four, neighbouring lanes neighbouring groups: 16-byte accesses on
+// the fp32 side, 4-byte ones on the other, four of each in flight (33.5 MB of fp32 and 8.4 of codes: quantize 13.9 -> 7.5 us,
+// dequantize 12.7 -> 7.8 us, against 8.2 at the rate of a large copy from HBM; one thread for four elements by scalar
+// accesses, or for one, was the slower).  Groups that are not whole or not aligned (vec = 0: x to 16 bytes, out to 4) go element by element.
+#define OGC_CONVERT_GROUPS 4
+__global__ void __launch_bounds__(256) ogc_quantize_e4m3_kernel(const float* __restrict__ x, uint8_t* __restrict__ out, size_t n,
+                                                               float inv_scale, int vec) {
+    const size_t i0 = ((size_t)blockIdx.x * OGC_CONVERT_GROUPS * 256 + threadIdx.x) * 4;
+    v4f v[OGC_CONVERT_GROUPS];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = i + j < n ? x[i + j] * inv_scale : 0.0f;
-    const uint32_t q = f32x4_to_e4m3x4(v[0], v[1], v[2], v[3]);
+    for (int g = 0; g < OGC_CONVERT_GROUPS; ++g) {
+        const size_t i = i0 + g * 1024;
+        if (vec && i + 4 <= n) v[g] = *(const v4f*)(x + i);
+        else
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-        if (i + j < n) out[i + j] = (uint8_t)(q >> (8 * j));
+            for (int j = 0; j < 4; ++j) v[g][j] = i + j < n ? x[i + j] : 0.0f;
+    }
+#pragma unroll
+    for (int g = 0; g < OGC_CONVERT_GROUPS; ++g) {
+        const size_t i = i0 + g * 1024;
+        const uint32_t q = f32x4_to_e4m3x4(v[g][0] * inv_scale, v[g][1] * inv_scale, v[g][2] * inv_scale, v[g][3] * inv_scale);
+        if (vec && i + 4 <= n) *(uint32_t*)(out + i) = q;
+        else
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (i + j < n) out[i + j] = (uint8_t)(q >> (8 * j));
+    }
 }
-__global__ void ogc_dequantize_e4m3_kernel(const uint8_t* __restrict__ x, float* __restrict__ out, size_t n, float scale) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    out[i] = __builtin_amdgcn_cvt_f32_fp8((int)x[i], 0) * scale;
+// (vec: x to 4 bytes, out to 16)
+__global__ void __launch_bounds__(256) ogc_dequantize_e4m3_kernel(const uint8_t* __restrict__ x, float* __restrict__ out, size_t n,
+                                                                  float scale, int vec) {
+    const size_t i0 = ((size_t)blockIdx.x * OGC_CONVERT_GROUPS * 256 + threadIdx.x) * 4;
+    uint32_t q[OGC_CONVERT_GROUPS];
+#pragma unroll
+    for (int g = 0; g < OGC_CONVERT_GROUPS; ++g) {
+        const size_t i = i0 + g * 1024;
+        q[g] = 0;
+        if (vec && i + 4 <= n) q[g] = *(const uint32_t*)(x + i);
+        else
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (i + j < n) q[g] |= (uint32_t)x[i + j] << (8 * j);
+    }
+#pragma unroll
+    for (int g = 0; g < OGC_CONVERT_GROUPS; ++g) {
+        const size_t i = i0 + g * 1024;
+        const v4f v = {__builtin_amdgcn_cvt_f32_fp8((int)q[g], 0) * scale, __builtin_amdgcn_cvt_f32_fp8((int)q[g], 1) * scale,
+                       __builtin_amdgcn_cvt_f32_fp8((int)q[g], 2) * scale, __builtin_amdgcn_cvt_f32_fp8((int)q[g], 3) * scale};
+        if (vec && i + 4 <= n) *(v4f*)(out + i) = v;
+        else
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (i + j < n) out[i + j] = v[j];
+    }
 }
+static size_t convert_blocks(size_t n) { return (n + 1024 * OGC_CONVERT_GROUPS - 1) / (1024 * OGC_CONVERT_GROUPS); }
 extern "C" int ogc_launch_quantize_e4m3(const float* x, uint8_t* out, size_t n, float inv_scale, void* stream) {
-    const size_t threads = (n + 3) / 4, blocks = (threads + 255) / 256;
+    const size_t blocks = convert_blocks(n);
     if (blocks == 0) return 0;
     if (blocks > 0x7fffffffu) return (int)hipErrorInvalidValue;
-    hipLaunchKernelGGL(ogc_quantize_e4m3_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, x, out, n, inv_scale);
+    const int vec = (((uintptr_t)x & 15) | ((uintptr_t)out & 3)) == 0;
+    hipLaunchKernelGGL(ogc_quantize_e4m3_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, x, out, n, inv_scale, vec);
     return (int)hipGetLastError();
 }
 extern "C" int ogc_launch_dequantize_e4m3(const uint8_t* x, float* out, size_t n, float scale, void* stream) {
-    const size_t blocks = (n + 255) / 256;
+    const size_t blocks = convert_blocks(n);
     if (blocks == 0) return 0;
     if (blocks > 0x7fffffffu) return (int)hipErrorInvalidValue;
-    hipLaunchKernelGGL(ogc_dequantize_e4m3_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, x, out, n, scale);
+    const int vec = (((uintptr_t)x & 3) | ((uintptr_t)out & 15)) == 0;
+    hipLaunchKernelGGL(ogc_dequantize_e4m3_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, x, out, n, scale, vec);
     return (int)hipGetLastError();
 }
 

@@ -143,6 +143,31 @@ def test_quantize_and_dequantize_match_the_oracle_encoding(oracle_mod):
     binding.ogc_quantize_e4m3(0, 0, 0, 1.0)   # nothing to do
 
 
+@pytest.mark.parametrize("n", [1, 3, 4095, 4096, 4099, 4096 * 2 + 1026])
+@pytest.mark.parametrize("off", [0, 1, 2, 4])
+def test_quantize_and_dequantize_tails_and_alignments(oracle_mod, n, off):
+    """Ends inside a group of four, a slice of 1024 and a workgroup's 4096, with tensors that start off the vector accesses'
+    alignment: every element as the oracle encodes it, nothing beyond the end written."""
+    import torch
+
+    rng = np.random.default_rng(n * 8 + off)
+    a = (rng.standard_normal(n + off) * 40).astype(np.float32)
+    a[np.abs(a) < 2.0 ** -60] = 0
+    x = torch.from_numpy(a).cuda()
+    q = torch.full((n + off + 9,), 0xCD, dtype=torch.uint8, device="cuda")
+    binding.ogc_quantize_e4m3(x.data_ptr() + 4 * off, q.data_ptr() + off, n, 0.25)
+    back = torch.full((n + off + 9,), 77.0, dtype=torch.float32, device="cuda")
+    binding.ogc_dequantize_e4m3(q.data_ptr() + off, back.data_ptr() + 4 * off, n, 0.25)
+    torch.cuda.synchronize()
+    got, dq = q.cpu().numpy(), back.cpu().numpy()
+    want = np.array([oracle_mod.oracle.f32_to_e4m3(float(v)) for v in a[off:] * np.float32(4.0)], dtype=np.uint8)
+    assert np.array_equal(got[off:off + n], want)
+    assert (got[:off] == 0xCD).all() and (got[off + n:] == 0xCD).all()
+    wantf = np.array([oracle_mod.oracle.e4m3_to_f32(int(c)) for c in want], dtype=np.float32) * np.float32(0.25)
+    assert np.array_equal(dq[off:off + n], wantf)
+    assert (dq[:off] == 77.0).all() and (dq[off + n:] == 77.0).all()
+
+
 # ---------------------------------------------------------------- one layer, every kernel
 @pytest.mark.parametrize("tile", [0, 1, 2, 3, 4, 5])
 def test_one_layer_every_tile(oracle_mod, tile):
