@@ -692,7 +692,12 @@ ogc_layer_kernel(const OgcLayerArgs a, int tiles_n, int tiles_total, int tiles_p
 // CNT output-channel blocks of one wave at a time: the activation operand read from LDS feeds CNT MFMAs, and
 // the CNT accumulator chains overlap (a single chain would wait out the full MFMA latency at every k-step).
 // stride: distance in channel blocks between a wave's consecutive blocks (the number of waves that share the layer).
-template <int DT, int OUT_PLAIN, int CNT, class YT>
+// The weights are what bounds it: every workgroup streams its share of them from the L2.  The loads run G k-steps ahead
+// of the matrix instructions all the time: a step's registers are loaded again as soon as its instructions have them
+// (8 to 16 KiB of a wave in flight; four steps loaded, waited for and used in turn before: bf16 479-1024-1024-512-256-1
+// at batch 8192 137 -> 62 us, four 1024-wide E4M3 layers 80 -> 70, int8 71 -> 64).  Eight steps of one or two blocks: with
+// four, 512-wide int8 layers had too little in flight (17.0 against 16.5).  G = 0: no more than four steps' loads in flight.
+template <int DT, int OUT_PLAIN, int CNT, int G, class YT>
 OGC_DEV void fused_blocks(const OgcLayerArgs& a, const uint8_t* xin, YT xout, int m0, int nb0, int lane, int stride) {
     const int KP2 = a.KC >> 1;  // 32-byte k-steps
     typename AccT<DT>::type acc[CNT];
@@ -703,46 +708,72 @@ OGC_DEV void fused_blocks(const OgcLayerArgs& a, const uint8_t* xin, YT xout, in
     const uint8_t* wp = a.w + (size_t)nb0 * a.KC * 512 + lane * 16;
     const size_t wstep = (size_t)stride * a.KC * 512;  // this wave's next block is `stride` further
     const uint8_t* xp = xin + lane * 16;
-    int kp = 0;
-    for (; kp + 4 <= KP2; kp += 4) {
-        v4i wf[CNT][4], xf[4];
+    const int groups = G ? KP2 / (G ? G : 1) : 0;
+    if constexpr (G > 0) if (groups > 0) {
+        v4i w[G][CNT];
 #pragma unroll
-        for (int i = 0; i < CNT; ++i)
+        for (int u = 0; u < G; ++u)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) wf[i][u] = *(const v4i*)(wp + i * wstep + (size_t)(kp + u) * 1024);
+            for (int i = 0; i < CNT; ++i) w[u][i] = *(const v4i*)(wp + i * wstep + (size_t)u * 1024);
+        for (int g = 1; g < groups; ++g) {
+            v4i xf[G];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) xf[u] = *(const v4i*)(xp + (size_t)(kp + u) * 1024);
+            for (int u = 0; u < G; ++u) xf[u] = *(const v4i*)(xp + (size_t)((g - 1) * G + u) * 1024);
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < G; ++u) {
 #pragma unroll
-            for (int i = 0; i < CNT; ++i) mma32<DT>(acc[i], wf[i][u], xf[u]);
+                for (int i = 0; i < CNT; ++i) mma32<DT>(acc[i], w[u][i], xf[u]);
+#pragma unroll
+                for (int i = 0; i < CNT; ++i) w[u][i] = *(const v4i*)(wp + i * wstep + (size_t)(g * G + u) * 1024);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        v4i xf[G];
+#pragma unroll
+        for (int u = 0; u < G; ++u) xf[u] = *(const v4i*)(xp + (size_t)((groups - 1) * G + u) * 1024);
+#pragma unroll
+        for (int u = 0; u < G; ++u)
+#pragma unroll
+            for (int i = 0; i < CNT; ++i) mma32<DT>(acc[i], w[u][i], xf[u]);
     }
-    for (; kp < KP2; ++kp) {
-        const v4i xf = *(const v4i*)(xp + (size_t)kp * 1024);
+    auto some = [&](auto steps, int kp) {  // a few k-steps, all their loads in flight at once
+        constexpr int S = decltype(steps)::value;
+        v4i wf[S][CNT], xf[S];
 #pragma unroll
-        for (int i = 0; i < CNT; ++i) mma32<DT>(acc[i], *(const v4i*)(wp + i * wstep + (size_t)kp * 1024), xf);
-    }
+        for (int u = 0; u < S; ++u)
+#pragma unroll
+            for (int i = 0; i < CNT; ++i) wf[u][i] = *(const v4i*)(wp + i * wstep + (size_t)(kp + u) * 1024);
+#pragma unroll
+        for (int u = 0; u < S; ++u) xf[u] = *(const v4i*)(xp + (size_t)(kp + u) * 1024);
+#pragma unroll
+        for (int u = 0; u < S; ++u)
+#pragma unroll
+            for (int i = 0; i < CNT; ++i) mma32<DT>(acc[i], wf[u][i], xf[u]);
+    };
+    int kp = groups * G;  // the rest (G = 0: all): an even number of steps
+    if constexpr (G != 4)
+        for (; kp + 4 <= KP2; kp += 4) some(std::integral_constant<int, 4>(), kp);
+    if (kp < KP2) some(std::integral_constant<int, 2>(), kp);
 #pragma unroll
     for (int i = 0; i < CNT; ++i) epilogue_block<DT, OUT_PLAIN>(acc[i], a, (nb0 + i * stride) * 32, m0, lane, xout);
 }
 
 // One layer of the fused chain for a 32-row tile: wave w of `waves` (the eight of one workgroup, or those of all
 // the workgroups that share the tile) owns the channel blocks w, w + waves, w + 2 waves, ...
-template <int DT, int OUT_PLAIN, class YT>
+template <int DT, int OUT_PLAIN, int G, class YT>
 OGC_DEV void fused_layer(const OgcLayerArgs& a, const uint8_t* xin, YT xout, int m0, int wave, int waves, int lane) {
     const int nblocks = OUT_PLAIN ? ((a.N + 31) >> 5) : a.NB_out;
     for (int nb0 = wave; nb0 < nblocks; nb0 += 4 * waves) {
         const int cnt = (nblocks - nb0 + waves - 1) / waves;  // blocks of this wave from nb0 on
-        if (cnt >= 4) fused_blocks<DT, OUT_PLAIN, 4>(a, xin, xout, m0, nb0, lane, waves);
-        else if (cnt == 3) fused_blocks<DT, OUT_PLAIN, 3>(a, xin, xout, m0, nb0, lane, waves);
-        else if (cnt == 2) fused_blocks<DT, OUT_PLAIN, 2>(a, xin, xout, m0, nb0, lane, waves);
-        else fused_blocks<DT, OUT_PLAIN, 1>(a, xin, xout, m0, nb0, lane, waves);
+        if (cnt >= 4) fused_blocks<DT, OUT_PLAIN, 4, (G > 4 ? 4 : G)>(a, xin, xout, m0, nb0, lane, waves);
+        else if (cnt == 3) fused_blocks<DT, OUT_PLAIN, 3, (G > 4 ? 4 : G)>(a, xin, xout, m0, nb0, lane, waves);
+        else if (cnt == 2) fused_blocks<DT, OUT_PLAIN, 2, G>(a, xin, xout, m0, nb0, lane, waves);
+        else fused_blocks<DT, OUT_PLAIN, 1, G>(a, xin, xout, m0, nb0, lane, waves);
     }
 }
 
-template <int DT>
-__global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_fused_chain_kernel(const OgcChainArgs c) {
-    extern __shared__ __align__(16) uint8_t smem[];
+// DEEP: the k-steps in flight of a wave (fused_blocks).
+template <int DT, int DEEP> OGC_DEV void fused_chain(const OgcChainArgs& c, uint8_t* smem) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // Workgroup b runs on XCD b%8.  A small batch is kept on few XCDs so that their L2s fetch the weights once
     // for all of their workgroups; the workgroups dealt to the other XCDs leave at once.
@@ -767,12 +798,24 @@ __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_fused_chain_kernel(cons
         const uint8_t* xin = (l & 1) ? buf1 : buf0;
         uint8_t* xout = (l & 1) ? buf0 : buf1;
         if (l + 1 < c.n_layers) {
-            fused_layer<DT, 0>(c.layer[l], xin, xout, m0, wave, OGC_FUSED_WAVES, lane);
+            fused_layer<DT, 0, DEEP>(c.layer[l], xin, xout, m0, wave, OGC_FUSED_WAVES, lane);
             __syncthreads();
         } else {
-            fused_layer<DT, 1>(c.layer[l], xin, (uint8_t*)nullptr, m0, wave, OGC_FUSED_WAVES, lane);
+            fused_layer<DT, 1, DEEP>(c.layer[l], xin, (uint8_t*)nullptr, m0, wave, OGC_FUSED_WAVES, lane);
         }
     }
+}
+
+template <int DT> __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_fused_chain_kernel(const OgcChainArgs c) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    fused_chain<DT, 8>(c, smem);
+}
+
+// For two workgroups on a CU: at most 128 registers (the loads of a few k-steps in flight, then none), and the one workgroup's
+// matrix instructions cover the other's loads.
+template <int DT> __global__ void __launch_bounds__(OGC_FUSED_THREADS, 4) ogc_fused_chain_pair_kernel(const OgcChainArgs c) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    fused_chain<DT, 0>(c, smem);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1210,14 +1253,14 @@ __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_cluster_chain_kernel(co
         uint8_t* xout = (l & 1) ? buf0 : buf1;
         if (l + 1 < c.n_layers && ((c.cluster_whole_mask >> l) & 1)) {
             // a layer too small to be worth an exchange: every member computes all of it, as the fused kernel does
-            fused_layer<DT, 0>(a, xin, xout, m0, wave, OGC_FUSED_WAVES, lane);
+            fused_layer<DT, 0, 4>(a, xin, xout, m0, wave, OGC_FUSED_WAVES, lane);
             __syncthreads();
         } else if (l + 1 < c.n_layers) {
             // the tile in blocked layout = its LDS image; a.y is the layer's exchange slot, in which every tile owns a
             // region at a fixed stride (not the layer's own row-block size: a tile two layers ahead of its neighbour
             // must not reach into the neighbour's region)
             uint8_t* ytile = a.y + (size_t)tile * c.cluster_tile_stride;
-            fused_layer<DT, 0>(a, xin, GlobalY{ytile}, m0, vwave, vwaves, lane);
+            fused_layer<DT, 0, 4>(a, xin, GlobalY{ytile}, m0, vwave, vwaves, lane);
             // xout is free until the copy below fills it: its first bytes carry the barrier's verdict
             if (!coop_grid_barrier(ctr, (unsigned long long)(++barriers) * S + c.barrier_extra, c.barrier_budget,
                                    sync + OGC_SYNC_ERR_WORD, (int*)xout, tid))
@@ -1225,7 +1268,7 @@ __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_cluster_chain_kernel(co
             copy_tile_coherent(xout, ytile, a.KC_out * 32, tid);
             __syncthreads();
         } else {
-            fused_layer<DT, 1>(a, xin, (uint8_t*)nullptr, m0, vwave, vwaves, lane);
+            fused_layer<DT, 1, 4>(a, xin, (uint8_t*)nullptr, m0, vwave, vwaves, lane);
         }
     }
     // the last member out resets its tile's counters for the next run (by then nobody waits on them)
@@ -1531,16 +1574,25 @@ extern "C" size_t ogc_fused_lds_limit(void) { return 160 * 1024; }
 extern "C" int ogc_fused_threads(void) { return OGC_FUSED_THREADS; }
 
 template <int DT> static int launch_fused_t(const OgcChainArgs* c, int m_blocks, hipStream_t stream) {
-    auto kern = ogc_fused_chain_kernel<DT>;
     const size_t lds = (size_t)2 * c->lds_buf_bytes;
+    // More row tiles than CUs, and room for two workgroups in a CU's LDS: the kernel of which two fit the registers as well.
+    // us with the deep kernel -> the pair, bf16: 64x4 at batch 16384 12.0 -> 10.4, 13-512-256-128-64 at 32768 38.6 -> 35.5 (E4M3:
+    // 11.8 -> 10.1 and 39.7 -> 36.2; fp32 64x4: 17.9 -> 16.7); up to 256 tiles a CU has one workgroup whichever it is.
+    // Not int8: its epilogue takes more registers, the pair spills (256x4 at 16384: 17.6 -> 25.4).
+    auto kern = ogc_fused_chain_kernel<DT>;
+    bool pair = false;
+    if constexpr (DT != OGC_I8) {
+        pair = m_blocks > 256 && 2 * lds <= ogc_fused_lds_limit();
+        if (pair) kern = ogc_fused_chain_pair_kernel<DT>;
+    }
     {   // the limit only ever grows; the lock keeps raising it and remembering it together
         static std::mutex mu;
-        static size_t attr_max = 0;
+        static size_t attr_max[2] = {0, 0};
         std::lock_guard<std::mutex> hold(mu);
-        if (lds > attr_max) {
+        if (lds > attr_max[pair]) {
             hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return (int)e;
-            attr_max = lds;
+            attr_max[pair] = lds;
         }
     }
     OgcChainArgs args = *c;

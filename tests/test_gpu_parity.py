@@ -123,6 +123,17 @@ def test_fused_ragged(oracle_mod, dtype):
     check(wl, "fused", oracle_mod)
 
 
+@pytest.mark.parametrize("dims", [[32, 96, 64], [96, 288, 160, 32], [224, 544, 800, 40], [480, 1060, 33]])
+@pytest.mark.parametrize("dtype", ["i8", "bf16", "f32"])
+def test_fused_k_steps_and_blocks(oracle_mod, dtype, dims):
+    """Reduction axes of every remainder of the loads in flight (fewer steps than are in flight, whole turns of four and
+    eight, two, four and six more), with one to five channel blocks to a wave; and more row tiles than CUs where the launch
+    takes two workgroups to a CU (the two narrow chains, one ragged tile beyond 256)."""
+    check(synth.make_mlp(dtype, 45, dims, [RELU] * (len(dims) - 1), seed=620, name="ksteps"), "fused", oracle_mod)
+    if max(dims) < 300:
+        check(synth.make_mlp(dtype, 8192 + 33, dims, [RELU] * (len(dims) - 1), seed=621, name="pairs"), "fused", oracle_mod)
+
+
 @pytest.mark.parametrize("mode", ["fused", "per_layer"])
 def test_reduced_cfg4_and_cfg5(oracle_mod, mode):
     check(synth.make_config(4, m=160), "per_layer", oracle_mod, tile=1)   # hidden 4096 does not fit the fused kernel
