@@ -123,7 +123,7 @@ def test_fused_ragged(oracle_mod, dtype):
     check(wl, "fused", oracle_mod)
 
 
-@pytest.mark.parametrize("dims", [[32, 96, 64], [96, 288, 160, 32], [224, 544, 608, 40], [480, 1060, 33]])
+@pytest.mark.parametrize("dims", [[32, 96, 64], [96, 288, 160, 32], [224, 544, 608, 40], [480, 352, 1060]])
 @pytest.mark.parametrize("dtype", ["i8", "bf16", "f32"])
 def test_fused_k_steps_and_blocks(oracle_mod, dtype, dims):
     """Reduction axes of every remainder of the loads in flight (fewer steps than are in flight, whole turns of four and
