@@ -251,6 +251,7 @@ typedef __attribute__((address_space(3))) v2i mha8_lds_v2i;
 constexpr int MHA8_UNIT = 64;        // keys per unit: two groups of 32
 constexpr int MHA8_LDS_KEYS = 4096;  // addends held in LDS; longer sequences replace them every 64 units
 constexpr int MHA8_SLOTS = 3;        // units of keys, and of values, in LDS: one in use, two on their way
+constexpr float MHA8_NEAR = 8192.0f; // scores (base-2 domain) that may go without an addend
 
 template <int D32> struct Mha8 {
     static constexpr int D = D32 * 32, CH = D / 16;  // bytes and 16-byte pieces of a row
@@ -277,7 +278,14 @@ template <int N> MHA8_DEV void mha8_wait_and_meet() {  // all but the N newest l
 //     read (ds_read_b64_tr_b8: 8 keys x 16 channels per 16 lanes, the keys' rows chosen by the lanes' addresses);
 //   * a group of 32 keys whose mask entries are all zero (most of them) takes its maximum over the integer scores, two
 //     per instruction, and needs no addend per score: the scale is positive, so the order is the same; the multiply by
-//     127 and the row maximum ride in the exponent's multiply-add (2^(x + log2 127) is 127 * 2^x);
+//     127 and the row maximum ride in the exponent's multiply-add (2^(x + log2 127) is 127 * 2^x).  log2(127) - maximum is
+//     one fp32 value, rounded at the maximum's magnitude, so this form is kept to scores below 2^13 (MHA8_NEAR): there it
+//     is off by 2^-11 at most, a numerator cannot pass 127.1, and over whole rows as many numerators round apart from
+//     exact ones as by the definition's order (512 keys near the top of the range: 2.9e-3 and 3.5e-3 of them at 2^13,
+//     9e-5 and 1e-4 at 264, where scales of 4 / 127 end);
+//   * all other groups go by the definition's order, the plain kernel's: the score with its mask, minus the maximum,
+//     exponentiated, times 127.  The difference is exact at the maximum, whatever its size, so a row that is masked alike
+//     has numerators of at most 127 too (a byte of 128 and more is negative to the matrix instruction);
 //   * a unit whose mask entries are so low that no int8 product can make up for it is left out of both passes: its
 //     numerators round to zero whatever q and k hold.  With |S| <= 16384 d, and some key's mask 0 or more, key j has none
 //     if mask[j] + 2 * 16384 d c1 + 16 < 0 (base-2 domain; a numerator is zero from 2^-8 on).
@@ -317,6 +325,8 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
     // per unit: bits 0, 1: groups with a nonzero addend; bit 2: an addend that counts beside one of 0 or more; bit 3: one of those
     mha8_lds_u32* const kinds = (mha8_lds_u32*)(add + add_keys);
     const float floor = a.c1 > 0.0f ? -(2.0f * 16384.0f * D * a.c1 + 16.0f) : -INFINITY;
+    // a scale that is not positive does not keep the order of the scores, a large one not the precision of the short form
+    const bool near = a.c1 > 0.0f && 16384.0f * D * a.c1 <= MHA8_NEAR;
     auto fill = [&](int first, int count) {  // keys first .. first + count - 1 (whole units, at most MHA8_LDS_KEYS)
         const float* mrow = a.mask + (long long)b * S;
 #pragma unroll 1
@@ -346,7 +356,7 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
         const uint32_t kd = lane < n ? kinds[lane] : 0u;
         odd0 = __builtin_amdgcn_ballot_w64((kd & 1) != 0);
         odd1 = __builtin_amdgcn_ballot_w64((kd & 2) != 0);
-        if (!(a.c1 > 0.0f)) odd0 = odd1 = ~0ull;  // a scale that is not positive does not keep the order of the scores
+        if (!near) odd0 = odd1 = ~0ull;
         const bool bounded = __builtin_amdgcn_ballot_w64((kd & 8) != 0) != 0;  // the row maximum is that of a score at least
         counts = __builtin_amdgcn_ballot_w64(lane < n && (!bounded || (kd & 4) != 0));
     };
@@ -409,7 +419,7 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
 #pragma unroll 1
         for (int i = 0; i < 2; ++i) issue();
         if (known) break;
-        if (!a.mask && a.c1 > 0.0f) {  // every unit counts, and only the last can have addends (read behind later barriers)
+        if (!a.mask && near) {  // every unit counts, and only the last can have addends (read behind later barriers)
             odd0 = S - (n - 1) * MHA8_UNIT < 32 ? 1ull << (n - 1) : 0;
             odd1 = S % MHA8_UNIT ? 1ull << (n - 1) : 0;
             if (S % MHA8_UNIT && tid < MHA8_UNIT) add[(n - 1) * MHA8_UNIT + tid] = (n - 1) * MHA8_UNIT + tid < S ? 0.0f : -INFINITY;
@@ -489,7 +499,8 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
         u = next_unit(u);
     }
     if (imax != -2147483647 - 1) fmx = fmaxf(fmx, (float)imax * a.c1);
-    const float k0 = 6.98868468677216586f - fmaxf(fmx, other_half_f(fmx));  // log2(127) - the row maximum (finite: key 0 exists)
+    const float row_max = fmaxf(fmx, other_half_f(fmx));  // finite: key 0 exists
+    const float k0 = 6.98868468677216586f - row_max;      // log2(127) - the maximum
 
     // ---- pass 2: numerators, quantized, and the second product
     v16i oacc[D32];
@@ -526,10 +537,12 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
                     uint32_t w = 0;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        float off = k0;
-                        if constexpr (decltype(with_mask_c)::value) off = mk[q][e] + k0;
-                        // in [0, 127]; a key past the end: 0; round to nearest even
-                        w = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_exp2f(__builtin_fmaf((float)s[g][4 * q + e], a.c1, off)), e, w);
+                        float x;  // in [0, 127]; a key past the end: 0
+                        if constexpr (decltype(with_mask_c)::value)
+                            x = __builtin_amdgcn_exp2f(__builtin_fmaf((float)s[g][4 * q + e], a.c1, mk[q][e]) - row_max) * 127.0f;
+                        else
+                            x = __builtin_amdgcn_exp2f(__builtin_fmaf((float)s[g][4 * q + e], a.c1, k0));
+                        w = __builtin_amdgcn_cvt_pk_u8_f32(x, e, w);  // round to nearest even
                     }
                     dw[q] = w;
                     row_sum = __builtin_amdgcn_sad_u8(w, 0u, row_sum);  // + the four bytes

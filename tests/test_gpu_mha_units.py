@@ -143,6 +143,70 @@ def test_i8_units_that_do_not_count(oracle_mod, head_dim):
     check_i8(oracle_mod, wl)
 
 
+def i8_in_fp32(wl, use_mask=True):
+    """The definition with its scores in fp32 and base 2, as every implementation here forms them: product, mask and maximum each
+    rounded once.  Against float64 scores this matters where a row's largest addend is so low that fp32 spaces the scores."""
+    q, k, v = (heads_view(t, wl).astype(np.float64) for t in (wl.q, wl.k, wl.v))  # (whole numbers far below 2^53: exact)
+    s = np.matmul(q, np.swapaxes(k, -1, -2))
+    qs, ks, vs, os = (np.float32(x) for x in wl.quant)
+    c1 = ((qs * ks) * np.float32(wl.scale)) * np.float32(1.44269504088896340736)
+    m = (wl.mask * np.float32(1.44269504088896340736))[:, None, None, :] if use_mask else np.zeros((1, 1, 1, 1), np.float32)
+    t = (s * np.float64(c1) + m.astype(np.float64)).astype(np.float32)
+    e = np.exp2((t - t.max(-1, keepdims=True)).astype(np.float64)).astype(np.float32)
+    p = np.rint(e * np.float32(127.0)).astype(np.float64)
+    assert p.max() == 127
+    r = (np.matmul(p, v).astype(np.float32) / p.sum(-1, keepdims=True).astype(np.float32)) * (vs / os)
+    return np.clip(np.rint(r), -128, 127).astype(np.int32)
+
+
+def check_i8_in_fp32(wl, use_mask=True):
+    """The same gate as check_i8."""
+    from paper_2301_01333_amd.harness import DeviceMHA
+
+    dev = DeviceMHA(wl, STABLE, use_mask)
+    dev.run()
+    got = dev.result().astype(np.int32)
+    diff = np.abs(got - i8_in_fp32(wl, use_mask).transpose(0, 2, 1, 3).reshape(got.shape))
+    assert diff.max() <= 1, "%s: an output differs by %d steps" % (wl.name, int(diff.max()))
+    assert (diff > 0).mean() < 0.01, "%s: %.3f %% of the outputs differ" % (wl.name, 100.0 * (diff > 0).mean())
+
+
+@pytest.mark.parametrize("level", [-1.0e4, -65504.0, -1.0e5, -1.0e6, -1.0e9, -1.0e30, 1.0e5])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_i8_rows_masked_alike(head_dim, level):
+    """Every key of a batch entry carries the same addend, however low: the maximum comes off exactly, and no numerator passes 127
+    (128 is negative to the matrix instruction).  Then all keys but a few, which stand above the others by a step of fp32."""
+    wl = i8_case(2, 384, head_dim, 8350 + head_dim, "i8 rows alike at %g" % level)
+    wl.mask[:] = 0.0
+    wl.mask[1] = level
+    check_i8_in_fp32(wl)
+    wl.mask[1, 5::97] = np.nextafter(np.float32(level), np.float32(np.inf))
+    check_i8_in_fp32(wl)
+
+
+@pytest.mark.parametrize("scale", [1.0, 4.0, 64.0])
+def test_i8_scales_of_either_form_of_the_numerators(scale):
+    """Scores up to 2^13 in base 2 take the short form without an addend, larger ones the definition's order."""
+    for head_dim in (64, 128):
+        wl = i8_case(2, 333, head_dim, 8450 + head_dim, "i8 scale %g" % scale)
+        wl.scale = scale
+        check_i8_in_fp32(wl)
+        check_i8_in_fp32(wl, use_mask=False)
+
+
+@pytest.mark.parametrize("head_dim", [32, 64])
+@pytest.mark.parametrize("seq", [31, 64, 65, 128, 197])
+def test_i8_short_sequences_of_wide_batches(seq, head_dim):
+    """The streaming kernel's other way in: few units (one, at the shortest), many query tiles."""
+    tiles = (seq + 127) // 128
+    batch = (131072 + 2 * tiles * seq - 1) // (2 * tiles * seq)
+    wl = i8_case(batch, seq, head_dim, 8600 + seq + head_dim, "i8 short S=%d d=%d" % (seq, head_dim))
+    check_i8_in_fp32(wl)
+    check_i8_in_fp32(wl, use_mask=False)
+    wl.mask[::3] = -1.0e6
+    check_i8_in_fp32(wl)
+
+
 @pytest.mark.parametrize("scale", [-0.125, 0.0])
 def test_i8_scales_that_do_not_keep_the_order(oracle_mod, scale):
     wl = i8_case(1, 333, 64, 8400, "i8 scale %g" % scale)
