@@ -76,7 +76,10 @@ ogc_status ogc_mha_run(const ogc_mha_desc* desc, const void* q, const void* k, c
  * mask), as a profiler's kernel trace prints it (static storage), or NULL for an invalid description.  A run
  * without a mask whose sequence is a whole number of key blocks (bf16: 64, fp32: 32) and whose scale is
  * positive takes a variant that spends no per-key addend; bf16 with head_dim <= 64 and seq >= 256 takes one in
- * which a wavefront owns 64 queries instead of 32 (the last template argument; desc->query_groups forces either). */
+ * which a wavefront owns 64 queries instead of 32 (the last template argument; desc->query_groups forces either).
+ * bf16 has two bodies, one that streams keys and values into LDS and one that stages them in registers: ogc_mha_kernel
+ * streams up to 96 channels and stages 128, ogc_mha_general_kernel stages up to 96 (short sequences, scales that are not
+ * positive or extreme, token strides of 2^26 bytes and more) and ogc_mha_stream_kernel streams 128 (large launches). */
 const char* ogc_mha_kernel_name(const ogc_mha_desc* desc, int32_t has_mask);
 
 /* Quantization scales of the Int8 attention: real value = scale * integer, zero point 0 for all four tensors

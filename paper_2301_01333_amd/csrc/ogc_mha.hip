@@ -21,7 +21,6 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
-#include <atomic>
 #include <type_traits>
 
 #include "ogc_mha.h"
@@ -71,19 +70,34 @@ MHA_DEV uint32_t pack_bf16(float lo, float hi) {  // round to nearest even, two 
 // n / d; m = floor(2^32 / d) + 1 where that is exact for every n in use (n * d < 2^32, and d > 1), else 0
 MHA_DEV uint32_t div_magic(uint32_t n, uint32_t d, uint32_t m) { return m ? __umulhi(n, m) : n / d; }
 
+// a mask of finite values stays finite when it is scaled (-infinity is for keys beyond the sequence); NaN passes
+MHA_DEV float finite_mask(float x, float most) { return x == x ? __builtin_fminf(__builtin_fmaxf(x, -most), most) : x; }
+
 #include "ogc_mha_bf16.h"
 
-constexpr int MHA_F32_KEYS = 32;    // keys per block of the fp32 body
-constexpr int MHA_BF16_WHOLE = 64;  // a bf16 sequence of whole blocks of this many keys without a mask needs no addend
+template <int DT> struct MhaCfg;
+template <> struct MhaCfg<OGC_BF16> {
+    static constexpr int E = 2, KB = 64;
+};
+template <> struct MhaCfg<OGC_F32> {
+    static constexpr int E = 4, KB = 32;
+};
 
-// The fp32 body.  PLAIN: no mask, whole key blocks and a positive scalar, so no key needs an addend.
-template <int D32, int FAST, int PLAIN> MHA_DEV void mha_f32_body(const MhaArgs& a) {
-    constexpr int KB = MHA_F32_KEYS, D = D32 * 32;
-    constexpr int KSTR = D * 4 + 16;   // bytes per key row of K in LDS (padded)
-    constexpr int VSTR = KB * 4 + 16;  // bytes per channel row of V^T in LDS (padded)
-    constexpr int CH = D * 4 / 16;     // 16-byte chunks per token row
-    constexpr int KU = KB * CH / 256;  // 16-byte chunks of K per thread
-    constexpr int VU = D32;            // chunks of V per thread
+// The staged body: keys and values through registers, blocks of 64 (bf16) or 32 (fp32) keys.  It serves fp32, bf16 heads of
+// 128 channels, and the bf16 calls that the streaming body does not take (stream_case below).
+// DT: OGC_F32 / OGC_BF16.  D32 = head_dim / 32.  FAST: softmax without the running maximum.  PLAIN: no mask, the
+// sequence is a whole number of key blocks and the scalar is positive, so no key needs an addend.
+// QS: 32-query groups per wavefront (1 or 2).  With 2, every key / value operand read from LDS feeds two matrix
+// instructions (one per group): the bf16 form is bound by LDS reads, one KiB per instruction, otherwise.
+template <int DT, int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_staged_body(const MhaArgs& a) {
+    constexpr int E = MhaCfg<DT>::E, KB = MhaCfg<DT>::KB, D = D32 * 32;
+    constexpr int SB = KB / 32;                 // 32-key sub-blocks per block
+    constexpr int KSTR = D * E + 16;            // bytes per key row of K in LDS (padded)
+    constexpr int VSTR = KB * E + 16;           // bytes per channel row of V^T in LDS (padded)
+    constexpr int CH = D * E / 16;              // 16-byte chunks per token row
+    constexpr int KU = KB * CH / 256;                          // 16-byte chunks of K per thread
+    constexpr int KP = KB / 2;                                 // bf16: key pairs per block
+    constexpr int VU = DT == OGC_BF16 ? (KP * CH + 255) / 256 : D32;  // V units per thread (bf16: a unit is two keys)
     __shared__ __attribute__((aligned(16))) uint8_t k_lds[KB * KSTR];
     __shared__ __attribute__((aligned(16))) uint8_t vt_lds[D * VSTR];
     __shared__ __attribute__((aligned(16))) float m_lds[KB];
@@ -99,29 +113,33 @@ template <int D32, int FAST, int PLAIN> MHA_DEV void mha_f32_body(const MhaArgs&
         qt = blockIdx.x % a.q_tiles;
     }
     const int b = bh / a.heads, hd = bh % a.heads, S = a.seq;
-    const uint8_t* kbase = a.k + (b * a.sk[0] + hd * a.sk[1]) * 4;
-    const uint8_t* vbase = a.v + (b * a.sv[0] + hd * a.sv[1]) * 4;
-    const long long kss = a.sk[2] * 4, vss = a.sv[2] * 4;
+    const uint8_t* kbase = a.k + (b * a.sk[0] + hd * a.sk[1]) * E;
+    const uint8_t* vbase = a.v + (b * a.sv[0] + hd * a.sv[1]) * E;
+    const long long kss = a.sk[2] * E, vss = a.sv[2] * E;
 
     // ---- this lane's query row as the second MFMA operand, resident for the whole kernel
-    constexpr int QN = D / 8;
-    const int query = (qt * 4 + wave) * 32 + col;
-    v4i qreg[QN];
-    v16f oacc[D32];
-    float run_max = -INFINITY, run_sum = 0.0f;  // run_sum: this lane's keys only, halves are added at the end
-    {
-        const int qrow = query < S ? query : S - 1;
-        const uint8_t* qp = a.q + (b * a.sq[0] + hd * a.sq[1] + qrow * a.sq[2]) * 4;
+    constexpr int QN = DT == OGC_BF16 ? D / 16 : D / 8;
+    int query[QS];
+    v4i qreg[QS][QN];
+    v16f oacc[QS][D32];
+    float run_max[QS], run_sum[QS];  // run_sum: this lane's keys only, halves are added at the end
 #pragma unroll
-        for (int i = 0; i < QN; ++i) qreg[i] = *(const v4i*)(qp + i * 32 + h * 16);
+    for (int qs = 0; qs < QS; ++qs) {
+        query[qs] = (qt * 4 + wave) * (32 * QS) + qs * 32 + col;
+        const int qrow = query[qs] < S ? query[qs] : S - 1;
+        const uint8_t* qp = a.q + (b * a.sq[0] + hd * a.sq[1] + qrow * a.sq[2]) * E;
+#pragma unroll
+        for (int i = 0; i < QN; ++i) qreg[qs][i] = *(const v4i*)(qp + i * 32 + h * 16);
 #pragma unroll
         for (int d = 0; d < D32; ++d)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[d][r] = 0.0f;
+            for (int r = 0; r < 16; ++r) oacc[qs][d][r] = 0.0f;
+        run_max[qs] = -INFINITY;
+        run_sum[qs] = 0.0f;
     }
 
     // ---- prefetch registers for one block of keys / values / mask
-    v4i kreg[KU], vreg[VU];
+    v4i kreg[KU], vreg[VU][DT == OGC_BF16 ? 2 : 1];
     float mreg = 0.0f;   // the mask value as loaded; scaled when it is written to LDS (scaling here would wait for the load,
                          // and with it for every key / value load issued just before)
     bool mpad = false;   // the key lies beyond the sequence
@@ -132,10 +150,20 @@ template <int D32, int FAST, int PLAIN> MHA_DEV void mha_f32_body(const MhaArgs&
             const int u = tid + 256 * i, key = key0 + u / CH, part = u % CH;
             kreg[i] = (full || key < S) ? *(const v4i*)(kbase + key * kss + part * 16) : (v4i){0, 0, 0, 0};
         }
+        if constexpr (DT == OGC_BF16) {
 #pragma unroll
-        for (int i = 0; i < VU; ++i) {
-            const int u = tid + 256 * i, key = key0 + (u & 31), c = u >> 5;
-            vreg[i] = (full || key < S) ? *(const v4i*)(vbase + key * vss + c * 16) : (v4i){0, 0, 0, 0};
+            for (int i = 0; i < VU; ++i) {
+                const int u = tid + 256 * i, kp = u % KP, c = u / KP, key = key0 + 2 * kp;
+                const bool on = (KP * CH) % 256 == 0 || 256 * (i + 1) <= KP * CH || c < CH;
+                vreg[i][0] = (on && (full || key < S)) ? *(const v4i*)(vbase + key * vss + c * 16) : (v4i){0, 0, 0, 0};
+                vreg[i][1] = (on && (full || key + 1 < S)) ? *(const v4i*)(vbase + (key + 1) * vss + c * 16) : (v4i){0, 0, 0, 0};
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < VU; ++i) {
+                const int u = tid + 256 * i, key = key0 + (u & 31), c = u >> 5;
+                vreg[i][0] = (full || key < S) ? *(const v4i*)(vbase + key * vss + c * 16) : (v4i){0, 0, 0, 0};
+            }
         }
         if (tid < KB) {
             const int key = key0 + tid;
@@ -150,11 +178,29 @@ template <int D32, int FAST, int PLAIN> MHA_DEV void mha_f32_body(const MhaArgs&
             const int u = tid + 256 * i;
             *(v4i*)(k_lds + (u / CH) * KSTR + (u % CH) * 16) = kreg[i];
         }
+        if constexpr (DT == OGC_BF16) {
+            // two keys x eight channels per unit -> eight dwords (key, key+1) at the permuted key position:
+            // within a group of 16 keys, key offset 8*gg + 4*hh + e sits at 8*hh + 4*gg + e
 #pragma unroll
-        for (int i = 0; i < VU; ++i) {
-            const int u = tid + 256 * i, kl = u & 31, c = u >> 5;
+            for (int i = 0; i < VU; ++i) {
+                const int u = tid + 256 * i, kp = u % KP, c = u / KP, o = (2 * kp) & 15;
+                const int pos = ((2 * kp) & ~15) + ((o & 3) | ((o & 8) >> 1) | ((o & 4) << 1));
+                if (c < CH) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) *(int*)(vt_lds + (4 * c + j) * VSTR + kl * 4) = vreg[i][j];
+                    for (int j = 0; j < 8; ++j) {
+                        const uint32_t lo = (uint32_t)vreg[i][0][j >> 1], hi = (uint32_t)vreg[i][1][j >> 1];
+                        const uint32_t w = __builtin_amdgcn_perm(hi, lo, (j & 1) ? 0x07060302u : 0x05040100u);
+                        *(uint32_t*)(vt_lds + (8 * c + j) * VSTR + pos * 2) = w;
+                    }
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < VU; ++i) {
+                const int u = tid + 256 * i, kl = u & 31, c = u >> 5;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) *(int*)(vt_lds + (4 * c + j) * VSTR + kl * 4) = vreg[i][0][j];
+            }
         }
         if (tid < KB) m_lds[tid] = mpad ? -INFINITY : mreg * LOG2E;
     };
@@ -168,202 +214,273 @@ template <int D32, int FAST, int PLAIN> MHA_DEV void mha_f32_body(const MhaArgs&
         if (kb + 1 < nkb) prefetch((kb + 1) * KB);
 
         // ---- scores, transposed: rows = keys, columns = queries
-        v16f sacc;
+        v16f sacc[QS][SB];
         {
+            // bf16: the operand reads of a 32-key group go out before its first matrix instruction (the compiler
+            // would otherwise issue each read just ahead of its use and wait for it)
             const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-            const uint8_t* krow = k_lds + col * KSTR + h * 16;
 #pragma unroll
-            for (int i = 0; i < QN; ++i) {
-                const v4f kf = *(const v4f*)(krow + i * 32), qf = __builtin_bit_cast(v4f, qreg[i]);
-                sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, qf.x, i ? sacc : zero, 0, 0, 0);
-                sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, qf.y, sacc, 0, 0, 0);
-                sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, qf.z, sacc, 0, 0, 0);
-                sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, qf.w, sacc, 0, 0, 0);
+            for (int sb = 0; sb < SB; ++sb) {
+                const uint8_t* krow = k_lds + (sb * 32 + col) * KSTR + h * 16;
+                v4i kfrag[QN];
+                if constexpr (DT == OGC_BF16) {
+#pragma unroll
+                    for (int i = 0; i < QN; ++i) kfrag[i] = *(const v4i*)(krow + i * 32);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int i = 0; i < QN; ++i)
+#pragma unroll
+                    for (int qs = 0; qs < QS; ++qs) {
+                        const v4i kv = DT == OGC_BF16 ? kfrag[i] : *(const v4i*)(krow + i * 32);
+                        if constexpr (DT == OGC_BF16) {
+                            sacc[qs][sb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                __builtin_bit_cast(v8bf, kv), __builtin_bit_cast(v8bf, qreg[qs][i]), i ? sacc[qs][sb] : zero, 0, 0, 0);
+                        } else {
+                            const v4f kf = __builtin_bit_cast(v4f, kv), qf = __builtin_bit_cast(v4f, qreg[qs][i]);
+                            sacc[qs][sb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, qf.x, i ? sacc[qs][sb] : zero, 0, 0, 0);
+                            sacc[qs][sb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, qf.y, sacc[qs][sb], 0, 0, 0);
+                            sacc[qs][sb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, qf.z, sacc[qs][sb], 0, 0, 0);
+                            sacc[qs][sb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, qf.w, sacc[qs][sb], 0, 0, 0);
+                        }
+                    }
             }
         }
         // ---- scalar, mask, running maximum (base-2 logarithm domain; a key beyond the sequence carries
         // -infinity).  A block of valid keys without a mask needs no per-key addend: the maximum is taken on
         // the raw products and the scalar rides in the exponent's multiply-add.
         const float c = a.scale_log2;
-        float cand = -INFINITY;
-        if constexpr (PLAIN) {
-            if constexpr (!FAST) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) cand = fmaxf(cand, sacc[r]);
-                cand *= c;
-            }
-        } else {
+        for (int qs = 0; qs < QS; ++qs) {
+            float cand = -INFINITY;
+            if constexpr (PLAIN) {
+                if constexpr (!FAST) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const v4f mk = *(const v4f*)(m_lds + 8 * g + 4 * h);
+                    for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float t = __builtin_fmaf(sacc[4 * g + e], c, mk[e]);
-                    sacc[4 * g + e] = t;
-                    if constexpr (!FAST) cand = fmaxf(cand, t);
+                        for (int r = 0; r < 16; ++r) cand = fmaxf(cand, sacc[qs][sb][r]);
+                    cand *= c;
                 }
+            } else {
+#pragma unroll
+                for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const v4f mk = *(const v4f*)(m_lds + sb * 32 + 8 * g + 4 * h);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float t = __builtin_fmaf(sacc[qs][sb][4 * g + e], c, mk[e]);
+                            sacc[qs][sb][4 * g + e] = t;
+                            if constexpr (!FAST) cand = fmaxf(cand, t);
+                        }
+                    }
             }
-        }
-        float off = 0.0f;
-        if constexpr (!FAST) {
-            // The reference point of the exponentials only has to be NEAR the maximum: it moves when a block
-            // exceeds it by more than 2^8, so most blocks skip the rescaling of the output accumulators.  The
-            // result is the same function (numerator and denominator carry the same factor); weights reach
-            // 256 at most, far from any overflow.  Key 0 of block 0 is always valid: the first block sets it.
-            cand = fmaxf(cand, other_half(cand));
-            const bool need = cand > run_max + 8.0f;
-            if (__builtin_amdgcn_ballot_w64(need) != 0) {
-                const float new_max = need ? cand : run_max;
-                const float alpha = __builtin_amdgcn_exp2f(run_max - new_max);
-                run_max = new_max;
-                run_sum *= alpha;
+            float off = 0.0f;
+            if constexpr (!FAST) {
+                // The reference point of the exponentials only has to be NEAR the maximum: it moves when a block
+                // exceeds it by more than 2^8, so most blocks skip the rescaling of the output accumulators.  The
+                // result is the same function (numerator and denominator carry the same factor); weights reach
+                // 256 at most, far from any overflow.  Key 0 of block 0 is always valid: the first block sets it.
+                cand = fmaxf(cand, other_half(cand));
+                const bool need = cand > run_max[qs] + 8.0f;
+                if (__builtin_amdgcn_ballot_w64(need) != 0) {
+                    const float new_max = need ? cand : run_max[qs];
+                    const float alpha = __builtin_amdgcn_exp2f(run_max[qs] - new_max);
+                    run_max[qs] = new_max;
+                    run_sum[qs] *= alpha;
 #pragma unroll
-                for (int d = 0; d < D32; ++d)
+                    for (int d = 0; d < D32; ++d)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) oacc[d][r] *= alpha;
+                        for (int r = 0; r < 16; ++r) oacc[qs][d][r] *= alpha;
+                }
+                off = -run_max[qs];
             }
-            off = -run_max;
-        }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float x;
-            if constexpr (PLAIN) x = __builtin_fmaf(sacc[r], c, off);
-            else x = FAST ? sacc[r] : sacc[r] + off;
-            sacc[r] = __builtin_amdgcn_exp2f(x);
+            for (int sb = 0; sb < SB; ++sb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    float x;
+                    if constexpr (PLAIN) x = __builtin_fmaf(sacc[qs][sb][r], c, off);
+                    else x = FAST ? sacc[qs][sb][r] : sacc[qs][sb][r] + off;
+                    sacc[qs][sb][r] = __builtin_amdgcn_exp2f(x);
+                }
         }
         // ---- O^T += V^T P^T
+        if constexpr (DT == OGC_BF16) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) run_sum += sacc[r];
+            for (int sb = 0; sb < SB; ++sb)
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+                for (int j = 0; j < 2; ++j) {
+                    // the row sum takes the weights as rounded, the values the second product multiplies
+                    v4i pw[QS];
 #pragma unroll
-            for (int d = 0; d < D32; ++d) {
-                const v4f vv = *(const v4f*)(vt_lds + (d * 32 + col) * VSTR + (8 * g + 4 * h) * 4);
-                oacc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.x, sacc[4 * g], oacc[d], 0, 0, 0);
-                oacc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.y, sacc[4 * g + 1], oacc[d], 0, 0, 0);
-                oacc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.z, sacc[4 * g + 2], oacc[d], 0, 0, 0);
-                oacc[d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.w, sacc[4 * g + 3], oacc[d], 0, 0, 0);
-            }
+                    for (int qs = 0; qs < QS; ++qs) {
+                        const v16f& p = sacc[qs][sb];
+                        uint32_t w[4];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const v2bf pr = {(__bf16)p[8 * j + 2 * t], (__bf16)p[8 * j + 2 * t + 1]};
+                            run_sum[qs] = __builtin_amdgcn_fdot2_f32_bf16(pr, (v2bf){(__bf16)1.0f, (__bf16)1.0f}, run_sum[qs], false);
+                            w[t] = __builtin_bit_cast(uint32_t, pr);
+                        }
+                        pw[qs] = (v4i){(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+                    }
+#pragma unroll
+                    for (int d = 0; d < D32; ++d) {
+                        const v4i vv = *(const v4i*)(vt_lds + (d * 32 + col) * VSTR + (sb * 32 + 16 * j + 8 * h) * 2);
+#pragma unroll
+                        for (int qs = 0; qs < QS; ++qs)
+                            oacc[qs][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, vv),
+                                                                                  __builtin_bit_cast(v8bf, pw[qs]), oacc[qs][d], 0, 0, 0);
+                    }
+                }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+#pragma unroll
+                for (int qs = 0; qs < QS; ++qs) run_sum[qs] += sacc[qs][0][r];
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+#pragma unroll
+                for (int d = 0; d < D32; ++d) {
+                    const v4f vv = *(const v4f*)(vt_lds + (d * 32 + col) * VSTR + (8 * g + 4 * h) * 4);
+#pragma unroll
+                    for (int qs = 0; qs < QS; ++qs) {
+                        oacc[qs][d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.x, sacc[qs][0][4 * g], oacc[qs][d], 0, 0, 0);
+                        oacc[qs][d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.y, sacc[qs][0][4 * g + 1], oacc[qs][d], 0, 0, 0);
+                        oacc[qs][d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.z, sacc[qs][0][4 * g + 2], oacc[qs][d], 0, 0, 0);
+                        oacc[qs][d] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv.w, sacc[qs][0][4 * g + 3], oacc[qs][d], 0, 0, 0);
+                    }
+                }
+        }
     }
 
     // ---- normalise and store: after the half exchange a lane holds 16 consecutive channels of its query
-    const float total = run_sum + other_half(run_sum);
-    const float inv = 1.0f / total;
-    uint8_t* op = a.o + (b * a.so[0] + hd * a.so[1] + (long long)query * a.so[2]) * 4;
 #pragma unroll
-    for (int d = 0; d < D32; ++d) {
-        uint32_t dw[4][4];
+    for (int qs = 0; qs < QS; ++qs) {
+        const float total = run_sum[qs] + other_half(run_sum[qs]);
+        const float inv = 1.0f / total;
+        uint8_t* op = a.o + (b * a.so[0] + hd * a.so[1] + (long long)query[qs] * a.so[2]) * E;
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+        for (int d = 0; d < D32; ++d) {
+            if constexpr (DT == OGC_BF16) {
+                uint32_t dw[4][2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) dw[g][e] = __builtin_bit_cast(uint32_t, oacc[d][4 * g + e] * inv);
+                for (int g = 0; g < 4; ++g) {
+                    dw[g][0] = pack_bf16(oacc[qs][d][4 * g] * inv, oacc[qs][d][4 * g + 1] * inv);
+                    dw[g][1] = pack_bf16(oacc[qs][d][4 * g + 2] * inv, oacc[qs][d][4 * g + 3] * inv);
+                }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            swap32(dw[0][e], dw[2][e]);
-            swap32(dw[1][e], dw[3][e]);
-        }
-        if (query < S) {
-            uint8_t* dst = op + (d * 32 + 16 * h) * 4;
-            const int order[4] = {0, 2, 1, 3};
+                for (int j = 0; j < 2; ++j) {
+                    swap32(dw[0][j], dw[2][j]);
+                    swap32(dw[1][j], dw[3][j]);
+                }
+                if (query[qs] < S) {
+                    uint8_t* dst = op + (d * 32 + 16 * h) * 2;
+                    *(v4i*)dst = (v4i){(int)dw[0][0], (int)dw[0][1], (int)dw[2][0], (int)dw[2][1]};
+                    *(v4i*)(dst + 16) = (v4i){(int)dw[1][0], (int)dw[1][1], (int)dw[3][0], (int)dw[3][1]};
+                }
+            } else {
+                uint32_t dw[4][4];
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                *(v4i*)(dst + 16 * g) = (v4i){(int)dw[order[g]][0], (int)dw[order[g]][1], (int)dw[order[g]][2], (int)dw[order[g]][3]};
+                for (int g = 0; g < 4; ++g)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) dw[g][e] = __builtin_bit_cast(uint32_t, oacc[qs][d][4 * g + e] * inv);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    swap32(dw[0][e], dw[2][e]);
+                    swap32(dw[1][e], dw[3][e]);
+                }
+                if (query[qs] < S) {
+                    uint8_t* dst = op + (d * 32 + 16 * h) * 4;
+                    const int order[4] = {0, 2, 1, 3};
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        *(v4i*)(dst + 16 * g) = (v4i){(int)dw[order[g]][0], (int)dw[order[g]][1], (int)dw[order[g]][2], (int)dw[order[g]][3]};
+                }
+            }
         }
     }
 }
 
-// Wavefronts per SIMD the registers are held to: one 32-query group with head_dim <= 64 fits three.
-constexpr int mha_waves(int dt, int d32, int qs) { return dt == OGC_BF16 && qs == 1 && d32 <= 2 ? 3 : 2; }
+// The body of ogc_mha_kernel: bf16 heads of up to 96 channels stream, the others are staged.  (The other body of a bf16
+// call has a kernel of its own; which one runs is stream_case's to say.)
+constexpr bool mha_streams(int dt, int d32) { return dt == OGC_BF16 && d32 <= 3; }
+// Wavefronts per SIMD the registers are held to: the streaming body with 32 channels, or 64 and one 32-query group, fits three.
+constexpr int mha_waves(int dt, int d32, int qs) { return mha_streams(dt, d32) && d32 * qs <= 2 ? 3 : 2; }
 
-// DT: OGC_F32 / OGC_BF16.  D32 = head_dim / 32.  FAST: softmax without the running maximum.  PLAIN: no mask, the
-// sequence is a whole number of key blocks and the scalar is positive, so no key needs an addend.
-// QS: 32-query groups per wavefront (1 or 2).  With 2, every key / value operand read from LDS feeds two matrix
-// instructions (one per group).
+// DT: OGC_F32 / OGC_BF16.  D32, FAST, PLAIN, QS: see the bodies.
 template <int DT, int D32, int FAST, int PLAIN, int QS>
 __global__ __launch_bounds__(256, mha_waves(DT, D32, QS)) void ogc_mha_kernel(MhaArgs a) {
-    if constexpr (DT == OGC_BF16) {
+    if constexpr (mha_streams(DT, D32)) {
         extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-        mha_bf16_body<D32, FAST, PLAIN ? MHA_NO_ADDEND : MHA_ADDEND_IN_LDS, QS>(a, (mha_lds_u8*)smem);
+        mha_stream_body<D32, FAST, PLAIN, QS>(a, (mha_lds_u8*)smem);
     } else {
-        mha_f32_body<D32, FAST, PLAIN>(a);
+        mha_staged_body<DT, D32, FAST, PLAIN, QS>(a);
     }
 }
 
-// bf16 calls that do not fit the other forms: scalars that are not positive or have no fp32 reciprocal, token strides
-// beyond 32 bits of byte offset.
-template <int D32, int FAST> __global__ __launch_bounds__(256, 2) void ogc_mha_general_kernel(MhaArgs a) {
+// bf16 calls with up to 96 channels that are staged, and those with 128 that stream.
+template <int D32, int FAST, int PLAIN, int QS> __global__ __launch_bounds__(256, 2) void ogc_mha_general_kernel(MhaArgs a) {
+    mha_staged_body<OGC_BF16, D32, FAST, PLAIN, QS>(a);
+}
+template <int D32, int FAST, int PLAIN> __global__ __launch_bounds__(256, 2) void ogc_mha_stream_kernel(MhaArgs a) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    mha_bf16_body<D32, FAST, MHA_ADDEND_GENERAL, 1>(a, (mha_lds_u8*)smem);
+    mha_stream_body<D32, FAST, PLAIN, 1>(a, (mha_lds_u8*)smem);
 }
 
 namespace {
 
-// Bytes of LDS of a bf16 launch: the ring, and the addends where the mode keeps them there.
-size_t bf16_lds(int d32, int seq, int plain) {
+// Bytes of LDS of a streaming launch: the ring, and an addend per key where a call has them.
+size_t stream_lds(int d32, int seq, int plain) {
     const int keys = seq <= MHA_UNIT ? 2 * MHA_UNIT : (seq + MHA_UNIT - 1) / MHA_UNIT * MHA_UNIT;  // at least two units
     return (size_t)2 * 4 * MHA_UNIT * d32 * 64 + (plain ? 0 : (size_t)(keys < MHA_LDS_KEYS ? keys : MHA_LDS_KEYS) * 4);
 }
 
-// One launch with dynamic LDS; the limit is raised once per kernel that can ask for more than 64 KiB (head_dim 128: up to
-// 80 KiB).  Two threads at once only repeat it.
-template <int DT, int D32, int FAST, int PLAIN, int QS> hipError_t launch_one(const MhaArgs& a, dim3 grid, hipStream_t st) {
-    auto kern = ogc_mha_kernel<DT, D32, FAST, PLAIN, QS>;
-    const size_t lds = DT == OGC_BF16 ? bf16_lds(D32, a.seq, PLAIN) : 0;
-    static std::atomic<bool> raised{false};
-    if (lds > 65536 && !raised.load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)bf16_lds(D32, MHA_LDS_KEYS, PLAIN));
-        if (e != hipSuccess) return e;
-        raised.store(true, std::memory_order_release);
+template <int DT, int D32, int FAST, int PLAIN, int QS> hipError_t launch_one(bool stream, const MhaArgs& a, dim3 grid, hipStream_t st) {
+    if constexpr (mha_streams(DT, D32)) {  // 64 KiB of LDS at most
+        if (stream) hipLaunchKernelGGL((ogc_mha_kernel<DT, D32, FAST, PLAIN, QS>), grid, dim3(256), stream_lds(D32, a.seq, PLAIN), st, a);
+        else hipLaunchKernelGGL((ogc_mha_general_kernel<D32, FAST, PLAIN, QS>), grid, dim3(256), 0, st, a);
+    } else {
+        if constexpr (DT == OGC_BF16) {
+            if (stream) {
+                const size_t lds = stream_lds(D32, a.seq, PLAIN);  // up to 80 KiB
+                if (lds > 65536) {  // said at every such launch: the limit belongs to the current device
+                    const hipError_t e = hipFuncSetAttribute((const void*)ogc_mha_stream_kernel<D32, FAST, PLAIN>,
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                    if (e != hipSuccess) return e;
+                }
+                hipLaunchKernelGGL((ogc_mha_stream_kernel<D32, FAST, PLAIN>), grid, dim3(256), lds, st, a);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((ogc_mha_kernel<DT, D32, FAST, PLAIN, QS>), grid, dim3(256), 0, st, a);
     }
-    hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a);
     return hipGetLastError();
 }
-template <int DT, int D32, int QS> hipError_t launch_fast(int fast, int plain, const MhaArgs& a, dim3 grid, hipStream_t st) {
-    if (fast && plain) return launch_one<DT, D32, 1, 1, QS>(a, grid, st);
-    if (fast) return launch_one<DT, D32, 1, 0, QS>(a, grid, st);
-    if (plain) return launch_one<DT, D32, 0, 1, QS>(a, grid, st);
-    return launch_one<DT, D32, 0, 0, QS>(a, grid, st);
+template <int DT, int D32, int QS> hipError_t launch_fast(bool stream, int fast, int plain, const MhaArgs& a, dim3 grid, hipStream_t st) {
+    if (fast && plain) return launch_one<DT, D32, 1, 1, QS>(stream, a, grid, st);
+    if (fast) return launch_one<DT, D32, 1, 0, QS>(stream, a, grid, st);
+    if (plain) return launch_one<DT, D32, 0, 1, QS>(stream, a, grid, st);
+    return launch_one<DT, D32, 0, 0, QS>(stream, a, grid, st);
 }
-template <int DT> hipError_t launch_dim(int d32, int qs, int fast, int plain, const MhaArgs& a, dim3 grid, hipStream_t st) {
+template <int DT> hipError_t launch_dim(bool stream, int d32, int qs, int fast, int plain, const MhaArgs& a, dim3 grid, hipStream_t st) {
     if (qs == 2) {  // bf16 with head_dim <= 64 only (query_groups)
-        if constexpr (DT == OGC_BF16) return d32 == 1 ? launch_fast<DT, 1, 2>(fast, plain, a, grid, st) : launch_fast<DT, 2, 2>(fast, plain, a, grid, st);
+        if constexpr (DT == OGC_BF16)
+            return d32 == 1 ? launch_fast<DT, 1, 2>(stream, fast, plain, a, grid, st) : launch_fast<DT, 2, 2>(stream, fast, plain, a, grid, st);
     }
     switch (d32) {
-    case 1: return launch_fast<DT, 1, 1>(fast, plain, a, grid, st);
-    case 2: return launch_fast<DT, 2, 1>(fast, plain, a, grid, st);
-    case 3: return launch_fast<DT, 3, 1>(fast, plain, a, grid, st);
-    default: return launch_fast<DT, 4, 1>(fast, plain, a, grid, st);
+    case 1: return launch_fast<DT, 1, 1>(stream, fast, plain, a, grid, st);
+    case 2: return launch_fast<DT, 2, 1>(stream, fast, plain, a, grid, st);
+    case 3: return launch_fast<DT, 3, 1>(stream, fast, plain, a, grid, st);
+    default: return launch_fast<DT, 4, 1>(stream, fast, plain, a, grid, st);
     }
-}
-template <int D32> void launch_general_dim(int fast, const MhaArgs& a, dim3 grid, hipStream_t st) {
-    if (fast) hipLaunchKernelGGL((ogc_mha_general_kernel<D32, 1>), grid, dim3(256), bf16_lds(D32, a.seq, 1), st, a);
-    else hipLaunchKernelGGL((ogc_mha_general_kernel<D32, 0>), grid, dim3(256), bf16_lds(D32, a.seq, 1), st, a);
-}
-hipError_t launch_general(int d32, int fast, const MhaArgs& a, dim3 grid, hipStream_t st) {
-    switch (d32) {
-    case 1: launch_general_dim<1>(fast, a, grid, st); break;
-    case 2: launch_general_dim<2>(fast, a, grid, st); break;
-    case 3: launch_general_dim<3>(fast, a, grid, st); break;
-    default: launch_general_dim<4>(fast, a, grid, st); break;
-    }
-    return hipGetLastError();
 }
 
 // no mask, whole key blocks only, positive scalar
 bool plain_case(const ogc_mha_desc* d, const float* mask) {
-    const int kb = d->dtype == OGC_BF16 ? MHA_BF16_WHOLE : MHA_F32_KEYS;
+    const int kb = d->dtype == OGC_BF16 ? MhaCfg<OGC_BF16>::KB : MhaCfg<OGC_F32>::KB;
     return mask == nullptr && d->seq % kb == 0 && d->scale > 0.0f;
-}
-
-// bf16 calls that take the general kernel.  A lane's piece is addressed by 32 bits of byte offset from its unit's first
-// row; the addend in LDS is the mask divided by the scalar.
-bool general_case(const ogc_mha_desc* d, const float* mask) {
-    if (d->dtype != OGC_BF16) return false;
-    const int64_t most = (int64_t)1 << 31;
-    if (d->k_stride[2] * 2 > most / MHA_UNIT || d->v_stride[2] * 2 > most / MHA_UNIT) return true;
-    if (plain_case(d, mask)) return false;
-    return !(d->scale >= 1e-30f && d->scale <= 1e30f);
 }
 
 // 32-query groups per wavefront.  Two where the registers allow it (bf16, head_dim <= 64) and the sequence is long
@@ -374,6 +491,34 @@ int query_groups(const ogc_mha_desc* d) {
     return (can && d->seq >= 256) ? 2 : 1;
 }
 
+// The streaming body or the staged one (bf16).  Streaming addresses a lane's piece by 32 bits of byte offset from its unit's
+// first row and divides the mask by the scalar: wider token strides, and scalars that are not positive or have no fp32
+// reciprocal to speak of, are staged.  Otherwise the faster one.  Staged / streaming, us, batch x heads x seq, with a mask:
+//   32 channels: 1x8x17 4.3 / 4.3, so staged as before;  256x12x64 18.3 / 13.6;  128x12x96 14.9 / 10.2;  8x12x197 6.8 / 6.5;  8x8x256 9.2 / 8.4;
+//     64x16x512 77 / 58.
+//   64: 1x8x32 4.4 / 4.8;  256x12x64 19.6 / 21.2;  128x12x96 17.4 / 17.2;  128x12x128 20.0 / 20.8: in two staged blocks or less
+//     streaming must save a unit to pay for its start.  8x12x192 6.6 / 7.0 (no mask 6.3 / 6.3);  8x12x197 7.6 / 7.8;  8x8x256
+//     10.5 / 10.6;  64x12x192 21.6 / 20.7;  64x16x256 32.4 / 32.1: up to four, addends need a chip full of workgroups
+//     (two on each of the 256 CUs).  8x8x384 13.8 / 13.7;  64x8x384 39.6 / 37.3;  64x16x512 95.7 / 88.6.
+//   96: 1x8x32 4.8 / 5.3;  1x16x64 5.3 / 5.2;  64x12x64 12.2 / 10.1;  8x8x384 12.7 / 12.4;  64x16x512 174 / 158.
+//   128: 256x12x64 37.3 / 39.4;  128x16x128 48.4 / 50.4;  64x16x256 60.1 / 60.8;  16x8x512 27.8 / 26.8;  64x8x512 96.7 / 91.3;
+//     32x16x1024 361 / 332;  1x8x8192 310 / 270, but 1x8x4096 102 / 112 (one workgroup a CU) and 46x4x444 35.0 / 36.4 (a third
+//     one left over): streaming from 384 keys on, where CUs have two workgroups each, or four and more.
+bool stream_case(const ogc_mha_desc* d, const float* mask) {
+    if (d->dtype != OGC_BF16) return false;
+    const int64_t most = (int64_t)1 << 31;
+    if (d->k_stride[2] * 2 > most / MHA_UNIT || d->v_stride[2] * 2 > most / MHA_UNIT) return false;
+    const bool plain = plain_case(d, mask);
+    if (!plain && !(d->scale >= 1e-30f && d->scale <= 1e30f)) return false;
+    const int units = d->seq <= 32 ? 2 : (d->seq + 31) / 32, blocks = (d->seq + 63) / 64;
+    const int64_t groups = (int64_t)d->batch * d->heads * ((d->seq + 128 * query_groups(d) - 1) / (128 * query_groups(d)));
+    switch (d->head_dim) {
+    case 32:
+    case 96: return d->seq > 32;
+    case 64: return blocks > 4 || (blocks > 2 ? plain || groups > 512 : units < 2 * blocks);
+    default: return d->seq >= 384 && (groups == 512 || groups >= 1024);
+    }
+}
 bool stride_ok(const int64_t s[3], int elt) {
     for (int i = 0; i < 3; ++i)
         if (s[i] < 0 || (s[i] * elt) % 16 != 0) return false;
@@ -422,8 +567,7 @@ ogc_status ogc_mha_run(const ogc_mha_desc* d, const void* q, const void* k, cons
     a.batch = d->batch;
     a.heads = d->heads;
     a.seq = d->seq;
-    const bool general = general_case(d, mask);
-    const int qs = general ? 1 : query_groups(d);
+    const int qs = query_groups(d);
     a.q_tiles = (d->seq + 128 * qs - 1) / (128 * qs);
     const int bh = d->batch * d->heads;
     auto magic = [](uint64_t n, uint64_t v) { return v == 1 || n * v >= 1ull << 32 ? 0u : (uint32_t)((1ull << 32) / v + 1); };
@@ -435,23 +579,30 @@ ogc_status ogc_mha_run(const ogc_mha_desc* d, const void* q, const void* k, cons
     a.addend_max = 3.0e38f / fmaxf(1.0f, a.scale_log2);
     const dim3 grid((unsigned)(bh * a.q_tiles));
     const int plain = plain_case(d, mask);
-    const hipError_t e = general ? launch_general(d->head_dim / 32, d->softmax, a, grid, (hipStream_t)stream)
-                       : d->dtype == OGC_F32 ? launch_dim<OGC_F32>(d->head_dim / 32, qs, d->softmax, plain, a, grid, (hipStream_t)stream)
-                                             : launch_dim<OGC_BF16>(d->head_dim / 32, qs, d->softmax, plain, a, grid, (hipStream_t)stream);
+    const bool stream_body = stream_case(d, mask);
+    const hipError_t e = d->dtype == OGC_F32 ? launch_dim<OGC_F32>(stream_body, d->head_dim / 32, qs, d->softmax, plain, a, grid, (hipStream_t)stream)
+                                             : launch_dim<OGC_BF16>(stream_body, d->head_dim / 32, qs, d->softmax, plain, a, grid, (hipStream_t)stream);
     return e == hipSuccess ? OGC_OK : OGC_ERR_DEVICE;
 }
 
 const char* ogc_mha_kernel_name(const ogc_mha_desc* d, int32_t has_mask) {
     if (ogc_mha_validate(d) != OGC_OK) return nullptr;
-    static char names[2][4][2][2][2][48], general[4][2][48];
-    if (general_case(d, has_mask ? (const float*)d : nullptr)) {
-        char* g = general[d->head_dim / 32 - 1][d->softmax];
-        if (!g[0]) snprintf(g, 48, "ogc_mha_general_kernel<%d, %d>", d->head_dim / 32, d->softmax);
+    static char names[2][4][2][2][2][48], general[4][2][2][2][48], wide[2][2][48];
+    const float* mask = has_mask ? (const float*)d : nullptr;
+    const int d32 = d->head_dim / 32, plain = plain_case(d, mask), qs = query_groups(d);
+    const bool stream = stream_case(d, mask);
+    if (stream && !mha_streams(d->dtype, d32)) {
+        char* w = wide[d->softmax][plain];
+        if (!w[0]) snprintf(w, 48, "ogc_mha_stream_kernel<%d, %d, %d>", d32, d->softmax, plain);
+        return w;
+    }
+    if (!stream && mha_streams(d->dtype, d32)) {
+        char* g = general[d32 - 1][d->softmax][plain][qs - 1];
+        if (!g[0]) snprintf(g, 48, "ogc_mha_general_kernel<%d, %d, %d, %d>", d32, d->softmax, plain, qs);
         return g;
     }
-    const int plain = plain_case(d, has_mask ? (const float*)d : nullptr), qs = query_groups(d);
-    char* s = names[d->dtype == OGC_BF16][d->head_dim / 32 - 1][d->softmax][plain][qs - 1];
-    if (!s[0]) snprintf(s, 48, "ogc_mha_kernel<%d, %d, %d, %d, %d>", d->dtype, d->head_dim / 32, d->softmax, plain, qs);
+    char* s = names[d->dtype == OGC_BF16][d32 - 1][d->softmax][plain][qs - 1];
+    if (!s[0]) snprintf(s, 48, "ogc_mha_kernel<%d, %d, %d, %d, %d>", d->dtype, d32, d->softmax, plain, qs);
     return s;
 }
 

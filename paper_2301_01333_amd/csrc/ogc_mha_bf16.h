@@ -16,8 +16,7 @@
 //     against the reference there is, and only if the row sum of the result (needed anyway) passes 2^8, or is no
 //     number, is the unit's maximum taken, the reference moved and the unit exponentiated again.  The same function:
 //     numerator and denominator carry the same factor, and every weight stays at or below 2^8.  A reference beyond 2^24
-//     (masks and scores whose spacing in fp32 is no longer small against 1) always takes that way, which subtracts
-//     exactly;
+//     (scores whose spacing in fp32 is no longer small against 1) always takes that way, which subtracts exactly;
 //   * the scores of the next unit and the second product of the one before are computed next to the exponentials of
 //     this one: the matrix pipe and the vector ALU work side by side inside a wavefront.
 // Measured against the kernel this replaces (64-key blocks through registers, maximum of every block, transposing LDS
@@ -38,12 +37,6 @@ typedef __attribute__((address_space(3))) v4i mha_lds_v4i;
 typedef __attribute__((address_space(3))) v4s mha_lds_v4s;
 typedef __attribute__((address_space(3))) v4f mha_lds_v4f;
 
-// MODE of the per-key addend
-enum {
-    MHA_NO_ADDEND = 0,      // no mask, whole units, positive scalar
-    MHA_ADDEND_IN_LDS = 1,  // mask / scalar of MHA_LDS_KEYS keys at a time in LDS, scalar positive
-    MHA_ADDEND_GENERAL = 2  // anything: the addend is read per unit and added after the product
-};
 constexpr int MHA_LDS_KEYS = 4096;  // longer sequences replace half of them every 64 units
 constexpr int MHA_UNIT = 32;  // keys per unit
 constexpr int MHA_PF = 2;     // units in flight ahead of the one in use
@@ -65,7 +58,8 @@ template <int N> MHA_DEV void mha_wait_and_meet() {  // all but the N newest loa
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const MhaArgs& a, mha_lds_u8* lds) {
+// D32 = head_dim / 32.  PLAIN: no mask, whole units, so no key needs an addend.  The scalar is positive.
+template <int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_stream_body(const MhaArgs& a, mha_lds_u8* lds) {
     typedef MhaB<D32> B;
     constexpr int D = B::D, QN = D / 16, NL = D32;  // NL: 1 KiB loads per wavefront and unit (keys and values together)
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, col = lane & 31;
@@ -84,7 +78,6 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
 
     // ---- direct loads.  The 4 * D32 loads of a unit's keys (the first half) and values go round the wavefronts.
     // Load m of 64 pieces covers the pieces 64 m + lane of the unit's linear LDS image.
-    [[maybe_unused]] int row_of[NL];
     uint32_t voff[NL];   // byte offset of the lane's piece from the unit's first row (32 bits: checked by the host)
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
@@ -92,8 +85,7 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
         const bool is_v = ld >= 2 * D32;
         const int p = (ld - (is_v ? 2 * D32 : 0)) * 64 + lane, r = p / B::CH, slot = p % B::CH;
         const int piece = slot ^ (is_v ? B::vswz(r) : B::kswz(r));
-        if constexpr (MODE == MHA_ADDEND_GENERAL) row_of[i] = r;
-        voff[i] = (MODE == MHA_ADDEND_GENERAL ? 0u : (uint32_t)r * (uint32_t)(is_v ? vss : kss)) + piece * 16;
+        voff[i] = (uint32_t)r * (uint32_t)(is_v ? vss : kss) + piece * 16;
     }
     // keys of unit ku into the slot at ko (bytes), values of unit vu into the one at vo; units that do not exist are left out
     auto issue = [&](int ku, uint32_t ko, int vu, uint32_t vo) {
@@ -108,12 +100,7 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
             const uint32_t dst = lds0 + (is_v ? B::SLOTS * B::UNIT_BYTES + vo + (ld - 2 * D32) * 1024 : ko + ld * 1024);
             const uint32_t m0 = __builtin_amdgcn_readfirstlane(dst);
             auto load = [&]() {
-                if constexpr (MODE == MHA_ADDEND_GENERAL) {
-                    const uint8_t* gl = g + (long long)row_of[i] * rs + voff[i];
-                    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0), "v"(gl) : "memory", "m0");
-                } else {
-                    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0), "v"(voff[i]), "s"(g) : "memory", "m0");
-                }
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0), "v"(voff[i]), "s"(g) : "memory", "m0");
             };
             if ((u + 1) * MHA_UNIT <= S) load();
             else {  // rows beyond the sequence are zero
@@ -141,7 +128,7 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
         for (int d = 0; d < D32; ++d)
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[qs][d][r] = 0.0f;
-        run_sum[qs] = 0.0f;
+        ref[qs] = run_sum[qs] = 0.0f;
     }
 
     // ---- first loads, oldest first: K0 | K1 V0 | K2 V1
@@ -149,28 +136,29 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
     issue(0, 0, -1, 0);
     issue(1, U, 0, 0);
     issue(2, 2 * U, 1, U);
-    mha_lds_u8* const add = lds + B::RING;  // MHA_ADDEND_IN_LDS: n * MHA_UNIT floats
-    auto fill_addend = [&](int first, int count) {  // keys first .. first + count - 1 (a multiple of MHA_UNIT, at most MHA_LDS_KEYS)
-        const float* mrow = a.mask + (long long)b * S;
+    // an addend per key in LDS, -infinity beyond the sequence: mask times `by`
+    typedef __attribute__((address_space(3))) float lds_f32;
+    lds_f32* const add = (lds_f32*)(lds + B::RING);
+    const float* mrow = a.mask + (long long)b * S;
+    auto each_mask = [&](int first, int count, auto use) {  // use(key, mask) for keys first .. first + count - 1, four loads in flight
         for (int j0 = first + tid; j0 < first + count; j0 += 1024) {
             float m[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) m[i] = a.mask && j0 + 256 * i < S ? mrow[j0 + 256 * i] : 0.0f;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int j = j0 + 256 * i;
-                float t = m[i] * a.inv_scale;
-                if (t == t) t = __builtin_fminf(__builtin_fmaxf(t, -a.addend_max), a.addend_max);  // finite masks stay finite
-                if (j < first + count)
-                    *(__attribute__((address_space(3))) float*)(add + (j & (MHA_LDS_KEYS - 1)) * 4) = j < S ? t : -INFINITY;
-            }
+            for (int i = 0; i < 4; ++i)
+                if (j0 + 256 * i < first + count) use(j0 + 256 * i, m[i]);
         }
     };
-    if constexpr (MODE == MHA_ADDEND_IN_LDS) fill_addend(0, n * MHA_UNIT < MHA_LDS_KEYS ? n * MHA_UNIT : MHA_LDS_KEYS);
+    auto fill_addends = [&](int first, int count, float by, float most) {  // a multiple of MHA_UNIT, at most MHA_LDS_KEYS
+        each_mask(first, count, [&](int j, float m) { add[j & (MHA_LDS_KEYS - 1)] = j < S ? finite_mask(m * by, most) : -INFINITY; });
+    };
+    const int add_keys = n * MHA_UNIT < MHA_LDS_KEYS ? n * MHA_UNIT : MHA_LDS_KEYS;
+    if constexpr (!PLAIN) fill_addends(0, add_keys, a.inv_scale, a.addend_max);
     if (3 * MHA_UNIT <= S) mha_wait_and_meet<2 * NL>();
     else mha_wait_and_meet<0>();
 
-    const float c = MODE == MHA_ADDEND_GENERAL ? 1.0f : a.scale_log2;
+    const float c = a.scale_log2;
     // ---- operand addresses in the first slot.  The other pieces of a row follow by exclusive or: a slot begins at a
     // multiple of the row's size, and the permutation is an exclusive or itself.
     const uint32_t kaddr = lds0 + col * B::ROW + ((h ^ B::kswz(col)) * 16);
@@ -178,14 +166,6 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
     const uint32_t vaddr = lds0 + B::SLOTS * B::UNIT_BYTES + (4 * h + vr) * B::ROW + (lane & 1) * 8 +
                            (((((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ B::vswz(4 * h + vr)) * 16);
 
-    auto add_general = [&](int u, v16f& s) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = u * MHA_UNIT + 8 * (r >> 2) + 4 * h + (r & 3);
-            const float m = key < S ? (a.mask ? a.mask[(long long)b * S + key] * LOG2E : 0.0f) : -INFINITY;
-            s[r] = __builtin_fmaf(s[r], a.scale_log2, m);
-        }
-    };
     // operand i of the first product: 32 keys x 16 channels
     auto read_keys = [&](uint32_t ko, int i) {
         // pieces 8 and up of a 256-byte row: the permutation leaves bit 3 alone; 64- and 192-byte rows: bits 2 and 3
@@ -193,10 +173,10 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
         return *(const mha_lds_v4i*)(uintptr_t)at;
     };
     auto read_addend = [&](int u, v16f& init) {
-        if constexpr (MODE == MHA_ADDEND_IN_LDS) {
+        if constexpr (!PLAIN) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const v4f m = *(const mha_lds_v4f*)(add + ((u * MHA_UNIT & (MHA_LDS_KEYS - 1)) + 8 * g + 4 * h) * 4);
+                const v4f m = *(const mha_lds_v4f*)(add + ((u * MHA_UNIT & (MHA_LDS_KEYS - 1)) + 8 * g + 4 * h));
 #pragma unroll
                 for (int e = 0; e < 4; ++e) init[4 * g + e] = m[e];
             }
@@ -250,12 +230,12 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
         if ((u + MHA_PF + 1) * MHA_UNIT <= S) mha_wait_and_meet<NL>();
         else mha_wait_and_meet<0>();
         issue(u + 3, slot(u + 3), u + 2, slot(u + 2));  // over K[u-1] and V[u-2], which no one reads any more
-        if constexpr (NEXT && MODE == MHA_ADDEND_IN_LDS) {
+        if constexpr (NEXT && !PLAIN) {
             // unit u + 1 opens a new half (the first two are there): over the half before unit u's
             constexpr int HALF = MHA_LDS_KEYS / 2;
             const int first = (u + 1) * MHA_UNIT;
             if (first % HALF == 0 && first >= MHA_LDS_KEYS) {
-                fill_addend(first, n * MHA_UNIT - first < HALF ? n * MHA_UNIT - first : HALF);
+                fill_addends(first, n * MHA_UNIT - first < HALF ? n * MHA_UNIT - first : HALF, a.inv_scale, a.addend_max);
                 asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             }
         }
@@ -298,7 +278,7 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
             bool far = false;
 #pragma unroll
             for (int qs = 0; qs < QS; ++qs) far = far || !(sum[qs] <= 256.0f) || !(fabsf(ref[qs]) <= 16777216.0f);
-            if (__builtin_amdgcn_ballot_w64(far) != 0) {
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(far) != 0, D32 == 1)) {  // (32 channels: spills, laid out as unlikely)
 #pragma unroll
                 for (int qs = 0; qs < QS; ++qs) {
                     // the scores once more: keeping them until here would cost 16 registers a group
@@ -311,7 +291,6 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
                         for (int i = 0; i < QN; ++i)
                             t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, read_keys(slot(u), i)),
                                                                         __builtin_bit_cast(v8bf, qreg[qs][i]), t, 0, 0, 0);
-                        if constexpr (MODE == MHA_ADDEND_GENERAL) add_general(u, t);
                     }
                     float cand = t[0];
 #pragma unroll
@@ -332,34 +311,25 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
         }
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs) run_sum[qs] += sum[qs];
-        if constexpr (NEXT && MODE == MHA_ADDEND_GENERAL) {
-#pragma unroll
-            for (int qs = 0; qs < QS; ++qs) add_general(u + 1, next[qs]);
-        }
     };
 
     v16f s0[QS], s1[QS];
     uint32_t w0[QS][8], w1[QS][8];
-    {
+    auto first_scores = [&](int u, v16f (&s)[QS]) {
         v4i kf[QN];
         v16f init;
 #pragma unroll
-        for (int i = 0; i < QN; ++i) kf[i] = read_keys(0, i);
-        read_addend(0, init);
+        for (int i = 0; i < QN; ++i) kf[i] = read_keys(slot(u), i);
+        read_addend(u, init);
 #pragma unroll
-        for (int t = 0; t < QN * QS; ++t) mma_score(t, kf, init, s0);
-        if constexpr (MODE == MHA_ADDEND_GENERAL) {
+        for (int t = 0; t < QN * QS; ++t) mma_score(t, kf, init, s);
+    };
+    auto top = [](const v16f& x, const v16f& y) {  // the maximum of two units' scores, this lane's query
+        float t = fmaxf(x[0], y[0]);
 #pragma unroll
-            for (int qs = 0; qs < QS; ++qs) add_general(0, s0[qs]);
-        }
-#pragma unroll
-        for (int qs = 0; qs < QS; ++qs) {  // the first reference: the first unit's maximum (key 0 is always valid)
-            float cand = s0[qs][0];
-#pragma unroll
-            for (int r = 1; r < 16; ++r) cand = fmaxf(cand, s0[qs][r]);
-            ref[qs] = FAST ? 0.0f : fmaxf(cand, other_half(cand)) * c;
-        }
-    }
+        for (int r = 1; r < 16; ++r) t = fmaxf(t, fmaxf(x[r], y[r]));
+        return fmaxf(t, other_half(t));
+    };
     auto last = [&](uint32_t (&w)[QS][8]) {  // the second product of the last unit
         mha_wait_and_meet<0>();
         v8s vf[2 * D32];
@@ -368,19 +338,25 @@ template <int D32, int FAST, int MODE, int QS> MHA_DEV void mha_bf16_body(const 
 #pragma unroll
         for (int t = 0; t < 2 * D32 * QS; ++t) mma_value(t, vf, w);
     };
-    step(no, yes, 0, s0, s1, w1, w0);
-    int u = 1;
-    for (; u + 2 < n; u += 2) {
-        step(yes, yes, u, s1, s0, w0, w1);
-        step(yes, yes, u + 1, s0, s1, w1, w0);
-    }
-    if (u + 2 == n) {
-        step(yes, yes, u, s1, s0, w0, w1);
-        step(yes, no, u + 1, s0, s1, w1, w0);
-        last(w0);
-    } else {
-        step(yes, no, u, s1, s0, w0, w1);
-        last(w1);
+    first_scores(0, s0);
+    {
+#pragma unroll
+        for (int qs = 0; qs < QS; ++qs)  // the first reference: the first unit's maximum (key 0 is always valid)
+            ref[qs] = FAST ? 0.0f : top(s0[qs], s0[qs]) * c;
+        step(no, yes, 0, s0, s1, w1, w0);
+        int u = 1;
+        for (; u + 2 < n; u += 2) {
+            step(yes, yes, u, s1, s0, w0, w1);
+            step(yes, yes, u + 1, s0, s1, w1, w0);
+        }
+        if (u + 2 == n) {
+            step(yes, yes, u, s1, s0, w0, w1);
+            step(yes, no, u + 1, s0, s1, w1, w0);
+            last(w0);
+        } else {
+            step(yes, no, u, s1, s0, w0, w1);
+            last(w1);
+        }
     }
 
     // ---- normalise and store: after the half exchange a lane holds 16 consecutive channels of its query

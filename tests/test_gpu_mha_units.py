@@ -52,7 +52,7 @@ def test_the_reference_of_the_exponentials_moves(oracle_mod, head_dim):
 
 @pytest.mark.parametrize("scale", [-0.125, 0.0, 1e-33])
 def test_scalars_without_a_usable_reciprocal(oracle_mod, scale):
-    """The addend cannot be divided by these: the general kernel, with and without a mask."""
+    """The addend cannot be divided by these: the staged body, with and without a mask."""
     wl = synth.make_mha("bf16", 2, 150, 2 * 64, 2, 7500, name="scale %g" % scale)
     wl.scale = scale
     desc = binding.mha_desc(binding.OGC_BF16, 2, 2, 150, 64, scale)
@@ -69,8 +69,34 @@ def test_sequences_beyond_the_addends_in_lds(oracle_mod, seq):
     run_and_compare(oracle_mod, wl)
 
 
+@pytest.mark.parametrize("head_dim, seq, name", [(64, 64, "general_kernel<2, 0, 0, 1>"), (64, 96, "kernel<1, 2, 0, 0, 1>"), (64, 97, "general_kernel<2, 0, 0, 1>"),
+                                                 (64, 129, "general_kernel<2, 0, 0, 1>"), (64, 257, "kernel<1, 2, 0, 0, 2>"), (96, 32, "general_kernel<3, 0, 0, 1>"), (96, 33, "kernel<1, 3, 0, 0, 1>"),
+                                                 (32, 32, "general_kernel<1, 0, 0, 1>"), (32, 33, "kernel<1, 1, 0, 0, 1>"), (128, 512, "kernel<1, 4, 0, 0, 1>")])
+def test_either_side_of_the_rule(oracle_mod, head_dim, seq, name):
+    wl = synth.make_mha("bf16", 2, seq, 2 * head_dim, 2, 8000 + seq + head_dim, name="rule S=%d d=%d" % (seq, head_dim))
+    assert binding.ogc_mha_kernel_name(binding.mha_desc(binding.OGC_BF16, 2, 2, seq, head_dim, wl.scale), True) == "ogc_mha_" + name
+    check(oracle_mod, wl)
+    check(oracle_mod, wl, FAST)
+
+
+@pytest.mark.parametrize("batch, heads, seq, head_dim, name", [
+    (129, 2, 129, 64, "kernel<1, 2, 0, 0, 1>"), (129, 2, 192, 64, "kernel<1, 2, 0, 0, 1>"), (129, 2, 225, 64, "kernel<1, 2, 0, 0, 1>"),
+    (257, 2, 256, 64, "kernel<1, 2, 0, 0, 2>"), (171, 2, 384, 128, "stream_kernel<4, 0, 0>"), (128, 2, 417, 128, "stream_kernel<4, 0, 0>"),
+    (16, 2, 4200, 128, "stream_kernel<4, 0, 0>")])
+def test_launches_that_fill_the_chip(oracle_mod, batch, heads, seq, head_dim, name):
+    """The streaming body where only large launches take it: padded, unmasked; the longest replaces addends and needs more LDS than a launch has by itself."""
+    wl = synth.make_mha("bf16", batch, seq, heads * head_dim, heads, 8200 + seq + head_dim, name="filling S=%d d=%d" % (seq, head_dim))
+    desc = binding.mha_desc(binding.OGC_BF16, batch, heads, seq, head_dim, wl.scale)
+    assert binding.ogc_mha_kernel_name(desc, True) == "ogc_mha_" + name
+    few = [0, 1, batch - 1] if seq < 1000 else [1, 2]
+    check(oracle_mod, wl, batches=few)
+    if seq < 1000:
+        check(oracle_mod, wl, use_mask=False, batches=few)
+        check(oracle_mod, wl, FAST, use_mask=False, batches=few)
+
+
 def test_token_strides_beyond_32_bits_of_offset(oracle_mod):
-    """Keys 64 MiB apart: the general kernel's 64-bit addresses."""
+    """Keys 64 MiB apart: the staged body's 64-bit addresses."""
     import torch
 
     wl = synth.make_mha("bf16", 1, 3, 64, 1, 7700, name="wide token stride")
@@ -82,7 +108,7 @@ def test_token_strides_beyond_32_bits_of_offset(oracle_mod):
     m_dev = torch.from_numpy(wl.mask.copy()).cuda()
     o_dev = torch.zeros(3 * 64, dtype=torch.uint16, device="cuda")
     desc = binding.mha_desc(binding.OGC_BF16, 1, 1, 3, 64, wl.scale, k_stride=(3 * ks, 64, ks))
-    assert binding.ogc_mha_kernel_name(desc, True) == "ogc_mha_general_kernel<2, 0>"
+    assert binding.ogc_mha_kernel_name(desc, True) == "ogc_mha_general_kernel<2, 0, 0, 1>"
     binding.ogc_mha_run(desc, q_dev.data_ptr(), k_dev.data_ptr(), v_dev.data_ptr(), m_dev.data_ptr(), o_dev.data_ptr(),
                         int(torch.cuda.current_stream().cuda_stream))
     torch.cuda.synchronize()
