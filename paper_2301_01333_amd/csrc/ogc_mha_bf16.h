@@ -11,7 +11,11 @@
 //   * V^T operands come out of LDS through the transposing read (ds_read_b64_tr_b16: 4 keys x 16 channels per 16
 //     lanes), whose four keys are exactly the four consecutive keys a register quad of the score accumulator holds;
 //   * a mask (and the -infinity of keys beyond the sequence) is the initial value of the score accumulator, divided
-//     by the scalar once per workgroup, so it costs no arithmetic per score;
+//     by the scalar once per workgroup, so it costs no arithmetic per score.  Such an accumulator is rounded at the size
+//     of the mask once per matrix instruction, so this is for tiles whose references end up near zero: some key's addend
+//     is within 2^10 of it (base 2) and none lies above.  Up to there the outputs of rows masked alike are as near to 64 bits
+//     as with the mask added last (0.00228 of their norm both ways at -700); at -10000 they were 0.00244 against 0.00231, at
+//     -100000 0.0067 against 0.0038.  The other tiles (batch entries that are masked throughout) take a loop of their own;
 //   * the reference point of the exponentials is not the running maximum of every unit.  A unit is exponentiated
 //     against the reference there is, and only if the row sum of the result (needed anyway) passes 2^8, or is no
 //     number, is the unit's maximum taken, the reference moved and the unit exponentiated again.  The same function:
@@ -40,6 +44,7 @@ typedef __attribute__((address_space(3))) v4f mha_lds_v4f;
 constexpr int MHA_LDS_KEYS = 4096;  // longer sequences replace half of them every 64 units
 constexpr int MHA_UNIT = 32;  // keys per unit
 constexpr int MHA_PF = 2;     // units in flight ahead of the one in use
+constexpr float MHA_ADDEND_NEAR = 1024.0f;  // addends (base-2 domain) of keys that may hold a tile's references near zero
 constexpr int MHA_READ_AHEAD = 3;  // pairs of weights between an operand's LDS read and its first matrix instruction
 
 template <int D32> struct MhaB {
@@ -136,7 +141,7 @@ template <int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_stream_body(con
     issue(0, 0, -1, 0);
     issue(1, U, 0, 0);
     issue(2, 2 * U, 1, U);
-    // an addend per key in LDS, -infinity beyond the sequence: mask times `by`
+    // an addend per key in LDS, -infinity beyond the sequence: mask times `by` (1 / scalar, or log2(e) in the last loop below)
     typedef __attribute__((address_space(3))) float lds_f32;
     lds_f32* const add = (lds_f32*)(lds + B::RING);
     const float* mrow = a.mask + (long long)b * S;
@@ -154,11 +159,23 @@ template <int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_stream_body(con
         each_mask(first, count, [&](int j, float m) { add[j & (MHA_LDS_KEYS - 1)] = j < S ? finite_mask(m * by, most) : -INFINITY; });
     };
     const int add_keys = n * MHA_UNIT < MHA_LDS_KEYS ? n * MHA_UNIT : MHA_LDS_KEYS;
-    if constexpr (!PLAIN) fill_addends(0, add_keys, a.inv_scale, a.addend_max);
+    // May addends start accumulators?  Only if some key holds the references near zero and none lifts them far above it.
+    lds_f32* const votes = (lds_f32*)(lds + 3 * U);  // (the slot of the fourth unit's keys, which are loaded later)
+    if constexpr (!PLAIN) {
+        bool some = false, high = false;
+        each_mask(0, n * MHA_UNIT, [&](int j, float m) {
+            if (j < add_keys) add[j] = j < S ? finite_mask(m * a.inv_scale, a.addend_max) : -INFINITY;
+            some = some || (j < S && !(fabsf(m * LOG2E) > MHA_ADDEND_NEAR));
+            high = high || m * LOG2E > MHA_ADDEND_NEAR;
+        });
+        const uint64_t somes = __builtin_amdgcn_ballot_w64(some), highs = __builtin_amdgcn_ballot_w64(high);
+        if (!FAST && lane == 0) votes[wave] = highs ? -8.0f : somes ? 1.0f : 0.0f;
+    }
     if (3 * MHA_UNIT <= S) mha_wait_and_meet<2 * NL>();
     else mha_wait_and_meet<0>();
 
     const float c = a.scale_log2;
+    float exact_c = c;  // for weights by rounded products; 1 in the last loop below
     // ---- operand addresses in the first slot.  The other pieces of a row follow by exclusive or: a slot begins at a
     // multiple of the row's size, and the permutation is an exclusive or itself.
     const uint32_t kaddr = lds0 + col * B::ROW + ((h ^ B::kswz(col)) * 16);
@@ -213,7 +230,7 @@ template <int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_stream_body(con
     // exactly at the maximum, however large they are)
     auto weight_pair = [&](auto split_c, const v16f& s, int t, float off, uint32_t& w, float& sum) {
         constexpr bool SPLIT = decltype(split_c)::value;
-        auto power = [&](float x) { return FAST ? x * c : SPLIT ? x * c + off : __builtin_fmaf(x, c, off); };
+        auto power = [&](float x) { return FAST ? x * c : SPLIT ? x * exact_c + off : __builtin_fmaf(x, c, off); };
         const float p0 = __builtin_amdgcn_exp2f(power(s[2 * t])), p1 = __builtin_amdgcn_exp2f(power(s[2 * t + 1]));
         const v2bf pr = {(__bf16)p0, (__bf16)p1};
         w = __builtin_bit_cast(uint32_t, pr);
@@ -338,8 +355,10 @@ template <int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_stream_body(con
 #pragma unroll
         for (int t = 0; t < 2 * D32 * QS; ++t) mma_value(t, vf, w);
     };
+    const v4f v = !PLAIN && !FAST ? *(const mha_lds_v4f*)votes : (v4f){1.0f, 0.0f, 0.0f, 0.0f};
     first_scores(0, s0);
-    {
+    const bool late = !PLAIN && !FAST && __builtin_amdgcn_readfirstlane((int)(v[0] + v[1] + v[2] + v[3])) <= 0;
+    if (__builtin_expect(!late, 1)) {
 #pragma unroll
         for (int qs = 0; qs < QS; ++qs)  // the first reference: the first unit's maximum (key 0 is always valid)
             ref[qs] = FAST ? 0.0f : top(s0[qs], s0[qs]) * c;
@@ -356,6 +375,62 @@ template <int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_stream_body(con
         } else {
             step(yes, no, u, s1, s0, w0, w1);
             last(w1);
+        }
+    } else if constexpr (!PLAIN && !FAST) {
+        // One unit at a time, each score in the base-2 domain and rounded once, after its product was summed near zero.
+        exact_c = 1.0f;
+        mha_wait_and_meet<0>();
+        fill_addends(0, add_keys, LOG2E, 3.40282347e38f);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        auto scores = [&](int u, int qs) {
+            v16f t, m;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) t[r] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < QN; ++i)
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, read_keys(slot(u), i)),
+                                                            __builtin_bit_cast(v8bf, qreg[qs][i]), t, 0, 0, 0);
+            read_addend(u, m);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) t[r] = __builtin_fmaf(t[r], a.scale_log2, m[r]);
+            return t;
+        };
+#pragma unroll
+        for (int qs = 0; qs < QS; ++qs) ref[qs] = top(scores(0, qs), scores(0, qs));
+#pragma unroll 1
+        for (int u = 0; u < n; ++u) {
+            // K[u] and V[u] were issued two steps ago at the latest
+            if ((u + MHA_PF + 1) * MHA_UNIT <= S) mha_wait_and_meet<NL>();
+            else mha_wait_and_meet<0>();
+            issue(u + 3, slot(u + 3), u + 2, slot(u + 2));
+            if (u * MHA_UNIT % MHA_LDS_KEYS == 0 && u > 0) {
+                const int left = n * MHA_UNIT - u * MHA_UNIT;
+                fill_addends(u * MHA_UNIT, left < MHA_LDS_KEYS ? left : MHA_LDS_KEYS, LOG2E, 3.40282347e38f);
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            }
+#pragma unroll
+            for (int qs = 0; qs < QS; ++qs) {
+                const v16f t = scores(u, qs);
+                const float cand = top(t, t);
+                if (__builtin_amdgcn_ballot_w64(!(cand <= ref[qs] + 8.0f)) != 0) {
+                    const float new_ref = fmaxf(cand, ref[qs]), alpha = __builtin_amdgcn_exp2f(ref[qs] - new_ref);
+                    ref[qs] = new_ref;
+                    run_sum[qs] *= alpha;
+#pragma unroll
+                    for (int d = 0; d < D32; ++d)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) oacc[qs][d][r] *= alpha;
+                }
+                float sum;
+#pragma unroll
+                for (int p = 0; p < 8; ++p) weight_pair(yes, t, p, -ref[qs], w0[qs][p], sum);
+                run_sum[qs] += sum;
+            }
+            v8s vf[2 * D32];
+#pragma unroll
+            for (int jd = 0; jd < 2 * D32; ++jd) vf[jd] = read_values(slot(u), jd);
+#pragma unroll
+            for (int t = 0; t < 2 * D32 * QS; ++t) mma_value(t, vf, w0);
         }
     }
 

@@ -69,6 +69,54 @@ def test_sequences_beyond_the_addends_in_lds(oracle_mod, seq):
     run_and_compare(oracle_mod, wl)
 
 
+@pytest.mark.parametrize("level", [-1.0e4, -1.0e5, -3.0e5, 1.0e5])
+@pytest.mark.parametrize("seq, head_dim", [(384, 32), (384, 64), (300, 96), (384, 128), (2100, 64), (64, 64)])
+def test_rows_masked_alike_keep_their_precision(oracle_mod, seq, head_dim, level):
+    """A score with a large addend is rounded once, at the addend's size: a weight is off by that rounding (half a spacing at
+    most, evenly spread: ln 2 * spacing / sqrt(12) of itself in the mean), beside the 2.5e-3 of bf16 weights and outputs.  One
+    rounding per matrix instruction, four to eight, was two to four times as much."""
+    from paper_2301_01333_amd.harness import DeviceMHA
+
+    wl = synth.make_mha("bf16", 2, seq, 2 * head_dim, 2, 7800 + seq + head_dim, name="alike at %g" % level)
+    wl.mask[:] = level
+    dev = DeviceMHA(wl, STABLE)
+    dev.run()
+    q, k, v = (heads_view(as_f64(t), wl) for t in (wl.q, wl.k, wl.v))
+    ref = oracle_mod.attention(q, k, v, wl.mask, wl.scale, STABLE).transpose(0, 2, 1, 3).reshape(wl.batch, wl.seq, wl.hidden)
+    err = np.linalg.norm(as_f64(dev.result()) - ref) / np.linalg.norm(ref)
+    spacing = float(np.spacing(np.float32(abs(level) * math.log2(math.e))))
+    assert err <= 1.2 * math.hypot(2.5e-3, math.log(2.0) * spacing / math.sqrt(12.0)), err
+    if level > 0:  # some keys lifted, the others not
+        wl.mask[:, ::3] = 0.0
+        ref = oracle_mod.attention(q, k, v, wl.mask, wl.scale, STABLE).transpose(0, 2, 1, 3).reshape(wl.batch, wl.seq, wl.hidden)
+        err = np.linalg.norm(run_units(wl) - ref) / np.linalg.norm(ref)
+        assert err <= 1.2 * math.hypot(2.5e-3, math.log(2.0) * spacing / math.sqrt(12.0)), err
+
+
+@pytest.mark.parametrize("seq, head_dim", [(384, 32), (384, 64), (300, 96), (384, 128), (2100, 64), (31, 96)])
+def test_masks_that_swallow_the_scores(oracle_mod, seq, head_dim):
+    """Beyond 1e9 fp32 spaces the scores wider than they differ: a row masked alike is the mean of the values.  Beside it rows
+    padded in front, over more than the addends that are in LDS at the longest."""
+    wl = synth.make_mha("bf16", 2, seq, 2 * head_dim, 2, 7900 + seq + head_dim, name="swallowed")
+    for level in (-1.0e9, -1.0e30, -2.0e38):
+        wl.mask[:] = 0.0
+        wl.mask[0, :seq * 9 // 10] = level
+        wl.mask[1] = level
+        dev = run_units(wl)
+        q, k, v = (heads_view(as_f64(t), wl) for t in (wl.q, wl.k, wl.v))
+        for i, keys in ((0, q[:1]), (1, 0.0 * q[1:])):  # a query of zeros: all scores alike
+            ref = oracle_mod.attention(keys, k[i:i + 1], v[i:i + 1], wl.mask[i:i + 1], wl.scale, STABLE).transpose(0, 2, 1, 3)
+            assert_close(dev[i], ref.reshape(seq, wl.hidden), TOL["bf16"], "level %g, row %d" % (level, i))
+
+
+def run_units(wl, softmax=STABLE):
+    from paper_2301_01333_amd.harness import DeviceMHA
+
+    dev = DeviceMHA(wl, softmax)
+    dev.run()
+    return as_f64(dev.result())
+
+
 @pytest.mark.parametrize("head_dim, seq, name", [(64, 64, "general_kernel<2, 0, 0, 1>"), (64, 96, "kernel<1, 2, 0, 0, 1>"), (64, 97, "general_kernel<2, 0, 0, 1>"),
                                                  (64, 129, "general_kernel<2, 0, 0, 1>"), (64, 257, "kernel<1, 2, 0, 0, 2>"), (96, 32, "general_kernel<3, 0, 0, 1>"), (96, 33, "kernel<1, 3, 0, 0, 1>"),
                                                  (32, 32, "general_kernel<1, 0, 0, 1>"), (32, 33, "kernel<1, 1, 0, 0, 1>"), (128, 512, "kernel<1, 4, 0, 0, 1>")])
@@ -84,14 +132,19 @@ def test_either_side_of_the_rule(oracle_mod, head_dim, seq, name):
     (257, 2, 256, 64, "kernel<1, 2, 0, 0, 2>"), (171, 2, 384, 128, "stream_kernel<4, 0, 0>"), (128, 2, 417, 128, "stream_kernel<4, 0, 0>"),
     (16, 2, 4200, 128, "stream_kernel<4, 0, 0>")])
 def test_launches_that_fill_the_chip(oracle_mod, batch, heads, seq, head_dim, name):
-    """The streaming body where only large launches take it: padded, unmasked; the longest replaces addends and needs more LDS than a launch has by itself."""
+    """The streaming body where only large launches take it: padded, masked alike (the loop that adds the mask last), lifted in
+    part, unmasked; the longest replaces addends and needs more LDS than a launch has by itself."""
     wl = synth.make_mha("bf16", batch, seq, heads * head_dim, heads, 8200 + seq + head_dim, name="filling S=%d d=%d" % (seq, head_dim))
     desc = binding.mha_desc(binding.OGC_BF16, batch, heads, seq, head_dim, wl.scale)
     assert binding.ogc_mha_kernel_name(desc, True) == "ogc_mha_" + name
     few = [0, 1, batch - 1] if seq < 1000 else [1, 2]
-    check(oracle_mod, wl, batches=few)
+    wl.mask[1] = -2.0e4
+    wl.mask[2] = 0.0
+    wl.mask[2, ::5] = 3.0e3
+    check(oracle_mod, wl, batches=few + [2] if seq < 1000 else few)
     if seq < 1000:
         check(oracle_mod, wl, use_mask=False, batches=few)
+        wl.mask[1] = 0.0
         check(oracle_mod, wl, FAST, use_mask=False, batches=few)
 
 
