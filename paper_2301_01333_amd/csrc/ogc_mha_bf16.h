@@ -388,7 +388,7 @@ template <int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_stream_body(con
         // One unit at a time, each score in the base-2 domain and rounded once, after its product was summed near zero.
         exact_c = 1.0f;
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        fill_addends(0, add_keys, LOG2E, 3.40282347e38f);
+        fill_addends(0, add_keys, LOG2E, MHA_F32_MAX);
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         auto scores = [&](int u, int qs) {
             v16f t, m;
@@ -413,7 +413,7 @@ template <int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_stream_body(con
             issue(u + 3, slot(u + 3), u + 2, slot(u + 2));
             if (u * MHA_UNIT % MHA_LDS_KEYS == 0 && u > 0) {
                 const int left = n * MHA_UNIT - u * MHA_UNIT;
-                fill_addends(u * MHA_UNIT, left < MHA_LDS_KEYS ? left : MHA_LDS_KEYS, LOG2E, 3.40282347e38f);
+                fill_addends(u * MHA_UNIT, left < MHA_LDS_KEYS ? left : MHA_LDS_KEYS, LOG2E, MHA_F32_MAX);
                 asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             }
 #pragma unroll

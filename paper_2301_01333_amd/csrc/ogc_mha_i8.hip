@@ -66,6 +66,12 @@ MHA8_DEV int other_half_i(int x) {
     return (int)((threadIdx.x & 32) ? a : b);
 }
 
+// a mask value in the base-2 domain; finite ones stay finite (-infinity is for keys beyond the sequence), NaN passes
+MHA8_DEV float base2_mask(float m) {
+    const float x = m * 1.44269504088896340736f;
+    return x == x ? fminf(fmaxf(x, -3.40282347e38f), 3.40282347e38f) : x;
+}
+
 // The plain kernel: keys and values through registers, both passes over 64-key blocks.  For launches that do not fill the
 // chip (stream_case below).  D32 = head_dim / 32.  Key blocks of 64 (two 32-key groups).
 template <int D32> __global__ __launch_bounds__(256, 2) void ogc_mha_i8_kernel(MhaI8Args a) {
@@ -140,7 +146,7 @@ template <int D32> __global__ __launch_bounds__(256, 2) void ogc_mha_i8_kernel(M
                 }
             }
         }
-        if (tid < KB) m_lds[tid] = mpad ? -INFINITY : mreg * 1.44269504088896340736f;
+        if (tid < KB) m_lds[tid] = mpad ? -INFINITY : base2_mask(mreg);
     };
     // scores of the current block in the base-2 domain, scalar and mask applied: t[sb][4g+e] <-> key 32 sb + 8g + 4h + e
     auto scores = [&](float (&t)[SB][16]) {
@@ -333,7 +339,7 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
         for (int j0 = first + tid; j0 < first + count; j0 += 1024) {  // a wavefront has one unit at a time
             float t[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) t[i] = a.mask && j0 + 256 * i < S ? mrow[j0 + 256 * i] * 1.44269504088896340736f : 0.0f;
+            for (int i = 0; i < 4; ++i) t[i] = a.mask && j0 + 256 * i < S ? base2_mask(mrow[j0 + 256 * i]) : 0.0f;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int j = j0 + 256 * i;

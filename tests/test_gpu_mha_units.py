@@ -117,6 +117,34 @@ def run_units(wl, softmax=STABLE):
     return as_f64(dev.result())
 
 
+@pytest.mark.parametrize("dtype, batch, seq, head_dim", [("f32", 2, 100, 64), ("bf16", 2, 100, 64), ("bf16", 2, 300, 64), ("bf16", 2, 300, 128),
+                                                          ("i8", 2, 100, 64), ("i8", 2, 400, 64)])
+def test_masks_of_the_lowest_float(oracle_mod, dtype, batch, seq, head_dim):
+    """Finite masks that no score holds in base 2 (torch.finfo.min and its like): a row masked alike is the mean of the values, in
+    other rows such keys do not count."""
+    from paper_2301_01333_amd.harness import DeviceMHA
+
+    wl = synth.make_mha(dtype, batch, seq, 2 * head_dim, 2, 8150 + seq + head_dim, name="lowest float, " + dtype)
+    wl.mask[0] = np.where(wl.mask[0] < 0, np.finfo(np.float32).min, 0).astype(np.float32)
+    wl.mask[1] = np.finfo(np.float32).min
+    dev = DeviceMHA(wl, STABLE)
+    dev.run()
+    got = dev.result()
+    alike = synth.make_mha(dtype, batch, seq, 2 * head_dim, 2, 8150 + seq + head_dim)
+    alike.mask[:] = wl.mask
+    alike.mask[0] = np.maximum(wl.mask[0], -1.0e4)
+    alike.mask[1] = 0.0
+    alike.q[1] = 0
+    q, k, v = (heads_view(t if dtype == "i8" else as_f64(t), alike) for t in (alike.q, alike.k, alike.v))
+    if dtype == "i8":
+        ref = oracle_mod.attention_i8(q, k, v, alike.mask, wl.scale, *wl.quant).transpose(0, 2, 1, 3).reshape(got.shape)
+        diff = np.abs(got.astype(np.int32) - ref.astype(np.int32))
+        assert diff.max() <= 1 and (diff > 0).mean() < 0.01
+    else:
+        ref = oracle_mod.attention(q, k, v, alike.mask, wl.scale, STABLE).transpose(0, 2, 1, 3).reshape(got.shape)
+        assert_close(as_f64(got), ref, TOL[dtype], wl.name)
+
+
 @pytest.mark.parametrize("head_dim", [32, 96])
 def test_the_first_reference_covers_64_keys(head_dim):
     """64 keys: the weights are taken against the row's maximum, so the largest is 1 and rounds to itself.  The outputs are then as
