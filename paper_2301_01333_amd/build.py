@@ -115,6 +115,10 @@ def check_stream_kernel_registers(verbose: bool = True) -> None:
             spilling += 1
             if fixed:
                 raise RuntimeError("%s uses %d bytes of scratch memory per lane (register spills)" % (name, scratch))
+    # The fused chain's pair kernel is for two workgroups on a CU: 128 registers, none of them spilled.
+    pairs = re.findall(r"\.name:\s+(_Z\d+ogc_fused_chain_pair_kernel\w+)\s*\n\s+\.private_segment_fixed_size:\s+(\d+)", text)
+    if len(pairs) != 4 or any(int(scratch) for _, scratch in pairs):
+        raise RuntimeError("fused pair kernels (name, bytes of scratch memory per lane): %s" % pairs)
     if verbose:
         print("stream kernels checked: %d (compiler writes nothing at or above v80, no calls; %d kernels of the general "
               "epilogue use scratch memory)" % (checked, spilling), flush=True)

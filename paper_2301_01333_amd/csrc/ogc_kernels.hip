@@ -696,7 +696,8 @@ ogc_layer_kernel(const OgcLayerArgs a, int tiles_n, int tiles_total, int tiles_p
 // of the matrix instructions all the time: a step's registers are loaded again as soon as its instructions have them
 // (8 to 16 KiB of a wave in flight; four steps loaded, waited for and used in turn before: bf16 479-1024-1024-512-256-1
 // at batch 8192 137 -> 62 us, four 1024-wide E4M3 layers 80 -> 70, int8 71 -> 64).  Eight steps of one or two blocks: with
-// four, 512-wide int8 layers had too little in flight (17.0 against 16.5).  G = 0: no more than four steps' loads in flight.
+// four, 512-wide int8 layers had too little in flight (17.0 against 16.5).  G = 0 (the pair kernel): four steps' loads at a
+// time, two of three or four blocks and in int8, whose epilogue is the largest.
 template <int DT, int OUT_PLAIN, int CNT, int G, class YT>
 OGC_DEV void fused_blocks(const OgcLayerArgs& a, const uint8_t* xin, YT xout, int m0, int nb0, int lane, int stride) {
     const int KP2 = a.KC >> 1;  // 32-byte k-steps
@@ -751,8 +752,9 @@ OGC_DEV void fused_blocks(const OgcLayerArgs& a, const uint8_t* xin, YT xout, in
             for (int i = 0; i < CNT; ++i) mma32<DT>(acc[i], wf[u][i], xf[u]);
     };
     int kp = groups * G;  // the rest (G = 0: all): an even number of steps
+    constexpr int PART = G == 0 && (CNT > 2 || DT == OGC_I8) ? 2 : 4;
     if constexpr (G != 4)
-        for (; kp + 4 <= KP2; kp += 4) some(std::integral_constant<int, 4>(), kp);
+        for (; kp + PART <= KP2; kp += PART) some(std::integral_constant<int, PART>(), kp);
     if (kp < KP2) some(std::integral_constant<int, 2>(), kp);
 #pragma unroll
     for (int i = 0; i < CNT; ++i) epilogue_block<DT, OUT_PLAIN>(acc[i], a, (nb0 + i * stride) * 32, m0, lane, xout);
@@ -763,11 +765,20 @@ OGC_DEV void fused_blocks(const OgcLayerArgs& a, const uint8_t* xin, YT xout, in
 template <int DT, int OUT_PLAIN, int G, class YT>
 OGC_DEV void fused_layer(const OgcLayerArgs& a, const uint8_t* xin, YT xout, int m0, int wave, int waves, int lane) {
     const int nblocks = OUT_PLAIN ? ((a.N + 31) >> 5) : a.NB_out;
-    for (int nb0 = wave; nb0 < nblocks; nb0 += 4 * waves) {
+    constexpr int MOST = G == 0 && DT != OGC_BF16 ? 2 : 4;  // blocks of a wave at a time (128 registers hold four in bf16 only)
+    for (int nb0 = wave; nb0 < nblocks; nb0 += MOST * waves) {
         const int cnt = (nblocks - nb0 + waves - 1) / waves;  // blocks of this wave from nb0 on
-        if (cnt >= 4) fused_blocks<DT, OUT_PLAIN, 4, (G > 4 ? 4 : G)>(a, xin, xout, m0, nb0, lane, waves);
-        else if (cnt == 3) fused_blocks<DT, OUT_PLAIN, 3, (G > 4 ? 4 : G)>(a, xin, xout, m0, nb0, lane, waves);
-        else if (cnt == 2) fused_blocks<DT, OUT_PLAIN, 2, G>(a, xin, xout, m0, nb0, lane, waves);
+        if constexpr (MOST == 4) {
+            if (cnt >= 4) {
+                fused_blocks<DT, OUT_PLAIN, 4, (G > 4 ? 4 : G)>(a, xin, xout, m0, nb0, lane, waves);
+                continue;
+            }
+            if (cnt == 3) {
+                fused_blocks<DT, OUT_PLAIN, 3, (G > 4 ? 4 : G)>(a, xin, xout, m0, nb0, lane, waves);
+                continue;
+            }
+        }
+        if (cnt >= 2) fused_blocks<DT, OUT_PLAIN, 2, G>(a, xin, xout, m0, nb0, lane, waves);
         else fused_blocks<DT, OUT_PLAIN, 1, G>(a, xin, xout, m0, nb0, lane, waves);
     }
 }
@@ -812,7 +823,8 @@ template <int DT> __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_fused
 }
 
 // For two workgroups on a CU: at most 128 registers (the loads of a few k-steps in flight, then none), and the one workgroup's
-// matrix instructions cover the other's loads.
+// matrix instructions cover the other's loads.  The registers are held without scratch memory (fused_layer, fused_blocks): with
+// eight to twelve of them spilled, chains of 768 row tiles were slower than one workgroup a CU (launch_fused_t).
 template <int DT> __global__ void __launch_bounds__(OGC_FUSED_THREADS, 4) ogc_fused_chain_pair_kernel(const OgcChainArgs c) {
     extern __shared__ __align__(16) uint8_t smem[];
     fused_chain<DT, 0>(c, smem);
@@ -1573,18 +1585,23 @@ extern "C" int ogc_launch_layer(int dtype, int tile, int x_plain, int out_plain,
 extern "C" size_t ogc_fused_lds_limit(void) { return 160 * 1024; }
 extern "C" int ogc_fused_threads(void) { return OGC_FUSED_THREADS; }
 
+// The kernel of which two workgroups fit a CU's registers: more row tiles than the 256 CUs, and LDS for two (lds: bytes of
+// one); up to 256 tiles a CU has one workgroup whichever it is.  us, deep kernel / pair, four layers of 128, then 13-512-256-128-64:
+//   batch   int8                bf16                E4M3                fp32
+//   16384   13.1/9.4 19.5/14.3  12.5/9.3 21.0/15.6  13.6/8.9 21.2/14.3  28.7/24.8 63.9/64.0
+//   24576   18.1/14.3 27.5/24.7 18.6/17.3 29.2/26.1 19.1/13.8 30.2/24.2 41.4/37.4 93.7/93.7
+//   32768   23.2/16.2 35.5/25.8 23.8/18.9 37.5/27.4 24.4/14.1 39.2/26.5 53.8/45.6 123/123
+// Wide int8 rows leave a workgroup that ends up alone on its CU with too few loads in flight: two layers of 1024 at batch 24576
+// 104 / 113 (16384: 63 / 58; 32768: 139 / 127; E4M3 at 24576: 114 / 106).
+static bool fused_pairs(int dtype, int m_blocks, size_t lds) {
+    if (m_blocks <= 256 || 2 * lds > ogc_fused_lds_limit()) return false;
+    return !(dtype == OGC_I8 && lds > 32 * 1024 && (m_blocks - 1) % 512 < 256);
+}
+
 template <int DT> static int launch_fused_t(const OgcChainArgs* c, int m_blocks, hipStream_t stream) {
     const size_t lds = (size_t)2 * c->lds_buf_bytes;
-    // More row tiles than CUs, and room for two workgroups in a CU's LDS: the kernel of which two fit the registers as well.
-    // us with the deep kernel -> the pair, bf16: 64x4 at batch 16384 12.0 -> 10.4, 13-512-256-128-64 at 32768 38.6 -> 35.5 (E4M3:
-    // 11.8 -> 10.1 and 39.7 -> 36.2; fp32 64x4: 17.9 -> 16.7); up to 256 tiles a CU has one workgroup whichever it is.
-    // Not int8: its epilogue takes more registers, the pair spills (256x4 at 16384: 17.6 -> 25.4).
-    auto kern = ogc_fused_chain_kernel<DT>;
-    bool pair = false;
-    if constexpr (DT != OGC_I8) {
-        pair = m_blocks > 256 && 2 * lds <= ogc_fused_lds_limit();
-        if (pair) kern = ogc_fused_chain_pair_kernel<DT>;
-    }
+    const bool pair = fused_pairs(DT, m_blocks, lds);
+    auto kern = pair ? ogc_fused_chain_pair_kernel<DT> : ogc_fused_chain_kernel<DT>;
     {   // the limit only ever grows; the lock keeps raising it and remembering it together
         static std::mutex mu;
         static size_t attr_max[2] = {0, 0};

@@ -188,6 +188,13 @@ def test_one_layer_chain_modes(oracle_mod, mode):
         check_one_layer(oracle_mod, wl, mode)
 
 
+@pytest.mark.parametrize("dims, acts", [([96, 288, 160, 32], [RELU, GELU, NONE]), ([64, 1060, 48], [NONE, RELU])])
+def test_fused_two_workgroups_to_a_cu(oracle_mod, dims, acts):
+    """More row tiles than CUs (the last one ragged), rows that leave LDS for two workgroups; one to five channel blocks to a wave."""
+    wl = synth.make_mlp("f8", 8192 + 33, dims, acts, seed=1650 + dims[0], name="two a CU")
+    check_chain(oracle_mod, wl, "fused", layers_alone=False)
+
+
 def test_saturation_subnormals_and_signed_zero(oracle_mod):
     """Scales chosen so that a large share of the outputs saturate at +-448, and another run so that most land in the
     subnormal range; no activation, so negative results and -0 are stored too."""

@@ -134,6 +134,18 @@ def test_fused_k_steps_and_blocks(oracle_mod, dtype, dims):
         check(synth.make_mlp(dtype, 8192 + 33, dims, [RELU] * (len(dims) - 1), seed=621, name="pairs"), "fused", oracle_mod)
 
 
+@pytest.mark.parametrize("dtype, dims, acts, more", [
+    ("i8", [224, 1060, 608, 40], [RELU, NONE, SIGM], dict(last_f32=True)), ("i8", [31, 96, 544, 300], [GELU, RELU, RELU], {}),
+    ("bf16", [160, 544, 608, 160], [GELU, RELU, NONE], dict(residual=True)), ("bf16", [31, 288, 640, 33], [RELU, SIGM, GELU], {}),
+    ("f32", [96, 288, 160, 96], [GELU, RELU, NONE], dict(residual=True)), ("f32", [31, 320, 64, 7], [RELU, SIGM, RELU], {})])
+def test_fused_two_workgroups_to_a_cu(oracle_mod, dtype, dims, acts, more):
+    """More row tiles than CUs and rows that leave LDS for two workgroups: one to five channel blocks to a wave, every activation,
+    residual, strided rows on both sides; the first tiles and the ragged last one."""
+    m, ld_x = 8192 + 33, dims[0] + (0 if "residual" in more else 13)
+    wl = synth.make_mlp(dtype, m, dims, acts, seed=630 + dims[0], name="two a CU", ld_x=ld_x, **more)
+    check(wl, "fused", oracle_mod, rows=[slice(0, 70), slice(m - 70, m)], ld_y=dims[-1] + 3)
+
+
 @pytest.mark.parametrize("mode", ["fused", "per_layer"])
 def test_reduced_cfg4_and_cfg5(oracle_mod, mode):
     check(synth.make_config(4, m=160), "per_layer", oracle_mod, tile=1)   # hidden 4096 does not fit the fused kernel
