@@ -71,7 +71,7 @@ def main(out_path: str = DEFAULT_OUT) -> None:
                         acts[-1] = synth.ACT_SIGMOID if dtype == "i8" else synth.ACT_NONE
                         kw = dict(last_f32=True) if dtype == "i8" else {}
                     wl = synth.make_mlp(dtype, m, dims, acts, seed=7, has_bias=True, **kw)
-                    cases = [("fused", 0, binding.OGC_MODE_FUSED, None, "ogc_fused_chain_kernel"),
+                    cases = [("fused", 0, binding.OGC_MODE_FUSED, None, "ogc_fused_chain_"),
                              ("coop", 0, binding.OGC_MODE_COOP, {"cluster_split": 0}, "ogc_coop_chain_kernel")]
                     if m <= 2048:
                         cases += [("cluster", s, binding.OGC_MODE_COOP, {"cluster_split": s, "cluster_ksplit": 0}, "ogc_cluster_chain_kernel")

@@ -922,7 +922,7 @@ ogc_status ogc_mlp_mode_estimates(ogc_mlp_plan_t plan, float us[3]) {
 
 const char* ogc_mlp_kernel_name(ogc_mlp_plan_t plan, int32_t layer) {
     if (!plan || layer < 0 || layer >= (int)plan->layers.size()) return nullptr;
-    if (plan->mode == OGC_MODE_FUSED) return ogc_fused_kernel_name(plan->desc.dtype);
+    if (plan->mode == OGC_MODE_FUSED) return ogc_fused_kernel_name(plan->desc.dtype, (plan->desc.m + 31) / 32, plan->lds_buf_bytes);
     if (plan->mode == OGC_MODE_COOP)
         return plan->cluster_split > 0 ? ogc_cluster_kernel_name(plan->desc.dtype, plan->cluster_ksplit) : ogc_coop_kernel_name(plan->desc.dtype);
     const int L = (int)plan->layers.size();

@@ -1818,7 +1818,8 @@ extern "C" const char* ogc_layer_kernel_name(int dtype, int tile, int x_plain, i
     }
     return n;
 }
-extern "C" const char* ogc_fused_kernel_name(int dtype) {
+extern "C" const char* ogc_fused_kernel_name(int dtype, int m_blocks, int lds_buf_bytes) {
     static const char* const names[4] = {"ogc_fused_chain_kernel<0>", "ogc_fused_chain_kernel<1>", "ogc_fused_chain_kernel<2>", "ogc_fused_chain_kernel<3>"};
-    return chain_kernel_name(names, dtype);
+    static const char* const pair[4] = {"ogc_fused_chain_pair_kernel<0>", "ogc_fused_chain_pair_kernel<1>", "ogc_fused_chain_pair_kernel<2>", "ogc_fused_chain_pair_kernel<3>"};
+    return fused_pairs(dtype, m_blocks, (size_t)2 * lds_buf_bytes) ? chain_kernel_name(pair, dtype) : chain_kernel_name(names, dtype);
 }

@@ -405,6 +405,20 @@ def test_auto_mode_choice_follows_the_cost_models():
     b.ogc_mlp_destroy(pl)
 
 
+@pytest.mark.parametrize("dtype, width, m, name", [
+    (b.OGC_BF16, 64, 8192, "kernel<1>"), (b.OGC_BF16, 64, 8193, "pair_kernel<1>"), (b.OGC_BF16, 640, 9000, "pair_kernel<1>"),
+    (b.OGC_BF16, 672, 9000, "kernel<1>"), (b.OGC_F32, 320, 9000, "pair_kernel<0>"), (b.OGC_F32, 352, 9000, "kernel<0>"),
+    (b.OGC_F8, 1280, 9000, "pair_kernel<3>"), (b.OGC_F8, 1344, 9000, "kernel<3>"), (b.OGC_I8, 512, 9000, "pair_kernel<2>"),
+    (b.OGC_I8, 512, 24576, "pair_kernel<2>"), (b.OGC_I8, 1024, 16384, "pair_kernel<2>"), (b.OGC_I8, 1024, 24576, "kernel<2>")])
+def test_fused_kernel_name_tells_the_one_that_runs(dtype, width, m, name):
+    """Two workgroups to a CU from the 257th row tile on, where LDS holds the rows of both."""
+    quant = dict(in_scale=0.05, in_zp=128 if dtype == b.OGC_I8 else 0, out_scale=0.1, out_zp=128 if dtype == b.OGC_I8 else 0) if dtype in (b.OGC_I8, b.OGC_F8) else {}
+    layers = [dict(k=width, n=width, act=b.OGC_ACT_RELU, **quant)] * 2
+    p = b.ogc_mlp_plan(dtype, m, layers, width, width, mode=b.OGC_MODE_FUSED)
+    assert b.ogc_mlp_kernel_name(p, 0) == b.ogc_mlp_kernel_name(p, 1) == "ogc_fused_chain_" + name
+    b.ogc_mlp_destroy(p)
+
+
 # ---- attention subgraph: description checks (host only) ---------------------------------------------------------
 @pytest.mark.parametrize("kw,status", [
     (dict(), 0),
