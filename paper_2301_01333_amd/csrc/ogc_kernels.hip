@@ -11,11 +11,11 @@
 
 #include <stdio.h>
 #include <string.h>
-#include <atomic>
 #include <mutex>
 #include <type_traits>
 
 #include "ogc_internal.h"
+#include "ogc_lds_limit.h"
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -1454,16 +1454,18 @@ template <int DT> static int launch_splitk_reduce(int op, const OgcLayerArgs* a,
     return (int)hipGetLastError();
 }
 
+static int raise_lds(OgcLdsLimit& limit, const void* kern, size_t bytes) {
+    int dev = -1;
+    if (const hipError_t e = hipGetDevice(&dev); e != hipSuccess) return (int)e;
+    return limit.raise(dev, bytes, [&]() { return (int)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); });
+}
+
 template <int DT, int TILE, int XP, int OP>
 static int launch_layer_t(const OgcLayerArgs* a, hipStream_t stream) {
     const OgcTileInfo ti = tile_info_t<TILE>();
     auto kern = ogc_layer_kernel<DT, TILE, XP, OP>;
-    static std::atomic<bool> attr_set{false};  // raising the LDS limit is idempotent; two threads at once only repeat it
-    if (!attr_set.load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ti.lds_bytes);
-        if (e != hipSuccess) return (int)e;
-        attr_set.store(true, std::memory_order_release);
-    }
+    static OgcLdsLimit limit;
+    if (const int rc = raise_lds(limit, (const void*)kern, ti.lds_bytes)) return rc;
     const int nrows = OP ? a->N : a->NB_out * 32;
     const int tiles_n = (nrows + ti.bn - 1) / ti.bn;
     const int tiles_m = (a->M + ti.bm - 1) / ti.bm;
@@ -1492,12 +1494,8 @@ template <int DT, int SHAPE, int XP, int OP, int EPI>
 static int launch_dma_t(const OgcLayerArgs* a, hipStream_t stream) {
     typedef StreamCfg<SHAPE> C;
     auto kern = ogc_layer_dma_kernel<DT, SHAPE, XP, OP, EPI>;
-    static std::atomic<bool> attr_set{false};
-    if (!attr_set.load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
-        if (e != hipSuccess) return (int)e;
-        attr_set.store(true, std::memory_order_release);
-    }
+    static OgcLdsLimit limit;
+    if (const int rc = raise_lds(limit, (const void*)kern, C::LDS)) return rc;
     // (a split-K launch always writes partials; NB_out == 0 marks the chain's last layer, whose width is N)
     const int nrows = (OP || (EPI == 2 && a->NB_out == 0)) ? a->N : a->NB_out * 32;
     const int tiles_n = ((nrows + C::BN - 1) / C::BN) << (EPI == 2 ? a->ksplit_log2 : 0);  // x k ranges when split
@@ -1602,16 +1600,8 @@ template <int DT> static int launch_fused_t(const OgcChainArgs* c, int m_blocks,
     const size_t lds = (size_t)2 * c->lds_buf_bytes;
     const bool pair = fused_pairs(DT, m_blocks, lds);
     auto kern = pair ? ogc_fused_chain_pair_kernel<DT> : ogc_fused_chain_kernel<DT>;
-    {   // the limit only ever grows; the lock keeps raising it and remembering it together
-        static std::mutex mu;
-        static size_t attr_max[2] = {0, 0};
-        std::lock_guard<std::mutex> hold(mu);
-        if (lds > attr_max[pair]) {
-            hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return (int)e;
-            attr_max[pair] = lds;
-        }
-    }
+    static OgcLdsLimit limit[2];
+    if (const int rc = raise_lds(limit[pair], (const void*)kern, lds)) return rc;
     OgcChainArgs args = *c;
     // Up to 16 row tiles per XCD before the next XCD is used: every XCD that takes part fetches all the weights
     // into its own L2, so a small batch on one XCD asks the fabric for them once instead of eight times
@@ -1680,16 +1670,8 @@ extern "C" int ogc_cluster_xcds(int m_blocks, int split, int spread) {
 template <int DT, int KSPLIT> static int launch_cluster_t(const OgcChainArgs* c, int m_blocks, int split, int spread, int cus, void* sync, hipStream_t stream) {
     auto kern = KSPLIT ? ogc_cluster_ksplit_chain_kernel<DT> : ogc_cluster_chain_kernel<DT>;
     const size_t lds = KSPLIT ? (size_t)c->lds_buf_bytes + OGC_KS_RED_BYTES : (size_t)2 * c->lds_buf_bytes;
-    {   // the limit only ever grows; the lock keeps raising it and remembering it together
-        static std::mutex mu;
-        static size_t attr_max = 0;
-        std::lock_guard<std::mutex> hold(mu);
-        if (lds > attr_max) {
-            hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return (int)e;
-            attr_max = lds;
-        }
-    }
+    static OgcLdsLimit limit;
+    if (const int rc = raise_lds(limit, (const void*)kern, lds)) return rc;
     const int xcds = ogc_cluster_xcds(m_blocks, split, spread);
     // every member waits for the others of its tile: all of them need a CU at once (the plan assumed 256 CUs)
     if (xcds < 0 || (long)m_blocks * split > cus) return (int)hipErrorInvalidValue;

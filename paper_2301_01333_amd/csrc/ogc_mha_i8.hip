@@ -22,7 +22,6 @@
 #include <math.h>
 #include <stdint.h>
 #include <stdio.h>
-#include <atomic>
 #include <type_traits>
 
 #include "ogc_mha.h"
@@ -604,12 +603,9 @@ template <int D32> void launch_i8(const MhaI8Args& a, bool stream, dim3 grid, hi
     }
     const int keys = (a.seq + MHA8_UNIT - 1) / MHA8_UNIT * MHA8_UNIT;
     const size_t lds = Mha8<D32>::RING + (size_t)(keys < MHA8_LDS_KEYS ? keys : MHA8_LDS_KEYS) * 4 + 64 * 4;
-    static std::atomic<bool> raised{false};  // (two threads at once only repeat it)
-    if (lds > 65536 && !raised.load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute((const void*)ogc_mha_i8_stream_kernel<D32>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)(Mha8<D32>::RING + MHA8_LDS_KEYS * 4 + 64 * 4)) != hipSuccess)
+    if (lds > 65536) {  // said at every such launch: the limit belongs to the current device
+        if (hipFuncSetAttribute((const void*)ogc_mha_i8_stream_kernel<D32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
             return;  // reported by the caller
-        raised.store(true, std::memory_order_release);
     }
     hipLaunchKernelGGL((ogc_mha_i8_stream_kernel<D32>), grid, dim3(256), lds, s, a);
 }
