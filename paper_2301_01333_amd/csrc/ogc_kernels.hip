@@ -765,21 +765,19 @@ OGC_DEV void fused_blocks(const OgcLayerArgs& a, const uint8_t* xin, YT xout, in
 template <int DT, int OUT_PLAIN, int G, class YT>
 OGC_DEV void fused_layer(const OgcLayerArgs& a, const uint8_t* xin, YT xout, int m0, int wave, int waves, int lane) {
     const int nblocks = OUT_PLAIN ? ((a.N + 31) >> 5) : a.NB_out;
-    constexpr int MOST = G == 0 && DT != OGC_BF16 ? 2 : 4;  // blocks of a wave at a time (128 registers hold four in bf16 only)
-    for (int nb0 = wave; nb0 < nblocks; nb0 += MOST * waves) {
-        const int cnt = (nblocks - nb0 + waves - 1) / waves;  // blocks of this wave from nb0 on
-        if constexpr (MOST == 4) {
-            if (cnt >= 4) {
-                fused_blocks<DT, OUT_PLAIN, 4, (G > 4 ? 4 : G)>(a, xin, xout, m0, nb0, lane, waves);
-                continue;
-            }
-            if (cnt == 3) {
-                fused_blocks<DT, OUT_PLAIN, 3, (G > 4 ? 4 : G)>(a, xin, xout, m0, nb0, lane, waves);
-                continue;
-            }
+    if constexpr (G == 0 && DT != OGC_BF16) {  // two blocks at a time: 128 registers hold four in bf16 only
+        for (int nb0 = wave; nb0 < nblocks; nb0 += 2 * waves) {
+            if (nb0 + waves < nblocks) fused_blocks<DT, OUT_PLAIN, 2, G>(a, xin, xout, m0, nb0, lane, waves);
+            else fused_blocks<DT, OUT_PLAIN, 1, G>(a, xin, xout, m0, nb0, lane, waves);
         }
-        if (cnt >= 2) fused_blocks<DT, OUT_PLAIN, 2, G>(a, xin, xout, m0, nb0, lane, waves);
-        else fused_blocks<DT, OUT_PLAIN, 1, G>(a, xin, xout, m0, nb0, lane, waves);
+    } else {
+        for (int nb0 = wave; nb0 < nblocks; nb0 += 4 * waves) {
+            const int cnt = (nblocks - nb0 + waves - 1) / waves;  // blocks of this wave from nb0 on
+            if (cnt >= 4) fused_blocks<DT, OUT_PLAIN, 4, (G > 4 ? 4 : G)>(a, xin, xout, m0, nb0, lane, waves);
+            else if (cnt == 3) fused_blocks<DT, OUT_PLAIN, 3, (G > 4 ? 4 : G)>(a, xin, xout, m0, nb0, lane, waves);
+            else if (cnt == 2) fused_blocks<DT, OUT_PLAIN, 2, G>(a, xin, xout, m0, nb0, lane, waves);
+            else fused_blocks<DT, OUT_PLAIN, 1, G>(a, xin, xout, m0, nb0, lane, waves);
+        }
     }
 }
 
