@@ -22,8 +22,7 @@
  * so both [batch, seq, heads*d] (what a projection layer leaves: stride_b = S*H*d, stride_h = d, stride_s = H*d)
  * and [batch, heads, seq, d] work without a transpose pass.  Every stride must be a multiple of 16 bytes and
  * every base pointer 16-byte aligned.  mask is fp32 [batch][seq], finite values (use -10000, not -infinity), or
- * NULL; its values are held to 2.35e38 in magnitude (3e38 * scale in bf16, where scale is below 0.78), so that the lowest
- * floats, which do not fit a score, are one value.  o has q's dtype.  The library allocates nothing and keeps no state between calls.
+ * NULL; values below -2.3e38 (bf16: or below -3e38 * scale), which no score holds, count as that one value.  o has q's dtype.  The library allocates nothing and keeps no state between calls.
  *
  * Arithmetic: OGC_F32 multiplies fp32 operands with fp32 accumulation throughout.  OGC_BF16 multiplies bf16
  * operands with fp32 accumulation; scores, exponentials and row sums are fp32; the softmax weights are rounded

@@ -71,7 +71,7 @@ MHA_DEV uint32_t pack_bf16(float lo, float hi) {  // round to nearest even, two 
 MHA_DEV uint32_t div_magic(uint32_t n, uint32_t d, uint32_t m) { return m ? __umulhi(n, m) : n / d; }
 
 // a mask of finite values stays finite when it is scaled (-infinity is for keys beyond the sequence); NaN passes
-constexpr float MHA_F32_MAX = 3.40282347e38f;
+constexpr float MHA_F32_MAX = 3.40282347e38f, MHA_MASK_LOW = -2.3e38f;  // (the latter is finite in base 2 still)
 MHA_DEV float finite_mask(float x, float most) { return x == x ? __builtin_fminf(__builtin_fmaxf(x, -most), most) : x; }
 
 #include "ogc_mha_bf16.h"
@@ -203,7 +203,7 @@ template <int DT, int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_staged_
                 for (int j = 0; j < 4; ++j) *(int*)(vt_lds + (4 * c + j) * VSTR + kl * 4) = vreg[i][0][j];
             }
         }
-        if (tid < KB) m_lds[tid] = mpad ? -INFINITY : finite_mask(mreg * LOG2E, MHA_F32_MAX);
+        if (tid < KB) m_lds[tid] = mpad ? -INFINITY : (mreg < MHA_MASK_LOW ? MHA_MASK_LOW : mreg) * LOG2E;
     };
 
     const int nkb = (S + KB - 1) / KB;

@@ -65,10 +65,9 @@ MHA8_DEV int other_half_i(int x) {
     return (int)((threadIdx.x & 32) ? a : b);
 }
 
-// a mask value in the base-2 domain; finite ones stay finite (-infinity is for keys beyond the sequence), NaN passes
+// a mask value in the base-2 domain; the lowest stay finite (-infinity is for keys beyond the sequence), NaN passes
 MHA8_DEV float base2_mask(float m) {
-    const float x = m * 1.44269504088896340736f;
-    return x == x ? fminf(fmaxf(x, -3.40282347e38f), 3.40282347e38f) : x;
+    return (m < -2.3e38f ? -2.3e38f : m) * 1.44269504088896340736f;
 }
 
 // The plain kernel: keys and values through registers, both passes over 64-key blocks.  For launches that do not fill the
