@@ -495,13 +495,15 @@ int query_groups(const ogc_mha_desc* d) {
 // The streaming body or the staged one (bf16).  Streaming addresses a lane's piece by 32 bits of byte offset from its unit's
 // first row and divides the mask by the scalar: wider token strides, and scalars that are not positive or have no fp32
 // reciprocal to speak of, are staged.  Otherwise the faster one.  Staged / streaming, us, batch x heads x seq, with a mask:
-//   32 channels: 1x8x17 4.3 / 4.3, so staged as before;  256x12x64 18.3 / 13.6;  128x12x96 14.9 / 10.2;  8x12x197 6.8 / 6.5;  8x8x256 9.2 / 8.4;
-//     64x16x512 77 / 58.
+//   32 channels: 1x8x17 4.3 / 4.3;  36x12x63 4.9 / 5.2;  78x8x101 7.0 / 7.3;  256x12x64 18.3 / 13.6;  1x12x96 5.0 / 4.8;
+//     128x12x96 14.9 / 10.2: up to 127 keys with addends, streaming must save a unit over staged blocks of 64, or fill the chip
+//     several times over.  8x12x197 6.8 / 6.5;  8x8x256 9.2 / 8.4;  64x16x512 77 / 58.
 //   64: 1x8x32 4.4 / 4.8;  256x12x64 19.6 / 21.2;  128x12x96 17.4 / 17.2;  128x12x128 20.0 / 20.8: in two staged blocks or less
 //     streaming must save a unit to pay for its start.  8x12x192 6.6 / 7.0 (no mask 6.3 / 6.3);  8x12x197 7.6 / 7.8;  8x8x256
 //     10.5 / 10.6;  64x12x192 21.6 / 20.7;  64x16x256 32.4 / 32.1: up to four, addends need a chip full of workgroups
 //     (two on each of the 256 CUs).  8x8x384 13.8 / 13.7;  64x8x384 39.6 / 37.3;  64x16x512 95.7 / 88.6.
-//   96: 1x8x32 4.8 / 5.3;  1x16x64 5.3 / 5.2;  64x12x64 12.2 / 10.1;  8x8x384 12.7 / 12.4;  64x16x512 174 / 158.
+//   96: 1x8x32 4.8 / 5.3;  7x12x64 5.3 / 5.5;  3x12x102 6.7 / 7.1;  1x12x96 6.7 / 6.1;  64x12x64 12.2 / 10.1: as 32 channels, from one
+//     workgroup a CU on.  8x8x384 12.7 / 12.4;  64x16x512 174 / 158.
 //   128: 256x12x64 37.3 / 39.4;  128x16x128 48.4 / 50.4;  64x16x256 60.1 / 60.8;  16x8x512 27.8 / 26.8;  64x8x512 96.7 / 91.3;
 //     32x16x1024 361 / 332;  1x8x8192 310 / 270, but 1x8x4096 102 / 112 (one workgroup a CU) and 46x4x444 35.0 / 36.4 (a third
 //     one left over): streaming from 384 keys on, where CUs have two workgroups each, or four and more.
@@ -514,9 +516,9 @@ bool stream_case(const ogc_mha_desc* d, const float* mask) {
     const int units = d->seq <= 32 ? 2 : (d->seq + 31) / 32, blocks = (d->seq + 63) / 64;
     const int64_t groups = (int64_t)d->batch * d->heads * ((d->seq + 128 * query_groups(d) - 1) / (128 * query_groups(d)));
     switch (d->head_dim) {
-    case 32:
-    case 96: return d->seq > 32;
     case 64: return blocks > 4 || (blocks > 2 ? plain || groups > 512 : units < 2 * blocks);
+    case 32:
+    case 96: return d->seq >= 128 || plain || units < 2 * blocks || (d->seq > 32 && groups > (d->head_dim == 32 ? 1024 : 256));
     default: return d->seq >= 384 && (groups == 512 || groups >= 1024);
     }
 }

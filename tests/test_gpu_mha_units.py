@@ -149,9 +149,9 @@ def test_masks_of_the_lowest_float(oracle_mod, dtype, batch, seq, head_dim):
 def test_the_first_reference_covers_64_keys(head_dim):
     """64 keys: the weights are taken against the row's maximum, so the largest is 1 and rounds to itself.  The outputs are then as
     far from float64 as that arithmetic, written out here, is; against the maximum of 32 keys they were 1.6 % further."""
-    wl = synth.make_mha("bf16", 16, 64, 8 * head_dim, 8, 8050 + head_dim, name="first reference")
+    wl = synth.make_mha("bf16", 16, 64, 8 * head_dim, 8, 8050 + head_dim, name="first reference", has_mask=False)
     q, k, v = (heads_view(as_f64(t), wl) for t in (wl.q, wl.k, wl.v))
-    s = np.matmul(q, np.swapaxes(k, -1, -2)) * wl.scale + wl.mask[:, None, None, :]
+    s = np.matmul(q, np.swapaxes(k, -1, -2)) * wl.scale
     p = np.exp(s - s.max(-1, keepdims=True))
     w = as_f64(synth.f32_to_bf16_bits(p.astype(np.float32)))
     o = as_f64(synth.f32_to_bf16_bits((np.matmul(w, v) / w.sum(-1, keepdims=True)).astype(np.float32)))
@@ -161,8 +161,8 @@ def test_the_first_reference_covers_64_keys(head_dim):
 
 
 @pytest.mark.parametrize("head_dim, seq, name", [(64, 64, "general_kernel<2, 0, 0, 1>"), (64, 96, "kernel<1, 2, 0, 0, 1>"), (64, 97, "general_kernel<2, 0, 0, 1>"),
-                                                 (64, 129, "general_kernel<2, 0, 0, 1>"), (64, 257, "kernel<1, 2, 0, 0, 2>"), (96, 32, "general_kernel<3, 0, 0, 1>"), (96, 33, "kernel<1, 3, 0, 0, 1>"),
-                                                 (32, 32, "general_kernel<1, 0, 0, 1>"), (32, 33, "kernel<1, 1, 0, 0, 1>"), (128, 512, "kernel<1, 4, 0, 0, 1>")])
+                                                 (64, 129, "general_kernel<2, 0, 0, 1>"), (64, 257, "kernel<1, 2, 0, 0, 2>"), (96, 64, "general_kernel<3, 0, 0, 1>"), (96, 65, "kernel<1, 3, 0, 0, 1>"), (96, 97, "general_kernel<3, 0, 0, 1>"), (96, 128, "kernel<1, 3, 0, 0, 1>"),
+                                                 (32, 64, "general_kernel<1, 0, 0, 1>"), (32, 65, "kernel<1, 1, 0, 0, 1>"), (128, 512, "kernel<1, 4, 0, 0, 1>")])
 def test_either_side_of_the_rule(oracle_mod, head_dim, seq, name):
     wl = synth.make_mha("bf16", 2, seq, 2 * head_dim, 2, 8000 + seq + head_dim, name="rule S=%d d=%d" % (seq, head_dim))
     assert binding.ogc_mha_kernel_name(binding.mha_desc(binding.OGC_BF16, 2, 2, seq, head_dim, wl.scale), True) == "ogc_mha_" + name
@@ -171,6 +171,7 @@ def test_either_side_of_the_rule(oracle_mod, head_dim, seq, name):
 
 
 @pytest.mark.parametrize("batch, heads, seq, head_dim, name", [
+    (257, 4, 57, 32, "kernel<1, 1, 0, 0, 1>"), (257, 4, 33, 32, "kernel<1, 1, 0, 0, 1>"), (65, 4, 102, 96, "kernel<1, 3, 0, 0, 1>"), (65, 4, 64, 96, "kernel<1, 3, 0, 0, 1>"),
     (129, 2, 129, 64, "kernel<1, 2, 0, 0, 1>"), (129, 2, 192, 64, "kernel<1, 2, 0, 0, 1>"), (129, 2, 225, 64, "kernel<1, 2, 0, 0, 1>"),
     (257, 2, 256, 64, "kernel<1, 2, 0, 0, 2>"), (171, 2, 384, 128, "stream_kernel<4, 0, 0>"), (128, 2, 417, 128, "stream_kernel<4, 0, 0>"),
     (16, 2, 4200, 128, "stream_kernel<4, 0, 0>")])
