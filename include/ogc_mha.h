@@ -79,7 +79,7 @@ ogc_status ogc_mha_run(const ogc_mha_desc* desc, const void* q, const void* k, c
  * which a wavefront owns 64 queries instead of 32 (the last template argument; desc->query_groups forces either).
  * bf16 has two bodies, one that streams keys and values into LDS and one that stages them in registers: ogc_mha_kernel
  * streams up to 96 channels and stages 128, ogc_mha_general_kernel stages up to 96 (short sequences, scales that are not
- * positive or extreme, token strides of 2^26 bytes and more) and ogc_mha_stream_kernel streams 128 (large launches). */
+ * positive or extreme, token strides beyond 2^26 bytes) and ogc_mha_stream_kernel streams 128 (large launches). */
 const char* ogc_mha_kernel_name(const ogc_mha_desc* desc, int32_t has_mask);
 
 /* Quantization scales of the Int8 attention: real value = scale * integer, zero point 0 for all four tensors

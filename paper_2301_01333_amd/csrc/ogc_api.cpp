@@ -550,8 +550,9 @@ ogc_status ogc_mlp_plan_with_overrides(const ogc_mlp_desc* desc, const ogc_plan_
     }
     if (mode == OGC_MODE_AUTO) {
         // The mode whose estimate is lowest (section "cost model" of the sources above: each mode has its own fitted
-        // model).  The fused kernel is a candidate only where it was timed without its cliff: bf16 / fp32 chains
-        // whose weights exceed about 2.5 MB run several times slower per byte in it.
+        // model).  The fused kernel is a candidate only where its model was fitted: bf16 / fp32 chains whose weights exceed
+        // about 2.5 MB ran several times slower per byte in the kernel of that sweep (the present one keeps its loads in
+        // flight and does not, but has not been swept).
         // A single-launch mode wins ties within 7 %: its model is the tighter one, and it keeps the intermediates
         // on chip.
         int single = -1;

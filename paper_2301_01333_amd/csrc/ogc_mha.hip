@@ -2,9 +2,9 @@
 // matmuls, the scalar, the mask and the softmax in one kernel, scores never leaving the compute unit.
 //
 // One workgroup = 4 wavefronts = 128 queries of one (batch, head); a wavefront owns 32 queries (64, as two
-// groups of 32, in the bf16 variant for head dimensions up to 64).  Keys and values stream through LDS 32 at a time
-// (bf16: straight from global memory, see ogc_mha_bf16.h; fp32: prefetched one block ahead in registers).  Both products
-// are computed TRANSPOSED so that a lane owns one query:
+// groups of 32, in the bf16 variant for head dimensions up to 64).  Keys and values go through LDS in blocks: straight from
+// global memory, 32 keys at a time (the streaming body, ogc_mha_bf16.h), or prefetched one block ahead in registers (the staged
+// body: fp32, and the bf16 calls that it is the faster for).  Both products are computed TRANSPOSED so that a lane owns one query:
 //
 //   S^T[key][query] = K * Q^T     first MFMA operand = 32 keys x k from LDS, second = Q^T, held in registers
 //   O^T[c][query]   = V^T * P^T   first operand = 32 channels x keys from LDS (V is transposed on its way into LDS,

@@ -23,11 +23,11 @@
 //     (scores whose spacing in fp32 is no longer small against 1) always takes that way, which subtracts exactly;
 //   * the scores of the next unit and the second product of the one before are computed next to the exponentials of
 //     this one: the matrix pipe and the vector ALU work side by side inside a wavefront.
-// Measured against the kernel this replaces (64-key blocks through registers, maximum of every block, transposing LDS
-// writes), both on one card: batch 128 x 16 heads x 512 tokens x 64, padding mask: 213 -> 188 us (650 -> 730 TFLOP/s);
-// batch 128 x 8 x 384 x 128: 126 -> 118 us; 32 x 8 x 512 x 32: 22.7 -> 18.0; 128 x 8 x 128 x 96: 25.5 -> 21.5;
-// 1 x 8 x 8192 x 128: 295 -> 270.  Of the 188 us, about 30 are the tensors' way from HBM (154 us with all of them in
-// cache), and 16 units are too few to hide a workgroup's first loads and its end behind its one neighbour on the
+// Measured against the staged body (64-key blocks through registers, maximum of every block, transposing LDS writes), both
+// on one card: batch 128 x 16 heads x 512 tokens x 64, padding mask: 210 -> 193 us (655 -> 713 TFLOP/s); 64 x 16 x 512 x 32:
+// 77 -> 58; 64 x 16 x 512 x 96: 174 -> 158; 1 x 8 x 8192 x 128: 310 -> 270.  More, and where it is the slower, at stream_case.
+// Counters at the first of these: vector ALU 48 % of the SIMDs' cycles, matrix pipe 31 %.  About 30 of its us are the tensors' way
+// from HBM, and 16 units are too few to hide a workgroup's first loads and its end behind its one neighbour on the
 // compute unit: 8 x 16 x 2048 x 64, the same arithmetic, takes 146 us.  Tried: workgroups that walk over several tiles
 // with the loads running on across them (no faster: the clock gives way), one query group per wavefront for long
 // sequences (LDS reads, 196 us), four pairs of weights between matrix instructions (182).

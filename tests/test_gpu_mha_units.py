@@ -1,5 +1,5 @@
-"""The bf16 attention kernel at the edges of its units of 32 keys and of the rule that chooses between its forms (no addend,
-addend in LDS, general), against the float64 oracle on the same inputs: within 1e-2, as the other bf16 attention tests.  The
+"""The bf16 attention kernels at the edges of their units of 32 keys and of the rule that chooses between the streaming and the
+staged body, against the float64 oracle on the same inputs: within 1e-2, as the other bf16 attention tests.  The
 streaming int8 kernel at the edges of its units of 64 keys, by the gate of the other int8 attention tests."""
 import math
 
