@@ -486,8 +486,8 @@ bool plain_case(const ogc_mha_desc* d, const float* mask) {
 
 // 32-query groups per wavefront.  Two where the registers allow it (bf16, head_dim <= 64) and the sequence is long
 // enough to keep the four wavefronts of a workgroup busy: the staged body, for which the line was drawn, is then no longer
-// bound by LDS reads.  Streaming 64 x 16 x 512 x 64 takes 88 us with two and 96 with one; with 32 channels one is the faster
-// in small launches (8 x 8 x 256: 6.8 against 8.4) and the slower in large ones (64 x 16 x 512: 64 against 58).
+// bound by LDS reads.  Both bodies gain by two groups in the largest launches only (one group / two, us, streaming: 64 x 16 x 512
+// x 64 95 / 88, x 32 62 / 57; but 64 x 8 x 384 x 64 30.8 / 36.6, 8 x 8 x 256 x 64 7.4 / 10.2, x 32 6.9 / 8.6).
 int query_groups(const ogc_mha_desc* d) {
     const bool can = d->dtype == OGC_BF16 && d->head_dim <= 64;
     if (d->query_groups != 0) return (d->query_groups == 2 && can) ? 2 : 1;
@@ -507,8 +507,8 @@ int query_groups(const ogc_mha_desc* d) {
 //   96: 1x8x32 4.8 / 5.3;  7x12x64 5.3 / 5.5;  3x12x102 6.7 / 7.1;  1x12x96 6.7 / 6.1;  64x12x64 12.2 / 10.1: as 32 channels, from one
 //     workgroup a CU on.  8x8x384 12.7 / 12.4;  64x16x512 174 / 158.
 //   128: 256x12x64 37.3 / 39.4;  128x16x128 48.4 / 50.4;  64x16x256 60.1 / 60.8;  16x8x512 27.8 / 26.8;  64x8x512 96.7 / 91.3;
-//     32x16x1024 361 / 332;  1x8x8192 310 / 270, but 1x8x4096 102 / 112 (one workgroup a CU) and 46x4x444 35.0 / 36.4 (a third
-//     one left over): streaming from 384 keys on, where CUs have two workgroups each, or four and more.
+//     32x16x1024 361 / 332;  10x16x640 53.8 / 50.2;  1x8x8192 310 / 270, but 1x8x4096 102 / 112 (one workgroup a CU) and 46x4x444
+//     33.3 / 35.0 (a third one for some CUs): streaming from 384 keys on, where every CU has two workgroups, or three and more.
 bool stream_case(const ogc_mha_desc* d, const float* mask) {
     if (d->dtype != OGC_BF16) return false;
     const int64_t most = (int64_t)1 << 31;
@@ -521,7 +521,7 @@ bool stream_case(const ogc_mha_desc* d, const float* mask) {
     case 64: return blocks > 4 || (blocks > 2 ? plain || groups > 512 : units < 2 * blocks);
     case 32:
     case 96: return d->seq >= 128 || plain || units < 2 * blocks || (d->seq > 32 && groups > (d->head_dim == 32 ? 1024 : 256));
-    default: return d->seq >= 384 && (groups == 512 || groups >= 1024);
+    default: return d->seq >= 384 && (groups == 512 || groups >= 768);
     }
 }
 bool stride_ok(const int64_t s[3], int elt) {

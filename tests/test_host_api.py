@@ -442,6 +442,13 @@ def test_mha_validate(kw, status):
     assert b.ogc_mha_validate(b.mha_desc(**args)) == status
 
 
+@pytest.mark.parametrize("batch, heads, seq, name", [(64, 4, 384, "stream_kernel<4, 0, 0>"), (51, 5, 384, "kernel<1, 4, 0, 0, 1>"), (32, 4, 512, "stream_kernel<4, 0, 0>"),
+                                                     (31, 4, 512, "kernel<1, 4, 0, 0, 1>"), (64, 4, 383, "kernel<1, 4, 0, 0, 1>")])
+def test_mha_128_channels_stream_in_large_launches(batch, heads, seq, name):
+    """From 384 keys on, with two workgroups or at least three for each of the 256 CUs."""
+    assert b.ogc_mha_kernel_name(b.mha_desc(b.OGC_BF16, batch, heads, seq, 128, 0.1)) == "ogc_mha_" + name
+
+
 def test_mha_kernel_names_and_null_checks():
     d = b.mha_desc(b.OGC_BF16, 2, 8, 128, 96, 0.1, b.OGC_SOFTMAX_FAST)
     assert b.ogc_mha_kernel_name(d) == "ogc_mha_kernel<1, 3, 1, 0, 1>"
