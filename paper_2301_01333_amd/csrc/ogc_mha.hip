@@ -4,7 +4,7 @@
 // One workgroup = 4 wavefronts = 128 queries of one (batch, head); a wavefront owns 32 queries (64, as two
 // groups of 32, in the bf16 variant for head dimensions up to 64).  Keys and values go through LDS in blocks: straight from
 // global memory, 32 keys at a time (the streaming body, ogc_mha_bf16.h), or prefetched one block ahead in registers (the staged
-// body: fp32, and the bf16 calls that it is the faster for).  Both products are computed TRANSPOSED so that a lane owns one query:
+// body: fp32, split into bf16 pieces on the way, ogc_mha_f32.h, or as it is; and the bf16 calls that it is the faster for).  Both products are computed TRANSPOSED so that a lane owns one query:
 //
 //   S^T[key][query] = K * Q^T     first MFMA operand = 32 keys x k from LDS, second = Q^T, held in registers
 //   O^T[c][query]   = V^T * P^T   first operand = 32 channels x keys from LDS (V is transposed on its way into LDS,
@@ -84,31 +84,36 @@ template <> struct MhaCfg<OGC_F32> {
     static constexpr int E = 4, KB = 32;
 };
 
-// The staged body: keys and values through registers, blocks of 64 (bf16) or 32 (fp32) keys.  It serves fp32, bf16 heads of
+// The staged body: keys and values through registers, blocks of 64 (bf16) or 32 (fp32) keys.  It serves fp32 heads of 128
+// channels, short fp32 sequences and what the split body cannot answer, bf16 heads of
 // 128 channels, and the bf16 calls that the streaming body does not take (stream_case below).
 // DT: OGC_F32 / OGC_BF16.  D32 = head_dim / 32.  FAST: softmax without the running maximum.  PLAIN: no mask, the
 // sequence is a whole number of key blocks and the scalar is positive, so no key needs an addend.
 // QS: 32-query groups per wavefront (1 or 2).  With 2, every key / value operand read from LDS feeds two matrix
 // instructions (one per group): the bf16 form is bound by LDS reads, one KiB per instruction, otherwise.
-template <int DT, int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_staged_body(const MhaArgs& a) {
+// RUNS: an XCD takes a contiguous run of (batch, head) pairs, as in mha_split_body, which may leave its tile to this body.
+template <int DT, int D32> struct MhaStaged {
+    static constexpr int E = MhaCfg<DT>::E, KB = MhaCfg<DT>::KB, D = D32 * 32;
+    static constexpr int KSTR = D * E + 16;     // bytes per key row of K in LDS (padded)
+    static constexpr int VSTR = KB * E + 16;    // bytes per channel row of V^T in LDS (padded)
+    static constexpr int K_BYTES = KB * KSTR, V_BYTES = D * VSTR;
+};
+template <int DT, int D32, int FAST, int PLAIN, int QS, int RUNS = 0>
+MHA_DEV void mha_staged_body(const MhaArgs& a, uint8_t* k_lds, uint8_t* vt_lds, float* m_lds) {
     constexpr int E = MhaCfg<DT>::E, KB = MhaCfg<DT>::KB, D = D32 * 32;
     constexpr int SB = KB / 32;                 // 32-key sub-blocks per block
-    constexpr int KSTR = D * E + 16;            // bytes per key row of K in LDS (padded)
-    constexpr int VSTR = KB * E + 16;           // bytes per channel row of V^T in LDS (padded)
+    constexpr int KSTR = MhaStaged<DT, D32>::KSTR, VSTR = MhaStaged<DT, D32>::VSTR;
     constexpr int CH = D * E / 16;              // 16-byte chunks per token row
     constexpr int KU = KB * CH / 256;                          // 16-byte chunks of K per thread
     constexpr int KP = KB / 2;                                 // bf16: key pairs per block
     constexpr int VU = DT == OGC_BF16 ? (KP * CH + 255) / 256 : D32;  // V units per thread (bf16: a unit is two keys)
-    __shared__ __attribute__((aligned(16))) uint8_t k_lds[KB * KSTR];
-    __shared__ __attribute__((aligned(16))) uint8_t vt_lds[D * VSTR];
-    __shared__ __attribute__((aligned(16))) float m_lds[KB];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, col = lane & 31;
     int bh, qt;
     if (a.xcd_order) {  // consecutive workgroup ids go round the 8 XCDs: keep one (batch, head) on one of them
         const int L = blockIdx.x, x = L & 7, r = L >> 3;
-        bh = x + 8 * (r / a.q_tiles);
-        qt = r % a.q_tiles;
+        bh = RUNS ? (int)(x * (gridDim.x >> 3) + r) / a.q_tiles : x + 8 * (r / a.q_tiles);
+        qt = r % a.q_tiles;  // (a run is a whole number of pairs)
     } else {
         bh = blockIdx.x / a.q_tiles;
         qt = blockIdx.x % a.q_tiles;
@@ -404,9 +409,19 @@ template <int DT, int D32, int FAST, int PLAIN, int QS> MHA_DEV void mha_staged_
     }
 }
 
-// The body of ogc_mha_kernel: bf16 heads of up to 96 channels stream, the others are staged.  (The other body of a bf16
-// call has a kernel of its own; which one runs is stream_case's to say.)
+// the staged body with LDS of its own
+#define MHA_STAGED(DT, QS)                                                                   \
+    __shared__ __attribute__((aligned(16))) uint8_t k_lds[MhaStaged<DT, D32>::K_BYTES];      \
+    __shared__ __attribute__((aligned(16))) uint8_t vt_lds[MhaStaged<DT, D32>::V_BYTES];     \
+    __shared__ __attribute__((aligned(16))) float m_lds[MhaStaged<DT, D32>::KB];             \
+    mha_staged_body<DT, D32, FAST, PLAIN, QS>(a, k_lds, vt_lds, m_lds)
+
+#include "ogc_mha_f32.h"
+
+// The body of ogc_mha_kernel: fp32 heads of up to 96 channels are split, bf16 heads of up to 96 channels stream, the others are
+// staged.  (The other body of a call has a kernel of its own; which one runs is stream_case's to say.)
 constexpr bool mha_streams(int dt, int d32) { return dt == OGC_BF16 && d32 <= 3; }
+constexpr bool mha_splits(int dt, int d32) { return dt == OGC_F32 && d32 <= 3; }
 // Wavefronts per SIMD the registers are held to: the streaming body with 32 channels, or 64 and one 32-query group, fits three.
 constexpr int mha_waves(int dt, int d32, int qs) { return mha_streams(dt, d32) && d32 * qs <= 2 ? 3 : 2; }
 
@@ -416,14 +431,22 @@ __global__ __launch_bounds__(256, mha_waves(DT, D32, QS)) void ogc_mha_kernel(Mh
     if constexpr (mha_streams(DT, D32)) {
         extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
         mha_stream_body<D32, FAST, PLAIN, QS>(a, (mha_lds_u8*)smem);
+    } else if constexpr (mha_splits(DT, D32)) {
+        extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+        mha_split_body<D32, FAST, PLAIN>(a, smem);
     } else {
-        mha_staged_body<DT, D32, FAST, PLAIN, QS>(a);
+        MHA_STAGED(DT, QS);
     }
+}
+
+// fp32 heads of up to 96 channels that are staged (split_case).
+template <int D32, int FAST, int PLAIN> __global__ __launch_bounds__(256, 2) void ogc_mha_f32_kernel(MhaArgs a) {
+    MHA_STAGED(OGC_F32, 1);
 }
 
 // bf16 calls with up to 96 channels that are staged, and those with 128 that stream.
 template <int D32, int FAST, int PLAIN, int QS> __global__ __launch_bounds__(256, 2) void ogc_mha_general_kernel(MhaArgs a) {
-    mha_staged_body<OGC_BF16, D32, FAST, PLAIN, QS>(a);
+    MHA_STAGED(OGC_BF16, QS);
 }
 template <int D32, int FAST, int PLAIN> __global__ __launch_bounds__(256, 2) void ogc_mha_stream_kernel(MhaArgs a) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -442,6 +465,17 @@ template <int DT, int D32, int FAST, int PLAIN, int QS> hipError_t launch_one(bo
     if constexpr (mha_streams(DT, D32)) {  // 64 KiB of LDS at most
         if (stream) hipLaunchKernelGGL((ogc_mha_kernel<DT, D32, FAST, PLAIN, QS>), grid, dim3(256), stream_lds(D32, a.seq, PLAIN), st, a);
         else hipLaunchKernelGGL((ogc_mha_general_kernel<D32, FAST, PLAIN, QS>), grid, dim3(256), 0, st, a);
+    } else if constexpr (mha_splits(DT, D32)) {
+        if (!stream) {
+            hipLaunchKernelGGL((ogc_mha_f32_kernel<D32, FAST, PLAIN>), grid, dim3(256), 0, st, a);
+            return hipGetLastError();
+        }
+        if (MhaS<D32>::BYTES > 65536) {  // said at every such launch: the limit belongs to the current device
+            const hipError_t e = hipFuncSetAttribute((const void*)ogc_mha_kernel<DT, D32, FAST, PLAIN, QS>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, MhaS<D32>::BYTES);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL((ogc_mha_kernel<DT, D32, FAST, PLAIN, QS>), grid, dim3(256), MhaS<D32>::BYTES, st, a);
     } else {
         if constexpr (DT == OGC_BF16) {
             if (stream) {
@@ -494,6 +528,18 @@ int query_groups(const ogc_mha_desc* d) {
     return (can && d->seq >= 256) ? 2 : 1;
 }
 
+// The split body or the staged one (fp32).  The split body multiplies a row's number by 24 bits of stride, and takes up to 96
+// channels (128: its registers do not hold a query's pieces).  Its first block costs more.  Staged / split, us, batch x heads x seq,
+// with a mask:
+//   32 channels: 64x12x33 10.5 / 11.0;  64x12x64 11.9 / 12.8;  64x12x96 16.4 / 16.3;  32x16x128 15.5 / 13.7;  8x16x512 43.7 / 31.6.
+//   64: 1x8x16 7.1 / 7.2;  1x8x33 7.6 / 7.4;  64x12x33 18.4 / 16.5;  64x12x96 28.2 / 25.5;  4x12x197 21.0 / 15.5;  32x16x512 277 / 197.
+//   96: 1x8x33 10.0 / 10.1;  64x12x64 30.1 / 28.9;  1x8x64 10.4 / 10.6;  64x12x96 43.7 / 44.5;  32x16x128 38.8 / 33.3;  8x16x512 110 / 78.
+bool split_case(const ogc_mha_desc* d) {
+    const int64_t most = (int64_t)1 << 24;
+    if (d->head_dim > 96 || d->k_stride[2] * 4 >= most || d->v_stride[2] * 4 >= most) return false;
+    return d->seq > (d->head_dim == 64 ? 32 : 96);
+}
+
 // The streaming body or the staged one (bf16).  Streaming addresses a lane's piece by 32 bits of byte offset from its unit's
 // first row and divides the mask by the scalar: wider token strides, and scalars that are not positive or have no fp32
 // reciprocal to speak of, are staged.  Otherwise the faster one.  Staged / streaming, us, batch x heads x seq, with a mask:
@@ -510,7 +556,7 @@ int query_groups(const ogc_mha_desc* d) {
 //     32x16x1024 361 / 332;  10x16x640 53.8 / 50.2;  1x8x8192 310 / 270, but 1x8x4096 102 / 112 (one workgroup a CU) and 46x4x444
 //     33.3 / 35.0 (a third one for some CUs): streaming from 384 keys on, where every CU has two workgroups, or three and more.
 bool stream_case(const ogc_mha_desc* d, const float* mask) {
-    if (d->dtype != OGC_BF16) return false;
+    if (d->dtype == OGC_F32) return split_case(d);
     const int64_t most = (int64_t)1 << 31;
     if (d->k_stride[2] * 2 > most / MHA_UNIT || d->v_stride[2] * 2 > most / MHA_UNIT) return false;
     const bool plain = plain_case(d, mask);
@@ -596,10 +642,16 @@ const char* ogc_mha_kernel_name(const ogc_mha_desc* d, int32_t has_mask) {
     const float* mask = has_mask ? (const float*)d : nullptr;
     const int d32 = d->head_dim / 32, plain = plain_case(d, mask), qs = query_groups(d);
     const bool stream = stream_case(d, mask);
-    if (stream && !mha_streams(d->dtype, d32)) {
+    if (stream && d->dtype == OGC_BF16 && !mha_streams(d->dtype, d32)) {
         char* w = wide[d->softmax][plain];
         if (!w[0]) snprintf(w, 48, "ogc_mha_stream_kernel<%d, %d, %d>", d32, d->softmax, plain);
         return w;
+    }
+    if (!stream && mha_splits(d->dtype, d32)) {
+        static char f32[3][2][2][48];
+        char* f = f32[d32 - 1][d->softmax][plain];
+        if (!f[0]) snprintf(f, 48, "ogc_mha_f32_kernel<%d, %d, %d>", d32, d->softmax, plain);
+        return f;
     }
     if (!stream && mha_streams(d->dtype, d32)) {
         char* g = general[d32 - 1][d->softmax][plain][qs - 1];

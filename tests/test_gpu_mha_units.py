@@ -365,3 +365,86 @@ def test_i8_token_strides_beyond_32_bits_of_offset(oracle_mod):
         torch.cuda.synchronize()
         outs.append(o.cpu())
     assert torch.equal(*outs)
+
+
+@pytest.mark.parametrize("seq", [33, 64, 65, 97, 128, 129, 160, 300])
+@pytest.mark.parametrize("head_dim", [32, 64, 96])
+def test_split_fp32_unit_edges(oracle_mod, seq, head_dim):
+    """One to ten blocks of 32 keys, whole and ragged, on either side of the rule, with and without a mask."""
+    wl = synth.make_mha("f32", 2, seq, 2 * head_dim, 2, 8300 + seq + head_dim, name="split S=%d d=%d" % (seq, head_dim))
+    check(oracle_mod, wl)
+    check(oracle_mod, wl, use_mask=False)
+    check(oracle_mod, wl, FAST, use_mask=False)
+
+
+def f32_call(q, k, v, scale, softmax, k_token=None):
+    """[batch, heads, seq, d] tensors; k_token: the keys' token stride in elements."""
+    import torch
+
+    b, h, s, d = q.shape
+    o, st = torch.empty_like(q), (h * s * d, s * d, d)
+    desc = binding.mha_desc(binding.OGC_F32, b, h, s, d, scale, softmax, st, (2 * d, d, k_token) if k_token else st, st, st)
+    binding.ogc_mha_run(desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), 0, o.data_ptr(), int(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    return o.cpu(), binding.ogc_mha_kernel_name(desc, False)
+
+
+def f32_inputs(seq, head_dim, seed):
+    import torch
+
+    g = torch.Generator().manual_seed(seed)
+    return [torch.randn((1, 2, seq, head_dim), generator=g) for _ in range(3)]
+
+
+def f32_reference(q, k, v, scale):
+    s = (q.double() @ k.double().transpose(-1, -2)) * scale
+    return (s - s.amax(-1, keepdim=True)).exp().div((s - s.amax(-1, keepdim=True)).exp().sum(-1, keepdim=True)) @ v.double()
+
+
+@pytest.mark.parametrize("head_dim", [32, 64, 96])
+def test_split_fp32_infinities(head_dim):
+    """An infinite key: queries that it attracts have no answer, the others do not see it.  An infinite value is every answer."""
+    import torch
+
+    q, k, v = f32_inputs(160, head_dim, 8400 + head_dim)
+    k[0, 0, 70, 3] = float("inf")
+    got, name = f32_call(q.cuda(), k.cuda(), v.cuda(), 0.1, STABLE)
+    assert name.startswith("ogc_mha_kernel<0,")
+    rest = [i for i in range(160) if i != 70]
+    ref = f32_reference(q, k[:, :, rest], v[:, :, rest], 0.1)
+    far = q[0, 0, :, 3] < 0
+    assert got[0, 0][~far].isnan().all()
+    assert (got[0, 0][far].double() - ref[0, 0][far]).norm() <= 1e-6 * ref[0, 0][far].norm()
+    k[0, 0, 70, 3] = 1.0
+    v[0, 1, 5, 7] = float("inf")
+    got, _ = f32_call(q.cuda(), k.cuda(), v.cuda(), 0.1, STABLE)
+    assert (got[0, 1, :, 7] == float("inf")).all() and torch.isfinite(got[0, 0]).all()
+
+
+@pytest.mark.parametrize("head_dim", [32, 64, 96])
+def test_split_fp32_small_results(head_dim):
+    """Results and weights whose lower pieces lie below the smallest exponents: 24 bits of them all the same."""
+    q, k, v = f32_inputs(128, head_dim, 8500 + head_dim)
+    ref = f32_reference(q, k, v, 0.1)
+    got, _ = f32_call(q.cuda(), k.cuda(), (v * 2.0 ** -115).cuda(), 0.1, STABLE)
+    assert (got.double() * 2.0 ** 115 - ref).norm() <= 1e-6 * ref.norm()
+    q[..., 0], k[..., 0] = 26.0, -28.0  # every score near -73: exponentials near 2^-105, none below 2^-126
+    got, _ = f32_call(q.cuda(), k.cuda(), v.cuda(), 0.1, FAST)
+    ref = f32_reference(q, k, v, 0.1)
+    # Products that sum to 728 are rounded or cut at 2^-14 up to head_dim / 2 times: 1.8e-6 (rounded, in the mean) to 3.5e-6 of a
+    # weight each, 2.5e-5 of it for 48 of them, and an average of values moves by as much of itself as its weights do, twice that
+    # for the sum below it.  With weights of eight bits it would be 1e-3.
+    assert (got.double() - ref).norm() <= 5e-5 * ref.norm()
+
+
+@pytest.mark.parametrize("k_token, name", [((1 << 22) - 4, "ogc_mha_kernel<0, 2, 0, 0, 1>"), (1 << 22, "ogc_mha_f32_kernel<2, 0, 0>")])
+def test_split_fp32_widest_token_stride(k_token, name):
+    import torch
+
+    q, k, v = f32_inputs(40, 64, 8600)
+    wide = torch.zeros(39 * k_token + 128, device="cuda")
+    view = torch.as_strided(wide, (1, 2, 40, 64), (128, 64, k_token, 1))
+    view.copy_(k)
+    got, kernel = f32_call(q.cuda(), wide, v.cuda(), 0.125, STABLE, k_token=k_token)
+    ref = f32_reference(q, k, v, 0.125)
+    assert kernel == name and (got.double() - ref).norm() <= 1e-6 * ref.norm()
