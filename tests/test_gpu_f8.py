@@ -302,3 +302,13 @@ def test_description_checks():
             binding.ogc_mlp_plan(binding.OGC_F8, 64, [bad], 64, 64, 0, binding.OGC_MODE_AUTO)
     with pytest.raises(binding.OgcError):    # the residual add belongs to the float dtypes
         binding.ogc_mlp_plan(binding.OGC_F8, 64, [lay()], 64, 64, 1, binding.OGC_MODE_AUTO)
+
+
+@pytest.mark.parametrize("k", [16, 64, 128, 192, 320, 576, 1024])
+@pytest.mark.parametrize("n", [33, 300, 1024])
+def test_pairs_of_k_steps(oracle_mod, k, n):
+    """Reduction axes of one pair of 32-byte steps up, whole groups of four and eight steps and what remains of them, one to four
+    channel blocks a wave, in the fused kernel, the one for two workgroups on a CU and the register-staged tile."""
+    for m, mode in ((70, "fused"), (70, "per_layer")) + (((8200, "fused"),) if n == 33 else ()):
+        wl = synth.make_mlp("f8", m, [k, n], [RELU], seed=synth.BASE_SEED + 900 + k + n, name="pairs K=%d N=%d M=%d" % (k, n, m))
+        check_one_layer(oracle_mod, wl, mode)
