@@ -64,19 +64,15 @@ template <int DT> OGC_DEV void mma32(typename AccT<DT>::type& c, const v4i& w, c
     }
 }
 
-// Two k-steps at once (any two, as long as both operands agree).  E4M3: one instruction over their 64 bytes at twice the rate of
-// the four that mma32 would take, with the same sums.  Four 1024-wide layers at batch 8192, fused, between fp32 rows: 82 -> 74 us
+// Two k-steps of E4M3 at once (any two, as long as both operands agree): one instruction over their 64 bytes at twice the rate
+// of the four that mma32 would take, with the same sums.  Four 1024-wide layers at batch 8192, fused, between fp32 rows: 82 -> 74 us
 // (the weights' way from the L2 bounds it now); 479-1024-1024-512-256-1 at 4096 38.9 -> 37.2.  Not where eight waves split K: there
-// a wave waits for its few instructions one by one (that chain at batch 256, 31.0 against 31.3).
+// a wave waits for its few instructions one by one (that chain at batch 256, 31.0 against 31.3).  (The other types keep one
+// instruction a step.)
 typedef int v8i __attribute__((ext_vector_type(8)));
-template <int DT> OGC_DEV void mma32x2(typename AccT<DT>::type& c, const v4i& w0, const v4i& w1, const v4i& x0, const v4i& x1) {
-    if constexpr (DT == OGC_F8) {
-        c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(__builtin_shufflevector(w0, w1, 0, 1, 2, 3, 4, 5, 6, 7),
-                                                            __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7), c, 0, 0, 0, 0, 0, 0);
-    } else {
-        mma32<DT>(c, w0, x0);
-        mma32<DT>(c, w1, x1);
-    }
+OGC_DEV void mma64(v16f& c, const v4i& w0, const v4i& w1, const v4i& x0, const v4i& x1) {
+    c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(__builtin_shufflevector(w0, w1, 0, 1, 2, 3, 4, 5, 6, 7),
+                                                        __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7), c, 0, 0, 0, 0, 0, 0);
 }
 
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
@@ -672,7 +668,7 @@ ogc_layer_kernel(const OgcLayerArgs a, int tiles_n, int tiles_total, int tiles_p
 #pragma unroll
             for (int i = 0; i < C::TN; ++i)
 #pragma unroll
-                for (int j = 0; j < C::TM; ++j) mma32x2<DT>(acc[i][j], wf[0][i], wf[1][i], xf[0][j], xf[1][j]);
+                for (int j = 0; j < C::TM; ++j) mma64(acc[i][j], wf[0][i], wf[1][i], xf[0][j], xf[1][j]);
         } else
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -739,7 +735,6 @@ OGC_DEV void fused_blocks(const OgcLayerArgs& a, const uint8_t* xin, YT xout, in
     const size_t wstep = (size_t)stride * a.KC * 512;  // this wave's next block is `stride` further
     const uint8_t* xp = xin + lane * 16;
     const int groups = G ? KP2 / (G ? G : 1) : 0;
-    constexpr int ST = DT == OGC_F8 ? 2 : 1;  // k-steps of a matrix instruction
     if constexpr (G > 0) if (groups > 0) {
         v4i w[G][CNT];
 #pragma unroll
@@ -750,27 +745,42 @@ OGC_DEV void fused_blocks(const OgcLayerArgs& a, const uint8_t* xin, YT xout, in
             v4i xf[G];
 #pragma unroll
             for (int u = 0; u < G; ++u) xf[u] = *(const v4i*)(xp + (size_t)((g - 1) * G + u) * 1024);
+            if constexpr (DT == OGC_F8) {
 #pragma unroll
-            for (int u = 0; u < G; u += ST) {
+                for (int u = 0; u < G; u += 2) {
 #pragma unroll
-                for (int i = 0; i < CNT; ++i) {
-                    if constexpr (ST == 2) mma32x2<DT>(acc[i], w[u][i], w[u + 1][i], xf[u], xf[u + 1]);
-                    else mma32<DT>(acc[i], w[u][i], xf[u]);
+                    for (int i = 0; i < CNT; ++i) mma64(acc[i], w[u][i], w[u + 1][i], xf[u], xf[u + 1]);
+#pragma unroll
+                    for (int t = u; t < u + 2; ++t)
+#pragma unroll
+                        for (int i = 0; i < CNT; ++i) w[t][i] = *(const v4i*)(wp + i * wstep + (size_t)(g * G + t) * 1024);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+                continue;
+            }
 #pragma unroll
-                for (int t = u; t < u + ST; ++t)
+            for (int u = 0; u < G; ++u) {
 #pragma unroll
-                    for (int i = 0; i < CNT; ++i) w[t][i] = *(const v4i*)(wp + i * wstep + (size_t)(g * G + t) * 1024);
+                for (int i = 0; i < CNT; ++i) mma32<DT>(acc[i], w[u][i], xf[u]);
+#pragma unroll
+                for (int i = 0; i < CNT; ++i) w[u][i] = *(const v4i*)(wp + i * wstep + (size_t)(g * G + u) * 1024);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
         v4i xf[G];
 #pragma unroll
         for (int u = 0; u < G; ++u) xf[u] = *(const v4i*)(xp + (size_t)((groups - 1) * G + u) * 1024);
+        if constexpr (DT == OGC_F8) {
 #pragma unroll
-        for (int u = 0; u < G; u += 2)
+            for (int u = 0; u < G; u += 2)
 #pragma unroll
-            for (int i = 0; i < CNT; ++i) mma32x2<DT>(acc[i], w[u][i], w[u + 1][i], xf[u], xf[u + 1]);
+                for (int i = 0; i < CNT; ++i) mma64(acc[i], w[u][i], w[u + 1][i], xf[u], xf[u + 1]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < G; ++u)
+#pragma unroll
+                for (int i = 0; i < CNT; ++i) mma32<DT>(acc[i], w[u][i], xf[u]);
+        }
     }
     auto some = [&](auto steps, int kp) {  // a few k-steps, all their loads in flight at once
         constexpr int S = decltype(steps)::value;
@@ -781,10 +791,17 @@ OGC_DEV void fused_blocks(const OgcLayerArgs& a, const uint8_t* xin, YT xout, in
             for (int i = 0; i < CNT; ++i) wf[u][i] = *(const v4i*)(wp + i * wstep + (size_t)(kp + u) * 1024);
 #pragma unroll
         for (int u = 0; u < S; ++u) xf[u] = *(const v4i*)(xp + (size_t)(kp + u) * 1024);
+        if constexpr (DT == OGC_F8) {
 #pragma unroll
-        for (int u = 0; u < S; u += 2)
+            for (int u = 0; u < S; u += 2)
 #pragma unroll
-            for (int i = 0; i < CNT; ++i) mma32x2<DT>(acc[i], wf[u][i], wf[u + 1][i], xf[u], xf[u + 1]);
+                for (int i = 0; i < CNT; ++i) mma64(acc[i], wf[u][i], wf[u + 1][i], xf[u], xf[u + 1]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < S; ++u)
+#pragma unroll
+                for (int i = 0; i < CNT; ++i) mma32<DT>(acc[i], wf[u][i], xf[u]);
+        }
     };
     int kp = groups * G;  // the rest (G = 0: all): an even number of steps
     constexpr int PART = G == 0 && (CNT > 2 || DT == OGC_I8) ? 2 : 4;
