@@ -20,9 +20,8 @@ import numpy as np
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSV = os.path.join(HERE, "data", "chain_times.csv")
 INC = os.path.join(os.path.dirname(HERE), "csrc", "ogc_cost_chains.inc")
-ESZ = {"f32": 4, "bf16": 2, "i8": 1, "f8": 1}
-DTYPES = ("f32", "bf16", "i8")     # the order of ogc_dtype: the tables are indexed by it; E4M3 has one of its own for the
-# fused kernel (its matrix instruction) and borrows int8's for the others
+ESZ = {"f32": 4, "bf16": 2, "i8": 1}
+DTYPES = ("f32", "bf16", "i8")     # the order of ogc_dtype: the tables are indexed by it
 
 
 def read_rows(path: str = CSV):
@@ -36,7 +35,7 @@ def read_rows(path: str = CSV):
 
 def layers(r):
     """Per layer: (padded input row bytes, 32-channel blocks written, is last), as the plan sizes them."""
-    e, g = ESZ[r["dtype"]], (64 if r["dtype"] in ("i8", "f8") else 32)
+    e, g = ESZ[r["dtype"]], (64 if r["dtype"] == "i8" else 32)
     dims, out = r["dims"], []
     for i, (k, n) in enumerate(zip(dims[:-1], dims[1:])):
         kp = -(-k // g) * g
@@ -114,7 +113,7 @@ MODELS = {
 
 def usable(r):
     """The fused kernel's model is fitted where the plan offers it: float chains whose weights fit the L2 share."""
-    if r["kind"] != "fused" or r["dtype"] in ("i8", "f8"):
+    if r["kind"] != "fused" or r["dtype"] == "i8":
         return True
     return sum(kb * nb * 32 for kb, nb, _, _ in layers(r)) <= 2.6e6
 
@@ -138,19 +137,16 @@ def fit(rows, kind: str, dtype: str):
 def main() -> None:
     rows = read_rows()
     text = ("// Written by paper_2301_01333_amd/calibration/fit_chains.py from calibration/data/chain_times.csv; do not edit.\n"
-            "// One row per dtype in the order of ogc_dtype (fp32, bf16, int8); E4M3 apart;\n"
-            "// fields as in the structs of ogc_api.cpp.\n")
+            "// One row per dtype in the order of ogc_dtype (fp32, bf16, int8); fields as in the structs of ogc_api.cpp.\n")
     for kind in ("fused", "coop", "cluster", "ksplit"):
         _, _, _, _, struct, name = MODELS[kind]
-        body = {}
-        for dtype in DTYPES + (("f8",) if kind == "fused" else ()):
+        body = []
+        for dtype in DTYPES:
             p, rms, worst, n = fit(rows, kind, dtype)
             print("%-7s %-4s %4d chains, rms log error %.3f, worst %.3f" % (kind, dtype, n, rms, worst), np.round(p, 4).tolist(), flush=True)
             text += "// %s %s: %d chains, rms log error %.3f, worst %.3f\n" % (kind, dtype, n, rms, worst)
-            body[dtype] = "{" + ", ".join("%.4ff" % v for v in p) + "}"
-        text += "const %s %s[3] = {%s};\n" % (struct, name, ",\n    ".join(body[d] for d in DTYPES))
-        if "f8" in body:
-            text += "const %s %sF8 = %s;\n" % (struct, name, body["f8"])
+            body.append("{" + ", ".join("%.4ff" % v for v in p) + "}")
+        text += "const %s %s[3] = {%s};\n" % (struct, name, ",\n    ".join(body))
     if "--check" in sys.argv:
         print(text)
         return

@@ -59,7 +59,7 @@ def main(out_path: str = DEFAULT_OUT) -> None:
     with open(out_path, "w", newline="") as f:
         w = csv.writer(f)
         w.writerow(["dtype", "dims", "m", "kind", "split", "whole", "us"])
-        for dtype in ("f32", "bf16", "i8", "f8"):
+        for dtype in ("f32", "bf16", "i8"):
             for dims in CHAINS:
                 for m in BATCHES:
                     if m * max(dims) * 4 > (1 << 27):
@@ -68,8 +68,8 @@ def main(out_path: str = DEFAULT_OUT) -> None:
                     acts = [synth.ACT_RELU] * nl
                     kw = {}
                     if dims[-1] == 1:
-                        acts[-1] = synth.ACT_SIGMOID if dtype in ("i8", "f8") else synth.ACT_NONE
-                        kw = dict(last_f32=True) if dtype in ("i8", "f8") else {}
+                        acts[-1] = synth.ACT_SIGMOID if dtype == "i8" else synth.ACT_NONE
+                        kw = dict(last_f32=True) if dtype == "i8" else {}
                     wl = synth.make_mlp(dtype, m, dims, acts, seed=7, has_bias=True, **kw)
                     cases = [("fused", 0, binding.OGC_MODE_FUSED, None, "ogc_fused_chain_"),
                              ("coop", 0, binding.OGC_MODE_COOP, {"cluster_split": 0}, "ogc_coop_chain_kernel")]

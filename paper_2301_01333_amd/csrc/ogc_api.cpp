@@ -184,12 +184,12 @@ void choose_tile_and_split(int dtype, int m, int n, int kt, bool dma_ok, int for
     *us_out = timed ? estimate_layer_us(dtype, m, n, kt, tile, ks) : -1.0;
 }
 
-// ---- Whole-chain models of the other two modes, fitted to timed chains (12 shapes, batch 32..16384; 2-10 %
-// rms; the fused kernel's with the loops it has now).  A chain run layer by layer costs the sum of its layers' estimates less the event overhead
+// ---- Whole-chain models of the other two modes, fitted to 357 timed chains (12 shapes, batch 32..16384, three
+// dtypes; 2-10 % rms).  A chain run layer by layer costs the sum of its layers' estimates less the event overhead
 // each of those carries from the way it was timed.
 constexpr double kProfiledLaunchExtraUs = 2.0;
-// The E4M3 path borrows int8's constants but for the fused kernel: it moves the same bytes through the same kernels, and what these
-// models decide between is bound by weight streaming and launch latency.
+// The E4M3 path has no constants of its own: it moves the same bytes as int8 through the same kernels, and the chains
+// these models decide between are bound by weight streaming and launch latency, so it borrows the int8 constants.
 inline int model_dtype(int dtype) { return dtype == OGC_F8 ? OGC_I8 : dtype; }
 struct FusedCost { float f0, per_mb, per_layer, fill, per_block; };
 struct CoopCost { float c0, barrier, block, step, fill; };
@@ -201,7 +201,7 @@ struct KsplitCost { float c0, block, step, barrier, copy_mb, fill, all_mb; };
 
 // One workgroup per 32 rows streams every weight: flat in the batch up to 8192 rows (256 CUs), then in rounds.
 double estimate_fused_us(const ogc_mlp_plan_s* p) {
-    const FusedCost& c = p->desc.dtype == OGC_F8 ? kFusedF8 : kFused[p->desc.dtype];
+    const FusedCost& c = kFused[model_dtype(p->desc.dtype)];
     const double m = p->desc.m, rounds = std::max(1.0, m / 8192.0);
     double sum = 0.0;
     for (const LayerPlan& lp : p->layers) {
@@ -550,7 +550,9 @@ ogc_status ogc_mlp_plan_with_overrides(const ogc_mlp_desc* desc, const ogc_plan_
     }
     if (mode == OGC_MODE_AUTO) {
         // The mode whose estimate is lowest (section "cost model" of the sources above: each mode has its own fitted
-        // model).  The fused kernel is not a candidate for bf16 / fp32 chains whose weights exceed about 2.5 MB.
+        // model).  The fused kernel is a candidate only where its model was fitted: bf16 / fp32 chains whose weights exceed
+        // about 2.5 MB ran several times slower per byte in the kernel of that sweep (the present one keeps its loads in
+        // flight and does not, but has not been swept).
         // A single-launch mode wins ties within 7 %: its model is the tighter one, and it keeps the intermediates
         // on chip.
         int single = -1;
