@@ -25,7 +25,7 @@
  * NULL; values below -2.3e38 (bf16: or below -3e38 * scale), which no score holds, count as that one value.  o has q's dtype.  The library allocates nothing and keeps no state between calls.
  *
  * Arithmetic: OGC_F32 multiplies fp32 operands with fp32 accumulation throughout (up to 96 channels by exact splits of the
- * operands into three bf16 values, whose products agree to 2^-24; operands below 2^-110 keep fewer bits there).  OGC_BF16 multiplies bf16
+ * operands into three bf16 values, whose products agree to 2^-24 at most and in the mean; operands below 2^-110 keep fewer bits there).  OGC_BF16 multiplies bf16
  * operands with fp32 accumulation; scores, exponentials and row sums are fp32; the softmax weights are rounded
  * to bf16 (nearest even) for the second matmul and o is rounded to bf16 once at the end.  OGC_I8 (Table I lists the
  * MHA rows as Int8 too) has an entry point of its own, ogc_mha_run_i8, because it needs quantization scales.

@@ -3,34 +3,36 @@
 //
 // The fp32 matrix instruction runs at a sixteenth of the bf16 one's rate, and the staged body was bound by it.  An fp32 value is
 // the sum of three bf16 values without any error (8 + 8 + 8 bits), so a product of two is nine bf16 products, of which
-// the three smallest (below 2^-24 of it) are left out: six instructions at sixteen times the rate.  The five small products of
+// the three smallest are left out: six instructions at sixteen times the rate.  The pieces are rounded to nearest, so that what is
+// left out is 2^-24 of a product at most and of either sign (pieces that are cut: 2^-21, always of the product's sign, which
+// does not average out: 8.9e-7 against 3.4e-7 for operands of +-1.0078124; 2 % of the time).  The five small products of
 // a sum are added up first and the large ones on top of them, a block of 32 keys at a time: the bf16 instruction truncates what
 // it adds to a larger sum, and in one running sum that added up (9.6e-6 at 4096 products of one sign against 1.0e-6 for the
-// fp32 instruction; sums kept apart 3.7e-7).  Error against 64 bits, relative 2-norm, fp32 instruction / this: 512 x 64 4.7e-7 /
-// 2.4e-7, 1024 x 96 6.0e-7 / 2.7e-7, 48 x 32 2.2e-7 / 1.4e-7.
+// fp32 instruction; sums kept apart 3.7e-7).  Error against 64 bits, relative 2-norm, fp32 instruction / this: 512 x 64 5.2e-7 /
+// 2.2e-7, 1024 x 96 7.2e-7 / 3.0e-7, 160 x 32 3.2e-7 / 1.4e-7; operands of one magnitude (+-1.0078124, +-1.1) 512 x 64 5.9e-7 / 3.4e-7
+// and 8.1e-7 / 2.8e-7, with the largest pieces there are (+-(1 + 2^-8 - 2^-17)) 5.6e-7 / 3.9e-7; log-normal ones 9.1e-7 / 3.2e-7.
 //
-// What bounds it: power.  32 x 16 heads x 512 x 64 (206 TFLOP of bf16 instructions): 277 -> 197 us, but 151 us where all
+// What bounds it: power.  32 x 16 heads x 512 x 64 (206 GFLOP of bf16 instructions): 277 -> 198 us, but 151 us where all
 // inputs are zero; fewer vector instructions (377 -> 300 a block and wavefront) changed nothing there and gave 10 % where half
-// of the chip works.  2 x 8 x 1024 x 64: 80 -> 47 us; 8 x 16 x 512 x 96: 110 -> 78; more at split_case.  Tried: eight wavefronts that
+// of the chip works.  2 x 8 x 1024 x 64: 80 -> 48 us; 8 x 16 x 512 x 96: 110 -> 78; more at split_case.  Tried: eight wavefronts that
 // share the pieces of keys and values (50.2 against 51.1 us at 8 x 16 x 512 x 64, 202 against 197 at 32); 96 and 128 channels with
 // 512 registers, one wavefront a SIMD (arrays in scratch memory, ten times as long).
 #ifndef OGC_MHA_F32_H
 #define OGC_MHA_F32_H
 
-// Three bf16 pieces of fp32 values that add up to them exactly: the upper 16 bits, the upper 16 bits of what is left (a
-// subtraction without rounding), and the rest, which has 8 bits.  Elements 2 t, 2 t + 1 share a register.
+// Three bf16 pieces of fp32 values that add up to them exactly: the nearest bf16 value, the nearest one to what is left (a
+// subtraction without rounding), and the rest, which has 7 bits.  Elements 2 t, 2 t + 1 share a register.
 struct Pieces8 {
     v4i p[3];
 };
-MHA_DEV uint32_t upper_halves(float x, float y) {
+MHA_DEV uint32_t upper_halves(float x, float y) {  // of values that have no others
     return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, y), __builtin_bit_cast(uint32_t, x), 0x07060302u);
 }
-MHA_DEV float below_upper(float x) { return x - __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & 0xffff0000u); }
 // one piece of a pair, and what is left of it
 MHA_DEV uint32_t next_piece(float& x, float& y) {
-    const uint32_t p = upper_halves(x, y);
-    x = below_upper(x);
-    y = below_upper(y);
+    const uint32_t p = pack_bf16(x, y);
+    x -= __builtin_bit_cast(float, p << 16);
+    y -= __builtin_bit_cast(float, p & 0xffff0000u);
     return p;
 }
 MHA_DEV Pieces8 split8(const v4f& a, const v4f& b) {

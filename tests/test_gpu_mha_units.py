@@ -448,3 +448,21 @@ def test_split_fp32_widest_token_stride(k_token, name):
     got, kernel = f32_call(q.cuda(), wide, v.cuda(), 0.125, STABLE, k_token=k_token)
     ref = f32_reference(q, k, v, 0.125)
     assert kernel == name and (got.double() - ref).norm() <= 1e-6 * ref.norm()
+
+
+@pytest.mark.parametrize("value", [1.0078124, 1.1, 1.0 + 2.0 ** -8 - 2.0 ** -17])
+@pytest.mark.parametrize("head_dim", [32, 64, 96])
+def test_split_fp32_errors_of_one_sign(head_dim, value):
+    """Operands of one magnitude: what the left-out products lose is the same in every product, and does not average out.  No
+    further from 64 bits than the fp32 instruction, which a token stride of 2^24 bytes takes the same call to.  The last value's
+    second and third pieces are as large as pieces can be (2^-8 and 2^-17 of it)."""
+    import torch
+
+    q, k, v = (torch.sign(t) * value for t in f32_inputs(160, head_dim, 8700 + head_dim))
+    ref, scale = f32_reference(q, k, v, head_dim ** -0.5), head_dim ** -0.5
+    got, split = f32_call(q.cuda(), k.cuda(), v.cuda(), scale, STABLE)
+    wide = torch.zeros(159 * (1 << 22) + 2 * head_dim, device="cuda")
+    torch.as_strided(wide, (1, 2, 160, head_dim), (2 * head_dim, head_dim, 1 << 22, 1)).copy_(k)
+    staged, name = f32_call(q.cuda(), wide, v.cuda(), scale, STABLE, k_token=1 << 22)
+    assert split.startswith("ogc_mha_kernel<0,") and name.startswith("ogc_mha_f32_kernel<")
+    assert float((got.double() - ref).norm()) <= float((staged.double() - ref).norm())
