@@ -25,7 +25,8 @@
  * NULL; values below -2.3e38 (bf16: or below -3e38 * scale), which no score holds, count as that one value.  o has q's dtype.  The library allocates nothing and keeps no state between calls.
  *
  * Arithmetic: OGC_F32 multiplies fp32 operands with fp32 accumulation throughout (up to 96 channels by exact splits of the
- * operands into three bf16 values, whose products agree to 2^-24 at most and in the mean; operands below 2^-110 keep fewer bits there).  OGC_BF16 multiplies bf16
+ * operands into three bf16 values, whose products are left 2^-24 of them at most; tiles with operands or results to which that
+ * does not apply are computed by the fp32 instruction).  OGC_BF16 multiplies bf16
  * operands with fp32 accumulation; scores, exponentials and row sums are fp32; the softmax weights are rounded
  * to bf16 (nearest even) for the second matmul and o is rounded to bf16 once at the end.  OGC_I8 (Table I lists the
  * MHA rows as Int8 too) has an entry point of its own, ogc_mha_run_i8, because it needs quantization scales.
@@ -79,8 +80,8 @@ ogc_status ogc_mha_run(const ogc_mha_desc* desc, const void* q, const void* k, c
  * positive takes a variant that spends no per-key addend; bf16 with head_dim <= 64 and seq >= 256 takes one in
  * which a wavefront owns 64 queries instead of 32 (the last template argument; desc->query_groups forces either).
  * bf16 has two bodies, one that streams keys and values into LDS and one that stages them in registers: ogc_mha_kernel
- * streams up to 96 channels and stages 128 (fp32: splits up to 96; ogc_mha_f32_kernel<D32, FAST, PLAIN> stages short sequences
- * and token strides from 2^24 bytes on), ogc_mha_general_kernel stages up to 96 (short sequences, scales that are not
+ * streams up to 96 channels and stages 128 (fp32: splits up to 96; ogc_mha_f32_kernel<D32, FAST, PLAIN> stages short sequences,
+ * token strides from 2^24 bytes on and scales beyond 2^60), ogc_mha_general_kernel stages up to 96 (short sequences, scales that are not
  * positive or extreme, token strides beyond 2^26 bytes) and ogc_mha_stream_kernel streams 128 (large launches). */
 const char* ogc_mha_kernel_name(const ogc_mha_desc* desc, int32_t has_mask);
 

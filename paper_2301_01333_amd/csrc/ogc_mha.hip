@@ -529,14 +529,16 @@ int query_groups(const ogc_mha_desc* d) {
 }
 
 // The split body or the staged one (fp32).  The split body multiplies a row's number by 24 bits of stride, and takes up to 96
-// channels (128: its registers do not hold a query's pieces).  Its first block costs more.  Staged / split, us, batch x heads x seq,
+// channels (128: its registers do not hold a query's pieces).  What it leaves out of small operands may count under extreme scalars
+// (see its end).  Its first block costs more.  Staged / split, us, batch x heads x seq,
 // with a mask:
-//   32 channels: 64x12x33 10.5 / 11.0;  64x12x64 11.9 / 12.8;  64x12x96 16.4 / 16.3;  32x16x128 15.5 / 13.7;  8x16x512 43.7 / 31.6.
-//   64: 1x8x16 7.1 / 7.2;  1x8x33 7.6 / 7.4;  64x12x33 18.4 / 16.5;  64x12x96 28.2 / 25.5;  4x12x197 21.0 / 15.5;  32x16x512 277 / 197.
-//   96: 1x8x33 10.0 / 10.1;  64x12x64 30.1 / 28.9;  1x8x64 10.4 / 10.6;  64x12x96 43.7 / 44.5;  32x16x128 38.8 / 33.3;  8x16x512 110 / 78.
+//   32 channels: 64x12x33 10.5 / 11.0;  64x12x64 11.9 / 12.8;  64x12x96 16.4 / 16.3;  32x16x128 15.6 / 14.1;  8x16x512 43.8 / 32.0.
+//   64: 1x8x16 7.1 / 7.2;  1x8x33 7.6 / 7.4;  64x12x33 18.4 / 16.5;  64x12x96 28.2 / 25.5;  4x12x197 21.0 / 15.3;  32x16x512 277 / 195.
+//   96: 1x8x33 10.0 / 10.1;  64x12x64 30.1 / 28.9;  1x8x64 10.4 / 10.6;  64x12x96 43.7 / 44.5;  32x16x128 38.7 / 33.4;  8x16x512 110 / 77.
 bool split_case(const ogc_mha_desc* d) {
     const int64_t most = (int64_t)1 << 24;
     if (d->head_dim > 96 || d->k_stride[2] * 4 >= most || d->v_stride[2] * 4 >= most) return false;
+    if (!(fabsf(d->scale) >= 0x1p-60f && fabsf(d->scale) <= 0x1p60f)) return false;
     return d->seq > (d->head_dim == 64 ? 32 : 96);
 }
 

@@ -5,16 +5,16 @@
 // the sum of three bf16 values without any error (8 + 8 + 8 bits), so a product of two is nine bf16 products, of which
 // the three smallest are left out: six instructions at sixteen times the rate.  The pieces are rounded to nearest, so that what is
 // left out is 2^-24 of a product at most and of either sign (pieces that are cut: 2^-21, always of the product's sign, which
-// does not average out: 8.9e-7 against 3.4e-7 for operands of +-1.0078124; 2 % of the time).  The five small products of
+// does not average out: 8.9e-7 against 3.4e-7 for operands of +-1.0078124).  The five small products of
 // a sum are added up first and the large ones on top of them, a block of 32 keys at a time: the bf16 instruction truncates what
 // it adds to a larger sum, and in one running sum that added up (9.6e-6 at 4096 products of one sign against 1.0e-6 for the
 // fp32 instruction; sums kept apart 3.7e-7).  Error against 64 bits, relative 2-norm, fp32 instruction / this: 512 x 64 5.2e-7 /
 // 2.2e-7, 1024 x 96 7.2e-7 / 3.0e-7, 160 x 32 3.2e-7 / 1.4e-7; operands of one magnitude (+-1.0078124, +-1.1) 512 x 64 5.9e-7 / 3.4e-7
 // and 8.1e-7 / 2.8e-7, with the largest pieces there are (+-(1 + 2^-8 - 2^-17)) 5.6e-7 / 3.9e-7; log-normal ones 9.1e-7 / 3.2e-7.
 //
-// What bounds it: power.  32 x 16 heads x 512 x 64 (206 GFLOP of bf16 instructions): 277 -> 198 us, but 151 us where all
+// What bounds it: power.  32 x 16 heads x 512 x 64 (206 GFLOP of bf16 instructions): 277 -> 195 us, but 151 us where all
 // inputs are zero; fewer vector instructions (377 -> 300 a block and wavefront) changed nothing there and gave 10 % where half
-// of the chip works.  2 x 8 x 1024 x 64: 80 -> 48 us; 8 x 16 x 512 x 96: 110 -> 78; more at split_case.  Tried: eight wavefronts that
+// of the chip works.  2 x 8 x 1024 x 64: 80 -> 48 us; 8 x 16 x 512 x 96: 110 -> 77; more at split_case.  Tried: eight wavefronts that
 // share the pieces of keys and values (50.2 against 51.1 us at 8 x 16 x 512 x 64, 202 against 197 at 32); 96 and 128 channels with
 // 512 registers, one wavefront a SIMD (arrays in scratch memory, ten times as long).
 #ifndef OGC_MHA_F32_H
@@ -31,10 +31,19 @@ MHA_DEV uint32_t upper_halves(float x, float y) {  // of values that have no oth
 // one piece of a pair, and what is left of it
 MHA_DEV uint32_t next_piece(float& x, float& y) {
     const uint32_t p = pack_bf16(x, y);
-    x -= __builtin_bit_cast(float, p << 16);
+    x -= __builtin_bit_cast(float, __builtin_amdgcn_alignbyte(p, 0u, 2u));  // (p << 16, for which the compiler converts x once more)
     y -= __builtin_bit_cast(float, p & 0xffff0000u);
     return p;
 }
+// The largest / the smallest of m and both magnitudes.  (As a builtin the former takes the masked body for 64 channels to scratch
+// memory.  The compiler does not know what the assembly's operands must keep away from: they are loaded, never computed.)
+MHA_DEV float widest(float m, float x, float y) {
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(x), "v"(y));
+    return m;
+}
+MHA_DEV float least(float m, float x, float y) { return __builtin_elementwise_minimum(__builtin_elementwise_minimum(fabsf(x), fabsf(y)), m); }
+// orders magnitudes, zero above all others
+MHA_DEV uint32_t zero_last(float x) { return (__builtin_bit_cast(uint32_t, x) << 1) - 1u; }
 MHA_DEV Pieces8 split8(const v4f& a, const v4f& b) {
     Pieces8 r;
 #pragma unroll
@@ -74,10 +83,21 @@ template <int D32, int FAST, int PLAIN> MHA_DEV void mha_split_body(const MhaArg
     // ---- this lane's query row as the second operand of the first product, in pieces
     const int query = (qt * 4 + wave) * 32 + col, qrow = query < S ? query : S - 1;
     Pieces8 qp[QN];
+    float wide = 0.0f;  // the largest magnitude among queries and values (see the end)
     {
+        uint32_t low = ~0u;
         const uint8_t* p = a.q + (b * a.sq[0] + hd * a.sq[1] + qrow * a.sq[2]) * 4 + h * 32;
 #pragma unroll
-        for (int i = 0; i < QN; ++i) qp[i] = split8(*(const v4f*)(p + i * 64), *(const v4f*)(p + i * 64 + 16));
+        for (int i = 0; i < QN; ++i) {
+            const v4f x = *(const v4f*)(p + i * 64), y = *(const v4f*)(p + i * 64 + 16);
+            qp[i] = split8(x, y);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                wide = widest(wide, x[e], y[e]);
+                low = min(low, min(zero_last(x[e]), zero_last(y[e])));
+            }
+        }
+        if (low < zero_last(0x1p-110f)) wide = INFINITY;
     }
 
     // ---- a block of keys and one of values (and mask) on their way: D32 units of 8 elements a thread, keys first.  No branch:
@@ -116,6 +136,7 @@ template <int D32, int FAST, int PLAIN> MHA_DEV void mha_split_body(const MhaArg
     auto fill_step = [&](int i, int t, int step, int kblk, int vblk) {
         if (step == 0) {
             left[0] = raw[i][t >> 1][2 * t & 3], left[1] = raw[i][t >> 1][(2 * t & 3) + 1];
+            if (256 * (i + 1) > UNITS) wide = widest(wide, left[0], left[1]);  // (not the units of keys alone)
             up[0][t] = next_piece(left[0], left[1]);
             return;
         }
@@ -399,23 +420,46 @@ template <int D32, int FAST, int PLAIN> MHA_DEV void mha_split_body(const MhaArg
     }
     if constexpr (LATE) add_late();
 
-    // ---- normalise; the pieces have no answer to infinities (infinity less its upper bits is no number), and results near
-    // the lowest exponents had pieces below them: such tiles are computed once more by the fp32 instruction
+    // ---- normalise.  Some tiles are computed once more by the fp32 instruction.  Pieces are multiples of 2^-133 (the instruction
+    // takes those below the smallest exponent as they are): what is below 2^-110 is off by 2^-134 at most.
+    //   * Infinities: the pieces have no answer to them (infinity less itself is no number; nor is then the sum of the weights).
+    //   * Queries beyond 2^20, or below 2^-110: smaller keys move a score by 96 x 2^-134 x 2^20 and scalars of up to 2^60, 2^-47.
+    //   * Values beyond 2^20, and sums below 2^-74: smaller weights, up to 2^16 of them, move a sum by 2^-98, 2^-24 of it.
+    //   * Results below 2^-100: smaller values move them by 2^-134, 2^-34 of them.
+    //   * Sums of zero where there are values below the smallest exponent, whose pieces may be zero.
+    // One look for the largest and the smallest of all, a closer one at what it finds.
     const float total = run_sum + other_half(run_sum), inv = 1.0f / total;
-    bool again = !(total >= 0x1p-90f && total <= MHA_F32_MAX);
+    float lowest = 1.0f;
 #pragma unroll
     for (int d = 0; d < D32; ++d)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            oacc[d][r] *= inv;
-            const float m = fabsf(oacc[d][r]);
-            again = again || !(m <= MHA_F32_MAX) || (m < 0x1p-100f && m > 0.0f);
+        for (int r = 0; r < 16; r += 2) lowest = least(lowest, oacc[d][r], oacc[d][r + 1]);
+    // (sums from 2^-74 on over a total of up to 2^26 are results from 2^-100 on)
+    if (__builtin_expect(__syncthreads_or(!(total > 0.0f && total <= 0x1p26f && wide <= 0x1p20f && lowest >= 0x1p-74f)), 0)) {
+        bool again = !(total > 0.0f && total <= 0x1p120f && wide <= 0x1p20f), nothing = false;
+#pragma unroll
+        for (int d = 0; d < D32; ++d)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                again = again || zero_last(oacc[d][r]) < zero_last(0x1p-74f) || zero_last(oacc[d][r] * inv) < zero_last(0x1p-100f);
+                nothing = nothing || oacc[d][r] == 0.0f;
+            }
+        if (__syncthreads_or(nothing))
+            for (int u = tid; !again && u < S * (D / 4); u += 256) {
+                const v4f x = *(const v4f*)(vbase + (u / (D / 4)) * vss + u % (D / 4) * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) again = again || zero_last(x[e]) < zero_last(0x1p-126f);
+            }
+        if (__syncthreads_or(again)) {
+            typedef MhaStaged<OGC_F32, D32> T;
+            mha_staged_body<OGC_F32, D32, FAST, PLAIN, 1, 1>(a, smem, smem + T::K_BYTES, (float*)(smem + T::K_BYTES + T::V_BYTES));
+            return;
         }
-    if (__builtin_expect(__syncthreads_or(again), 0)) {
-        typedef MhaStaged<OGC_F32, D32> T;
-        mha_staged_body<OGC_F32, D32, FAST, PLAIN, 1, 1>(a, smem, smem + T::K_BYTES, (float*)(smem + T::K_BYTES + T::V_BYTES));
-        return;
     }
+#pragma unroll
+    for (int d = 0; d < D32; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[d][r] *= inv;
     uint8_t* op = a.o + (b * a.so[0] + hd * a.so[1] + (long long)query * a.so[2]) * 4;
 #pragma unroll
     for (int d = 0; d < D32; ++d) {

@@ -377,16 +377,17 @@ def test_split_fp32_unit_edges(oracle_mod, seq, head_dim):
     check(oracle_mod, wl, FAST, use_mask=False)
 
 
-def f32_call(q, k, v, scale, softmax, k_token=None):
-    """[batch, heads, seq, d] tensors; k_token: the keys' token stride in elements."""
+def f32_call(q, k, v, scale, softmax, k_token=None, mask=None):
+    """[batch, heads, seq, d] tensors; k_token: the keys' token stride in elements; mask: [batch, seq]."""
     import torch
 
     b, h, s, d = q.shape
     o, st = torch.empty_like(q), (h * s * d, s * d, d)
     desc = binding.mha_desc(binding.OGC_F32, b, h, s, d, scale, softmax, st, (2 * d, d, k_token) if k_token else st, st, st)
-    binding.ogc_mha_run(desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), 0, o.data_ptr(), int(torch.cuda.current_stream().cuda_stream))
+    binding.ogc_mha_run(desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), 0 if mask is None else mask.data_ptr(), o.data_ptr(),
+                        int(torch.cuda.current_stream().cuda_stream))
     torch.cuda.synchronize()
-    return o.cpu(), binding.ogc_mha_kernel_name(desc, False)
+    return o.cpu(), binding.ogc_mha_kernel_name(desc, mask is not None)
 
 
 def f32_inputs(seq, head_dim, seed):
@@ -396,8 +397,8 @@ def f32_inputs(seq, head_dim, seed):
     return [torch.randn((1, 2, seq, head_dim), generator=g) for _ in range(3)]
 
 
-def f32_reference(q, k, v, scale):
-    s = (q.double() @ k.double().transpose(-1, -2)) * scale
+def f32_reference(q, k, v, scale, mask=None):
+    s = (q.double() @ k.double().transpose(-1, -2)) * scale + (0.0 if mask is None else mask.double()[:, None, None, :])
     return (s - s.amax(-1, keepdim=True)).exp().div((s - s.amax(-1, keepdim=True)).exp().sum(-1, keepdim=True)) @ v.double()
 
 
@@ -466,3 +467,75 @@ def test_split_fp32_errors_of_one_sign(head_dim, value):
     staged, name = f32_call(q.cuda(), wide, v.cuda(), scale, STABLE, k_token=1 << 22)
     assert split.startswith("ogc_mha_kernel<0,") and name.startswith("ogc_mha_f32_kernel<")
     assert float((got.double() - ref).norm()) <= float((staged.double() - ref).norm())
+
+
+@pytest.mark.parametrize("head_dim", [32, 64, 96])
+def test_split_fp32_small_operands(head_dim):
+    """Queries, keys, weights and values whose lower pieces lie below the smallest exponents, next to operands that make them
+    count: 24 bits of them all the same."""
+    q, k, v = f32_inputs(160, head_dim, 8800 + head_dim)
+    ref, scale = f32_reference(q, k, v, head_dim ** -0.5), head_dim ** -0.5
+    for a, b in ((-120, 120), (120, -120), (-112, 100)):
+        got, name = f32_call((q * 2.0 ** a).cuda(), (k * 2.0 ** b).cuda(), v.cuda(), scale * 2.0 ** -(a + b), STABLE)
+        assert name.startswith("ogc_mha_kernel<0,") and float((got.double() - ref).norm()) <= 1e-6 * float(ref.norm()), (a, b)
+    got, name = f32_call((q * 2.0 ** -60).cuda(), (k * 2.0 ** -60).cuda(), v.cuda(), scale * 2.0 ** 120, STABLE)  # (2^-149 counts)
+    assert name.startswith("ogc_mha_f32_kernel<") and float((got.double() - ref).norm()) <= 1e-6 * float(ref.norm())
+    # half of the keys with weights near 2^-122 of the others', and values near 2^122.  A score near 122 (base 2) is rounded at
+    # 2^-18 some head_dim / 2 times, and a weight moves by as much of itself: 2^-16.  One of 12 bits is off by 2^-12.8 in the mean
+    far_k, far_v = 0.1 * k, v.clone()
+    q[..., 0], far_k[..., 0] = 1.0, 0.0
+    far_k[:, :, 1::2, 0] = -122.0 * math.log(2.0) / scale
+    far_v[:, :, 1::2] *= 2.0 ** 122
+    ref = f32_reference(q, far_k, far_v, scale)
+    got, _ = f32_call(q.cuda(), far_k.cuda(), far_v.cuda(), scale, STABLE)
+    assert float((got.double() - ref).norm()) <= 2.0 ** -15 * float(ref.norm())
+    # a channel of values below the smallest exponent: sums and results rounded at 2^-149, a few times each after the division
+    v[..., 3] *= 2.0 ** -140
+    ref = f32_reference(q, k, v, scale)
+    got, _ = f32_call(q.cuda(), k.cuda(), v.cuda(), scale, STABLE)
+    assert float((got.double() - ref)[..., 3].abs().max()) <= 2.0 ** -147 and float(ref[..., 3].abs().max()) > 2.0 ** -143
+    # sums beyond 2^100 under the softmax without a maximum: their results are what they are (scores near 72 are rounded at 2^-18,
+    # base 2 at 2^-17, as above)
+    q[..., 0], far_k = 8.0, 0.1 * k
+    far_k[..., 0] = 9.0 / scale
+    v[..., 3] = 0.1
+    ref = f32_reference(q, far_k, v, scale)
+    got, _ = f32_call(q.cuda(), far_k.cuda(), v.cuda(), scale, FAST)
+    assert float((got.double() - ref).norm()) <= 2.0 ** -15 * float(ref.norm())
+    v[..., 3] = 0.0  # nothing but zeros is nothing else
+    ref = f32_reference(q, k, v, scale)
+    got, _ = f32_call(q.cuda(), k.cuda(), v.cuda(), scale, STABLE)
+    assert (got[..., 3] == 0.0).all() and float((got.double() - ref).norm()) <= 1e-6 * float(ref.norm())
+
+
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("seq", [384, 300])
+@pytest.mark.parametrize("head_dim", [32, 64, 96])
+def test_split_fp32_tiles_computed_again(head_dim, seq, masked):
+    """Three query tiles of sixteen (batch, head) pairs, in runs of two pairs an XCD: every tile that is computed again is the
+    same tile again, and its neighbours are left as they are."""
+    import torch
+
+    g = torch.Generator().manual_seed(8900 + seq + head_dim)
+    q, k, v = (torch.randn((2, 8, seq, head_dim), generator=g) for _ in range(3))
+    mask = None
+    if masked:
+        mask = torch.where(torch.arange(seq)[None, :] < torch.tensor([[seq // 2], [seq - 5]]), 0.0, -10000.0)
+    ref, scale = f32_reference(q, k, v, head_dim ** -0.5, mask), head_dim ** -0.5
+    on_gpu = mask.cuda() if masked else None
+    q[0, 5, seq - 1] = 0.0
+    q[0, 5, seq - 1, 0] = float("inf")                 # the last tile of one pair,
+    v[1, 2, 7, 9] = float("inf")                       # every tile of another, in one channel,
+    q[1, 6, 130] *= 2.0 ** 25                          # the middle tile of a third
+    ref[1, 6, 130] = f32_reference(q[1:, 6:7], k[1:, 6:7], v[1:, 6:7], scale, mask[1:] if masked else None)[0, 0, 130]
+    got, _ = f32_call(q.cuda(), k.cuda(), v.cuda(), scale, STABLE, mask=on_gpu)
+    assert (got[1, 2, :, 9] == float("inf")).all() and got[0, 5, seq - 1].isnan().all()
+    got[1, 2, :, 9] = ref[1, 2, :, 9].float()
+    got[0, 5, seq - 1] = ref[0, 5, seq - 1].float()
+    # (that one query's scores near 2^28 are rounded at 2^4: it has one key, and may be between two)
+    got[1, 6, 130] = ref[1, 6, 130].float()
+    assert float(((got.double() - ref).norm(dim=-1) / ref.norm(dim=-1)).max()) <= 1e-5
+    if masked:  # a mask that is no number: so is every result of its batch entry, and of no other
+        on_gpu[1, 40] = float("nan")
+        got, _ = f32_call(q.cuda(), k.cuda(), v.cuda(), scale, STABLE, mask=on_gpu)
+        assert got[1].isnan().all() and float((got[0, :5].double() - ref[0, :5]).norm()) <= 1e-6 * float(ref[0, :5].norm())
