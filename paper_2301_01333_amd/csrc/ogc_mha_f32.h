@@ -423,11 +423,14 @@ template <int D32, int FAST, int PLAIN> MHA_DEV void mha_split_body(const MhaArg
     // ---- normalise.  Some tiles are computed once more by the fp32 instruction.  Pieces are multiples of 2^-133 (the instruction
     // takes those below the smallest exponent as they are): what is below 2^-110 is off by 2^-134 at most.
     //   * Infinities: the pieces have no answer to them (infinity less itself is no number; nor is then the sum of the weights).
-    //   * Queries beyond 2^20, or below 2^-110: smaller keys move a score by 96 x 2^-134 x 2^20 and scalars of up to 2^60, 2^-47.
-    //   * Values beyond 2^20, and sums below 2^-74: smaller weights, up to 2^16 of them, move a sum by 2^-98, 2^-24 of it.
+    //   * Queries below 2^-110, or Q beyond 2^90 over the scalar: smaller keys move a score by 96 x 2^-134 Q times that, 2^-37.
+    //   * Values up to V and sums below 2^-94 V: smaller weights, up to 2^16 of them, move a sum by 2^-118 V, 2^-24 of it.  (Values
+    //     beyond 2^100 in any case: their sums, and the first piece of the largest of them, are close to infinity.)
     //   * Results below 2^-100: smaller values move them by 2^-134, 2^-34 of them.
     //   * Sums of zero where there are values below the smallest exponent, whose pieces may be zero.
-    // One look for the largest and the smallest of all, a closer one at what it finds.
+    // One look for the largest and the smallest of all (scalars of up to 2^60: queries and values up to 2^20, sums from 2^-74 on), a
+    // closer one at what it finds, for which the wavefronts put together what each saw of the values: 32 x 16 x 512 x 64 with values
+    // of 2^21 194 us, 190 without; all computed again 452.
     const float total = run_sum + other_half(run_sum), inv = 1.0f / total;
     float lowest = 1.0f;
 #pragma unroll
@@ -436,14 +439,22 @@ template <int D32, int FAST, int PLAIN> MHA_DEV void mha_split_body(const MhaArg
         for (int r = 0; r < 16; r += 2) lowest = least(lowest, oacc[d][r], oacc[d][r + 1]);
     // (sums from 2^-74 on over a total of up to 2^26 are results from 2^-100 on)
     if (__builtin_expect(__syncthreads_or(!(total > 0.0f && total <= 0x1p26f && wide <= 0x1p20f && lowest >= 0x1p-74f)), 0)) {
-        bool again = !(total > 0.0f && total <= 0x1p120f && wide <= 0x1p20f), nothing = false;
+        float* const seen = (float*)smem;  // (the barrier above: nothing in LDS is read any more)
+#pragma unroll
+        for (int i = 1; i < 64; i *= 2) wide = fmaxf(wide, __shfl_xor(wide, i));
+        if (lane == 0) seen[wave] = wide;
+        __syncthreads();
+        wide = fmaxf(fmaxf(seen[0], seen[1]), fmaxf(seen[2], seen[3]));
+        const float low = fmaxf(0x1p-74f, wide * 0x1p-94f);
+        bool again = !(total > 0.0f && total <= 0x1p120f && wide <= 0x1p100f && wide * fabsf(c) <= 0x1p90f), nothing = false;
 #pragma unroll
         for (int d = 0; d < D32; ++d)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                again = again || zero_last(oacc[d][r]) < zero_last(0x1p-74f) || zero_last(oacc[d][r] * inv) < zero_last(0x1p-100f);
+                again = again || zero_last(oacc[d][r]) < zero_last(low) || zero_last(oacc[d][r] * inv) < zero_last(0x1p-100f);
                 nothing = nothing || oacc[d][r] == 0.0f;
             }
+        again = again || (nothing && wide > 0x1p20f);
         if (__syncthreads_or(nothing))
             for (int u = tid; !again && u < S * (D / 4); u += 256) {
                 const v4f x = *(const v4f*)(vbase + (u / (D / 4)) * vss + u % (D / 4) * 16);

@@ -526,7 +526,9 @@ def test_split_fp32_tiles_computed_again(head_dim, seq, masked):
     q[0, 5, seq - 1] = 0.0
     q[0, 5, seq - 1, 0] = float("inf")                 # the last tile of one pair,
     v[1, 2, 7, 9] = float("inf")                       # every tile of another, in one channel,
-    q[1, 6, 130] *= 2.0 ** 25                          # the middle tile of a third
+    q[1, 6, 130] *= 2.0 ** 25                          # the middle tile of a third (which its closer look lets pass),
+    q[1, 1, 140] *= 2.0 ** -115                        # the middle tile of a fourth
+    ref[1, 1, 140] = f32_reference(q[1:, 1:2], k[1:, 1:2], v[1:, 1:2], scale, mask[1:] if masked else None)[0, 0, 140]
     ref[1, 6, 130] = f32_reference(q[1:, 6:7], k[1:, 6:7], v[1:, 6:7], scale, mask[1:] if masked else None)[0, 0, 130]
     got, _ = f32_call(q.cuda(), k.cuda(), v.cuda(), scale, STABLE, mask=on_gpu)
     assert (got[1, 2, :, 9] == float("inf")).all() and got[0, 5, seq - 1].isnan().all()
@@ -539,3 +541,36 @@ def test_split_fp32_tiles_computed_again(head_dim, seq, masked):
         on_gpu[1, 40] = float("nan")
         got, _ = f32_call(q.cuda(), k.cuda(), v.cuda(), scale, STABLE, mask=on_gpu)
         assert got[1].isnan().all() and float((got[0, :5].double() - ref[0, :5]).norm()) <= 1e-6 * float(ref[0, :5].norm())
+
+
+@pytest.mark.parametrize("power", [19, 21, 56, 99, 110])
+@pytest.mark.parametrize("head_dim", [32, 64, 96])
+def test_split_fp32_large_operands(head_dim, power):
+    """Queries and values on either side of what the first look and the closer one let pass, between zero values, next to weights
+    that their smallest pieces are lost of and next to ones that none are: the fp32 instruction's bits all the same."""
+    import torch
+
+    q, k, v = f32_inputs(160, head_dim, 9000 + head_dim)
+    ref, scale = f32_reference(q, k, v, head_dim ** -0.5), head_dim ** -0.5
+    if power <= 56:
+        got, name = f32_call((q * 2.0 ** power).cuda(), k.cuda(), (v * 2.0 ** power).cuda(), scale * 2.0 ** -power, STABLE)
+        assert name.startswith("ogc_mha_kernel<0,")
+        assert float((got.double() * 2.0 ** -power - ref).norm()) <= 1e-6 * float(ref.norm())
+    # one channel is zero but for large values under weights near 2^-c of the others', which carry their result: as many bits as the
+    # staged body has, which a token stride of 2^24 bytes takes the same call to (scores near c are rounded at c x 2^-24)
+    q[..., 0], far_k = 1.0, 0.1 * k
+    for c in (60, 112):
+        far_k[..., 0] = 0.0
+        far_k[:, :, 1::2, 0] = -c * math.log(2.0) / scale
+        far_v = v.clone()
+        far_v[..., 3] = 0.0
+        far_v[:, :, 1::2, 3] = 2.0 ** power * (1.0 + v[:, :, 1::2, 3].abs())
+        ref = f32_reference(q, far_k, far_v, scale)
+        got, name = f32_call(q.cuda(), far_k.cuda(), far_v.cuda(), scale, STABLE)
+        assert name.startswith("ogc_mha_kernel<0,")
+        err = (got.double() - ref)[..., 3].norm() / ref[..., 3].norm()
+        wide = torch.zeros(159 * (1 << 22) + 2 * head_dim, device="cuda")
+        torch.as_strided(wide, (1, 2, 160, head_dim), (2 * head_dim, head_dim, 1 << 22, 1)).copy_(far_k)
+        staged, name = f32_call(q.cuda(), wide, far_v.cuda(), scale, STABLE, k_token=1 << 22)
+        assert name.startswith("ogc_mha_f32_kernel<")
+        assert float(err) <= 1.5 * float((staged.double() - ref)[..., 3].norm() / ref[..., 3].norm()) + 2.0 ** -22, (c, float(err))
