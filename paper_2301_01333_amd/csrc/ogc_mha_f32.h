@@ -455,12 +455,24 @@ template <int D32, int FAST, int PLAIN> MHA_DEV void mha_split_body(const MhaArg
                 nothing = nothing || oacc[d][r] == 0.0f;
             }
         again = again || (nothing && wide > 0x1p20f);
-        if (__syncthreads_or(nothing))
-            for (int u = tid; !again && u < S * (D / 4); u += 256) {
-                const v4f x = *(const v4f*)(vbase + (u / (D / 4)) * vss + u % (D / 4) * 16);
+        // Channels of zeros, as padding leaves them, are told from small values by the values themselves, eight loads on their way at
+        // a time: 2 x 8 x 1024 x 64 53 us, 47.6 without such channels (61 with one load at a time).
+        if (__syncthreads_or(nothing)) {
+            constexpr int AT_ONCE = 8;
+            const int n = S * (D / 4);
+            for (int u = tid; !again && u < n; u += 256 * AT_ONCE) {
+                v4f x[AT_ONCE];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) again = again || zero_last(x[e]) < zero_last(0x1p-126f);
+                for (int t = 0; t < AT_ONCE; ++t) {
+                    const int w = u + 256 * t < n ? u + 256 * t : u;
+                    x[t] = *(const v4f*)(vbase + (w / (D / 4)) * vss + w % (D / 4) * 16);
+                }
+#pragma unroll
+                for (int t = 0; t < AT_ONCE; ++t)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) again = again || zero_last(x[t][e]) < zero_last(0x1p-126f);
             }
+        }
         if (__syncthreads_or(again)) {
             typedef MhaStaged<OGC_F32, D32> T;
             mha_staged_body<OGC_F32, D32, FAST, PLAIN, 1, 1>(a, smem, smem + T::K_BYTES, (float*)(smem + T::K_BYTES + T::V_BYTES));
