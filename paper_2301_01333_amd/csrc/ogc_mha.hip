@@ -171,7 +171,7 @@ MHA_DEV void mha_staged_body(const MhaArgs& a, uint8_t* k_lds, uint8_t* vt_lds, 
                 vreg[i][0] = (full || key < S) ? *(const v4i*)(vbase + key * vss + c * 16) : (v4i){0, 0, 0, 0};
             }
         }
-        if (tid < KB) {
+        if (!PLAIN && tid < KB) {  // (asked here, not left to the compiler, which cannot tell that nothing reads LDS that it is handed)
             const int key = key0 + tid;
             mpad = key >= S;
             mreg = 0.0f;
@@ -208,7 +208,7 @@ MHA_DEV void mha_staged_body(const MhaArgs& a, uint8_t* k_lds, uint8_t* vt_lds, 
                 for (int j = 0; j < 4; ++j) *(int*)(vt_lds + (4 * c + j) * VSTR + kl * 4) = vreg[i][0][j];
             }
         }
-        if (tid < KB) m_lds[tid] = mpad ? -INFINITY : (mreg < MHA_MASK_LOW ? MHA_MASK_LOW : mreg) * LOG2E;
+        if (!PLAIN && tid < KB) m_lds[tid] = mpad ? -INFINITY : (mreg < MHA_MASK_LOW ? MHA_MASK_LOW : mreg) * LOG2E;
     };
 
     const int nkb = (S + KB - 1) / KB;
