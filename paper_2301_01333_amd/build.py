@@ -52,13 +52,7 @@ def build_library(verbose: bool = True) -> str:
     return LIB
 
 
-def check_stream_kernel_registers(verbose: bool = True) -> None:
-    """The stream kernel keeps its operands and accumulators in v80..v255 behind the compiler's back
-    (amdgpu_num_vgpr caps the compiler below v80).  This compiles the kernels to assembly and fails if any
-    compiler-generated instruction of those kernels WRITES a register at or above v80, reads one outside the
-    accumulator range v128..v255 (the epilogue takes the accumulators as sources where they are), or if the
-    kernels contain calls."""
-    import re
+def _device_assembly(source: str) -> str:
     import tempfile
 
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -66,11 +60,23 @@ def check_stream_kernel_registers(verbose: bool = True) -> None:
         out = os.path.join(td, "k.s")
         cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-ffp-contract=off", "-Xclang", "-target-feature",
                "-Xclang", "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-S", "--cuda-device-only",
-               "-o", out, os.path.join(CSRC, "ogc_kernels.hip")]
+               "-o", out, os.path.join(CSRC, source)]
         r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         if r.returncode != 0:
             raise RuntimeError("hipcc -S failed\n" + r.stdout)
-        text = open(out).read()
+        with open(out) as f:
+            return f.read()
+
+
+def check_stream_kernel_registers(verbose: bool = True) -> None:
+    """The stream kernel keeps its operands and accumulators in v80..v255 behind the compiler's back
+    (amdgpu_num_vgpr caps the compiler below v80).  This compiles the kernels to assembly and fails if any
+    compiler-generated instruction of those kernels WRITES a register at or above v80, reads one outside the
+    accumulator range v128..v255 (the epilogue takes the accumulators as sources where they are), or if the
+    kernels contain calls."""
+    import re
+
+    text = _device_assembly("ogc_kernels.hip")
     reg = re.compile(r"\bv(\d+)\b|\bv\[(\d+):(\d+)\]")
     checked = 0
     for m in re.finditer(r"^(_Z20ogc_layer_dma_kernel\w*):[^\n]*\n(.*?)\n\ts_endpgm", text, re.S | re.M):
@@ -124,7 +130,40 @@ def check_stream_kernel_registers(verbose: bool = True) -> None:
               "epilogue use scratch memory)" % (checked, spilling), flush=True)
 
 
+def check_split_attention_loops(verbose: bool = True) -> None:
+    """The split fp32 attention kernels use (nearly) all registers, and at 96 channels some are spilled around the loop over the
+    keys.  Inside it they must not be: this compiles the kernels to assembly, finds the loop of two rounds (48 matrix instructions
+    for 32 channels) and fails if it touches scratch memory more than once (one reload in two rounds is what the masked fast
+    softmax at 96 channels has)."""
+    import re
+
+    text = _device_assembly("ogc_mha.hip")
+    checked = 0
+    for m in re.finditer(r"^(_Z14ogc_mha_kernelILi0ELi([123])E\w*):[^\n]*\n(.*?)\n\.Lfunc_end", text, re.S | re.M):
+        name, lines, at, found = m.group(1), [l.split(";")[0] for l in m.group(3).splitlines()], {}, 0
+        for i, line in enumerate(lines):
+            label, branch = re.match(r"(\.LBB\w+):", line), re.match(r"\s+s_c?branch\w*\s+(\.LBB\w+)", line)
+            if label:
+                at[label.group(1)] = i
+            if not branch or branch.group(1) not in at:
+                continue
+            body = lines[at[branch.group(1)]:i]
+            if sum("v_mfma_f32_32x32x16_bf16" in l for l in body) != 48 * int(m.group(2)):
+                continue
+            found += 1
+            if sum("scratch_" in l for l in body) > 1:
+                raise RuntimeError("%s spills registers in its loop over the keys" % name)
+        if not found:
+            raise RuntimeError("%s: no loop over the keys found in the assembly" % name)
+        checked += 1
+    if checked != 12:
+        raise RuntimeError("split attention kernels found in the assembly: %d of 12" % checked)
+    if verbose:
+        print("split attention kernels checked: %d (no spills in the loop over the keys)" % checked, flush=True)
+
+
 if __name__ == "__main__":
     print(build_library())
     check_stream_kernel_registers()
+    check_split_attention_loops()
     sys.exit(0)
