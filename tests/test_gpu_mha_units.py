@@ -367,10 +367,11 @@ def test_i8_token_strides_beyond_32_bits_of_offset(oracle_mod):
     assert torch.equal(*outs)
 
 
-@pytest.mark.parametrize("seq", [33, 64, 65, 97, 128, 129, 160, 300])
+@pytest.mark.parametrize("seq", [16, 32, 33, 64, 65, 96, 97, 128, 129, 160, 300])
 @pytest.mark.parametrize("head_dim", [32, 64, 96])
 def test_split_fp32_unit_edges(oracle_mod, seq, head_dim):
-    """One to ten blocks of 32 keys, whole and ragged, on either side of the rule, with and without a mask."""
+    """One to ten blocks of 32 keys, whole and ragged, with and without a mask, on either side of the rule (32 keys for 64 channels,
+    96 for the others)."""
     wl = synth.make_mha("f32", 2, seq, 2 * head_dim, 2, 8300 + seq + head_dim, name="split S=%d d=%d" % (seq, head_dim))
     check(oracle_mod, wl)
     check(oracle_mod, wl, use_mask=False)
