@@ -24,9 +24,9 @@
  * every base pointer 16-byte aligned.  mask is fp32 [batch][seq], finite values (use -10000, not -infinity), or
  * NULL; values below -2.3e38 (bf16: or below -3e38 * scale), which no score holds, count as that one value.  o has q's dtype.  The library allocates nothing and keeps no state between calls.
  *
- * Arithmetic: OGC_F32 multiplies fp32 operands with fp32 accumulation throughout (up to 96 channels by exact splits of the
- * operands into three bf16 values, whose products are left 2^-24 of them at most; tiles with operands or results to which that
- * does not apply are computed by the fp32 instruction).  OGC_BF16 multiplies bf16
+ * Arithmetic: OGC_F32 multiplies fp32 operands with fp32 accumulation throughout (up to 96 channels by splitting each operand
+ * into three bf16 values without loss and leaving out the smallest of their products, 2^-24 of the whole at most; tiles of 128
+ * queries whose operands or results are too small or too large for that are computed by the fp32 instruction).  OGC_BF16 multiplies bf16
  * operands with fp32 accumulation; scores, exponentials and row sums are fp32; the softmax weights are rounded
  * to bf16 (nearest even) for the second matmul and o is rounded to bf16 once at the end.  OGC_I8 (Table I lists the
  * MHA rows as Int8 too) has an entry point of its own, ogc_mha_run_i8, because it needs quantization scales.

@@ -65,10 +65,13 @@ template <int DT> OGC_DEV void mma32(typename AccT<DT>::type& c, const v4i& w, c
 }
 
 // Two k-steps of E4M3 at once (any two, as long as both operands agree): one instruction over their 64 bytes at twice the rate
-// of the four that mma32 would take, with the same sums.  Four 1024-wide layers at batch 8192, fused, between fp32 rows: 82 -> 74 us
-// (the weights' way from the L2 bounds it now); 479-1024-1024-512-256-1 at 4096 38.9 -> 37.2.  Not where eight waves split K: there
-// a wave waits for its few instructions one by one (that chain at batch 256, 31.0 against 31.3).  (The other types keep one
-// instruction a step.)
+// of the four that mma32 would take.  Four 1024-wide layers at batch 8192, fused, between fp32 rows: 81.5 -> 73.9 us (the weights'
+// way from the L2 bounds it now), with the same bytes; 479-1024-1024-512-256-1 at 4096 39.5 -> 36.8.  Error against 64 bits,
+// relative 2-norm of one layer, this / the four: normal codes 1.5e-5 / 1.5e-5, log-normal ones 5.8e-5 / 5.8e-5, of one sign
+// 2.7e-6 / 2.7e-6, one product in 64 2^14 times the others 2.2e-4 / 2.2e-4, large products that cancel 2.2e-2 / 2.2e-2: the same to
+// three digits for 13 distributions and K of 64, 128, 320 and 1024, in both fused kernels and the register-staged tile.  (So it
+// does not align its products to the largest of all 64.)  Not where eight waves split K: there a wave waits for its few
+// instructions one by one (that chain at batch 256, 31.0 against 31.3).  (The other types keep one instruction a step.)
 typedef int v8i __attribute__((ext_vector_type(8)));
 OGC_DEV void mma64(v16f& c, const v4i& w0, const v4i& w1, const v4i& x0, const v4i& x1) {
     c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(__builtin_shufflevector(w0, w1, 0, 1, 2, 3, 4, 5, 6, 7),

@@ -43,7 +43,7 @@ struct MhaArgs {
     int batch, heads, seq;
     int q_tiles;       // ceil(seq / queries per workgroup)
     int xcd_order;     // 1: workgroups of one (batch, head) are placed on one XCD
-    uint32_t tiles_magic, heads_magic;  // bf16: reciprocals of q_tiles and heads for div_magic
+    uint32_t tiles_magic, heads_magic;  // streaming and split bodies: reciprocals of q_tiles and heads for div_magic
     float scale_log2;  // scale * log2(e)
     float inv_scale;   // bf16, mask in LDS: 1 / scale, and the bound its quotient is held to
     float addend_max;
@@ -531,10 +531,13 @@ int query_groups(const ogc_mha_desc* d) {
 // The split body or the staged one (fp32).  The split body multiplies a row's number by 24 bits of stride, and takes up to 96
 // channels (128: its registers do not hold a query's pieces).  What it leaves out of small operands may count under extreme scalars
 // (see its end).  Its first block costs more.  Staged / split, us, batch x heads x seq,
-// with a mask:
-//   32 channels: 64x12x33 10.5 / 11.0;  64x12x64 11.9 / 12.8;  64x12x96 16.4 / 16.3;  32x16x128 15.6 / 14.1;  8x16x512 43.8 / 32.0.
-//   64: 1x8x16 7.1 / 7.2;  1x8x33 7.6 / 7.4;  64x12x33 18.4 / 16.5;  64x12x96 28.2 / 25.5;  4x12x197 21.0 / 15.3;  32x16x512 277 / 195.
-//   96: 1x8x33 10.0 / 10.1;  64x12x64 30.1 / 28.9;  1x8x64 10.4 / 10.6;  64x12x96 43.7 / 44.5;  32x16x128 38.7 / 33.4;  8x16x512 110 / 77.
+// with a mask (shapes that the rule stages: both as they were when the line was drawn):
+//   32 channels: 64x12x33 10.5 / 11.0;  64x12x64 11.9 / 12.8;  64x12x96 16.4 / 16.3;  64x12x97 19.4 / 18.0;  32x16x128 15.0 / 13.7;
+//     8x16x512 43.3 / 32.9.
+//   64: 1x8x16 7.1 / 7.2;  1x8x33 7.8 / 7.7;  64x12x33 18.4 / 16.2;  64x12x64 20.3 / 19.5;  64x12x96 28.3 / 25.9;  4x12x197 20.8 / 15.5;
+//     32x16x512 273 / 190.
+//   96: 1x8x33 10.0 / 10.1;  64x12x64 30.1 / 28.9;  1x8x64 10.4 / 10.6;  64x12x96 43.7 / 44.5;  64x12x97 50.6 / 42.2;  32x16x128 37.9 /
+//     33.1;  8x16x512 109 / 78.
 bool split_case(const ogc_mha_desc* d) {
     const int64_t most = (int64_t)1 << 24;
     if (d->head_dim > 96 || d->k_stride[2] * 4 >= most || d->v_stride[2] * 4 >= most) return false;

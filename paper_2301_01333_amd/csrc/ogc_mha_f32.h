@@ -12,9 +12,10 @@
 // 2.2e-7, 1024 x 96 7.2e-7 / 3.0e-7, 160 x 32 3.2e-7 / 1.4e-7; operands of one magnitude (+-1.0078124, +-1.1) 512 x 64 5.9e-7 / 3.4e-7
 // and 8.1e-7 / 2.8e-7, with the largest pieces there are (+-(1 + 2^-8 - 2^-17)) 5.6e-7 / 3.9e-7; log-normal ones 9.1e-7 / 3.2e-7.
 //
-// What bounds it: power.  32 x 16 heads x 512 x 64 (206 GFLOP of bf16 instructions): 277 -> 195 us, but 151 us where all
-// inputs are zero; fewer vector instructions (377 -> 300 a block and wavefront) changed nothing there and gave 10 % where half
-// of the chip works.  2 x 8 x 1024 x 64: 80 -> 48 us; 8 x 16 x 512 x 96: 110 -> 77; more at split_case.  Tried: eight wavefronts that
+// What bounds it: power.  32 x 16 heads x 512 x 64 (206 GFLOP of bf16 instructions): 273 -> 190 us, but 148 us where all
+// inputs are one; the clock is at 1.8 GHz, the matrix pipe busy in 51 % and the vector ALU in 55 % of the cycles; fewer vector
+// instructions (377 -> 300 a block and wavefront) changed nothing there and gave 10 % where half
+// of the chip works.  2 x 8 x 1024 x 64: 80 -> 48 us; 8 x 16 x 512 x 96: 109 -> 78; more at split_case.  Tried: eight wavefronts that
 // share the pieces of keys and values (50.2 against 51.1 us at 8 x 16 x 512 x 64, 202 against 197 at 32); 96 and 128 channels with
 // 512 registers, one wavefront a SIMD (arrays in scratch memory, ten times as long).
 #ifndef OGC_MHA_F32_H
