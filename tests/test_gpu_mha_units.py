@@ -575,3 +575,29 @@ def test_split_fp32_large_operands(head_dim, power):
         staged, name = f32_call(q.cuda(), wide, far_v.cuda(), scale, STABLE, k_token=1 << 22)
         assert name.startswith("ogc_mha_f32_kernel<")
         assert float(err) <= 1.5 * float((staged.double() - ref)[..., 3].norm() / ref[..., 3].norm()) + 2.0 ** -22, (c, float(err))
+
+
+@pytest.mark.parametrize("head_dim", [64, 96])
+def test_split_fp32_recorded_in_a_hip_graph(head_dim):
+    """One call under stream capture (96 channels raise the kernel's LDS limit at every launch), replayed with other inputs in the
+    same buffers, eager calls and synchronisations in between; one of the inputs has tiles that are computed again."""
+    import torch
+
+    q, k, v = (t.cuda() for t in f32_inputs(200, head_dim, 9100 + head_dim))
+    o, st, scale = torch.empty_like(q), (2 * 200 * head_dim, 200 * head_dim, head_dim), head_dim ** -0.5
+    desc = binding.mha_desc(binding.OGC_F32, 1, 2, 200, head_dim, scale, STABLE, st, st, st, st)
+    assert binding.ogc_mha_kernel_name(desc, False).startswith("ogc_mha_kernel<0,")
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        binding.ogc_mha_run(desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), 0, o.data_ptr(), int(torch.cuda.current_stream().cuda_stream))
+    for i in range(4):
+        for t, new in zip((q, k, v), f32_inputs(200, head_dim, 9200 + 10 * i)):
+            t.copy_(new)
+        if i == 2:
+            q[0, 1, 150, 0] = float("inf")
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        want, _ = f32_call(q, k, v, scale, STABLE)
+        assert torch.equal(o.cpu().nan_to_num(7.0), want.nan_to_num(7.0)) and bool(want.isnan().any()) == (i == 2)
