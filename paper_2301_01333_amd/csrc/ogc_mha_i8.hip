@@ -42,6 +42,7 @@ struct MhaI8Args {
     long long sq[3], sk[3], sv[3], so[3];  // element (= byte) strides: batch, head, token
     int batch, heads, seq;
     int q_tiles;    // ceil(seq / 128)
+    int key_slots;  // streaming kernel: units of keys that LDS holds
     int xcd_order;  // 1: the query tiles of one (batch, head) are placed on one XCD
     uint32_t tiles_magic, heads_magic;  // reciprocals of q_tiles and heads (0: divide)
     int far;        // 1: a unit's rows span more than 32 bits of byte offset
@@ -70,8 +71,8 @@ MHA8_DEV float base2_mask(float m) {
     return (m < -2.3e38f ? -2.3e38f : m) * 1.44269504088896340736f;
 }
 
-// The plain kernel: keys and values through registers, both passes over 64-key blocks.  For launches that do not fill the
-// chip (stream_case below).  D32 = head_dim / 32.  Key blocks of 64 (two 32-key groups).
+// The plain kernel: keys and values through registers, both passes over 64-key blocks.  For launches of 32 and 64 channels that
+// do not fill the chip (stream_case below).  D32 = head_dim / 32.  Key blocks of 64 (two 32-key groups).
 template <int D32> __global__ __launch_bounds__(256, 2) void ogc_mha_i8_kernel(MhaI8Args a) {
     constexpr int D = D32 * 32, KB = 64, SB = 2;
     constexpr int KSTR = D + 16;    // bytes per key row of K in LDS (padded: consecutive rows start 4 banks apart)
@@ -254,34 +255,56 @@ typedef __attribute__((address_space(3))) v2i mha8_lds_v2i;
 
 constexpr int MHA8_UNIT = 64;        // keys per unit: two groups of 32
 constexpr int MHA8_LDS_KEYS = 4096;  // addends held in LDS; longer sequences replace them every 64 units
-constexpr int MHA8_SLOTS = 3;        // units of keys, and of values, in LDS: one in use, two on their way
+constexpr int MHA8_VSLOTS = 3;       // units of values in LDS: one in use, two on their way
 constexpr float MHA8_NEAR = 8192.0f; // scores (base-2 domain) that may go without an addend
 
 template <int D32> struct Mha8 {
     static constexpr int D = D32 * 32, CH = D / 16;  // bytes and 16-byte pieces of a row
-    static constexpr int UNIT_BYTES = MHA8_UNIT * D, RING = 2 * MHA8_SLOTS * UNIT_BYTES;
-    // Position of piece c of row r inside the row: c ^ swz(r).  A read of the first product takes the same piece of eight
-    // consecutive keys, one of the second (byte transpose) 16-byte pieces of the keys 8 a + 4 h + (0..3), a = 0, 1: these
-    // permutations put the eight pieces on distinct groups of four banks, for rows of 32, 64, 96 and 128 bytes.
-    static __device__ __forceinline__ int kswz(int r) { return D32 == 4 ? (r & 7) : D32 == 2 ? ((r >> 1) & 3) : ((r >> 2) & 1); }
+    static constexpr int UNIT_BYTES = MHA8_UNIT * D;
+    static constexpr int RESIDENT = D32 == 1 ? 6 : D32 == 2 ? 5 : D32 == 3 ? 4 : 3;  // workgroups that the registers of a compute unit hold
+    // Position of piece c of row r inside the row: c ^ swz(r).  LDS takes a 16-byte read in groups of 16 lanes and has 64 banks:
+    // a read of the first product takes the same piece of sixteen consecutive keys, one of the second (byte transpose) 16-byte
+    // pieces of the keys 8 a + 4 h + (0..3), a = 0, 1.  With these permutations, for rows of 32, 64, 96 and 128 bytes, the
+    // former takes 4.1 clocks (8.0 with the pieces of eight keys apart), the latter 3.4 to 4.1.
+    static __device__ __forceinline__ int kswz(int r) { return D32 == 4 ? ((r >> 1) & 7) : D32 == 2 ? ((r >> 2) & 3) : ((r >> 3) & 1); }
     static __device__ __forceinline__ int vswz(int r) {
         return D32 == 4 ? ((r & 3) | ((r >> 1) & 4)) : D32 == 2 ? (((r >> 1) & 1) | ((r >> 2) & 2)) : ((r >> 3) & 1);
     }
 };
 
-template <int N> MHA8_DEV void mha8_wait_and_meet() {  // all but the N newest loads have landed, LDS accesses are done, then the workgroup meets
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+// All but the n newest loads have landed (or a few more), LDS accesses are done, then the workgroup meets.
+MHA8_DEV void mha8_wait_and_meet(int n) {
+    if (n >= 4) {
+        if (n >= 18) asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
+        else if (n >= 12) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+        else if (n >= 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else if (n >= 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    } else if (n >= 2) {
+        if (n == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+    } else {
+        if (n == 1) asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // The streaming kernel.  D32 = head_dim / 32.
 //
-// What it spends most on, and what follows from that: the vector ALU (49 % of the SIMDs' cycles issue to it, 16 % of the
-// matrix pipe's are busy, 37 % of the LDS cycles are conflicts; 128 x 8 x 384 x 128).  Per score it owes a conversion, a multiply-add, an
-// exponential and a packing conversion in the second pass; the plain kernel spends three times that, and its byte-wise
-// transposed LDS writes of the values conflict for two thirds of the LDS cycles.  Here
-//   * keys and values go from global memory straight into LDS, two units ahead; V^T leaves LDS through the transposing
-//     read (ds_read_b64_tr_b8: 8 keys x 16 channels per 16 lanes, the keys' rows chosen by the lanes' addresses);
-//   * a group of 32 keys whose mask entries are all zero (most of them) takes its maximum over the integer scores, two
+// What bounds it, and what follows from that: the vector ALU (65 % of the SIMDs' cycles at 128 x 16 x 512 x 64, 49 % at 128 x 8 x
+// 384 x 128; the matrix pipe 20 to 25 %), the way of the first keys from HBM, and how many workgroups a compute unit has to
+// cover that with.  Per score it owes a conversion, a multiply-add, an exponential and a packing conversion in the second pass.
+//   * Keys and values go from global memory straight into LDS; V^T leaves it through the transposing read
+//     (ds_read_b64_tr_b8: 8 keys x 16 channels per 16 lanes, the keys' rows chosen by the lanes' addresses).
+//   * The first half of the keys, the queries and the mask are asked for at once; then all keys for which LDS has slots.
+//     Where that is all that count (up to 384 keys of 128 channels), the second pass finds them there and loads values only.
+//   * Registers are kept to 80 / 96 / 128 / 168 (32 / 64 / 96 / 128 channels) for 6 / 5 / 4 / 3 workgroups on a compute unit
+//     (Mha8::RESIDENT): one group of 32 keys at a time in the second pass, one place where its product is taken, so that the
+//     accumulators stay in place.  128 channels in 128 registers for four: 88 -> 103 us, slots for two units of keys only.
+//     Workgroups of six or eight wavefronts share their loads among more queries and are slower all the same: six leave two
+//     SIMDs with a wavefront too many for a second workgroup (131 us), eight of 128 channels spill (109).
+//   * A group of 32 keys whose mask entries are all zero (most of them) takes its maximum over the integer scores, two
 //     per instruction, and needs no addend per score: the scale is positive, so the order is the same; the multiply by
 //     127 and the row maximum ride in the exponent's multiply-add (2^(x + log2 127) is 127 * 2^x).  log2(127) - maximum is
 //     one fp32 value, rounded at the maximum's magnitude, so this form is kept to scores below 2^13 (MHA8_NEAR): there it
@@ -294,10 +317,12 @@ template <int N> MHA8_DEV void mha8_wait_and_meet() {  // all but the N newest l
 //   * a unit whose mask entries are so low that no int8 product can make up for it is left out of both passes: its
 //     numerators round to zero whatever q and k hold.  With |S| <= 16384 d, and some key's mask 0 or more, key j has none
 //     if mask[j] + 2 * 16384 d c1 + 16 < 0 (base-2 domain; a numerator is zero from 2^-8 on).
-// Measured (same card, padding masks of half the length to all of it, plain / this): batch 128 x 8 heads x 384 tokens x 128:
-// 167 -> 105 us (460 -> 735 TOP/s); 128 x 16 x 512 x 64: 241 -> 171 (without a mask 242 -> 187); 1 x 8 x 8192 x 128: 505 -> 290.
+// Measured (same card, padding masks of half the length to all of it, inputs from HBM; two workgroups on a compute unit, slots for
+// three units of keys, keys twice, a division per output / this): batch 128 x 8 heads x 384 tokens x 128: 125 -> 88 us (619 ->
+// 880 TOP/s); 128 x 16 x 512 x 64: 189 -> 166; 16 x 8 x 1024 x 96: 79 -> 60; 64 x 8 x 384 x 32: 32.7 -> 26.1; 1 x 8 x 384 x 128: 16.3 -> 14.8.
+// Without any arithmetic over the keys 62 of the 88 us are left: loads, barriers, a workgroup's start and its end.
 // Both passes in one loop body (less code) was 15 % slower: the accumulators of the second live through the first.
-template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_mha_i8_stream_kernel(MhaI8Args a) {
+template <int D32> __global__ __launch_bounds__(256, Mha8<D32>::RESIDENT) void ogc_mha_i8_stream_kernel(MhaI8Args a) {
     typedef Mha8<D32> B;
     constexpr int D = B::D, U = B::UNIT_BYTES;
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -305,6 +330,7 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, col = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int NW = 4, threads = NW * 64, PW = (2 * D32 + NW - 1) / NW;  // PW: 1 KiB loads of a wavefront for a unit's keys (or values)
     // each XCD takes a contiguous run of (batch, head) pairs: the query tiles of a pair share its L2
     const uint32_t wg = blockIdx.x, lin = a.xcd_order ? (wg & 7) * (gridDim.x >> 3) + (wg >> 3) : wg;
     const int bh = a.tiles_magic ? __umulhi(lin, a.tiles_magic) : lin / a.q_tiles, qt = (int)lin - bh * a.q_tiles;
@@ -313,8 +339,10 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
     const uint8_t* kbase = a.k + b * a.sk[0] + hd * a.sk[1];
     const uint8_t* vbase = a.v + b * a.sv[0] + hd * a.sv[1];
     const long long kss = a.sk[2], vss = a.sv[2];
+    const uint32_t ring = (uint32_t)a.key_slots * U;  // bytes of the keys' slots; the values' follow
 
     // this lane's query row as the second operand of the first product: bytes 32 i + 16 h .. + 15 of the row
+    const bool idle = (qt * 4 + wave) * 32 >= S;  // (loads its share and meets the others)
     const int query = (qt * 4 + wave) * 32 + col;
     v4i qreg[D32];
     {
@@ -323,33 +351,76 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
 #pragma unroll
         for (int i = 0; i < D32; ++i) qreg[i] = *(const v4i*)(qp + i * 32 + h * 16);
     }
+    // ... and the first of the mask
+    const float* const mrow = a.mask + (long long)b * S;
+    float mfirst[4];
+    auto read_mask = [&](int from, float (&t)[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[i] = a.mask && from + tid + threads * i < S ? mrow[from + tid + threads * i] : 0.0f;
+    };
+    read_mask(0, mfirst);
+
+    // ---- direct loads.  A unit's keys are 2 * D32 KiB, dealt round the wavefronts from the first on, its values from the last.
+    // Load m covers the pieces 64 m + lane of the unit's LDS image.
+    const int first[2] = {wave, NW - 1 - wave};  // this wavefront's first load of a unit's keys, values
+    uint32_t voff[2][PW];  // byte offset of the lane's piece from the unit's first row; !a.far: it fits 32 bits
+#pragma unroll
+    for (int is_v = 0; is_v < 2; ++is_v)
+#pragma unroll
+        for (int i = 0; i < PW; ++i) {
+            const int p = (first[is_v] + i * NW) * 64 + lane, r = p / B::CH;
+            voff[is_v][i] = (uint32_t)r * (uint32_t)(is_v ? vss : kss) + ((p % B::CH) ^ (is_v ? B::vswz(r) : B::kswz(r))) * 16;
+        }
+    int loads = 0;  // direct loads of this wavefront so far
+    auto load = [&](int is_v, int unit, uint32_t slot) {
+        const long long rs = is_v ? vss : kss;
+        const uint8_t* g = (is_v ? vbase : kbase) + (long long)(unit * MHA8_UNIT) * rs;
+        const bool full = (unit + 1) * MHA8_UNIT <= S;
+#pragma unroll
+        for (int i = 0; i < PW; ++i) {
+            const int ld = first[is_v] + i * NW;
+            if (ld >= 2 * D32) break;
+            const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds0 + slot + ld * 1024);
+            if (full && !a.far) {
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0), "v"(voff[is_v][i]), "s"(g) : "memory", "m0");
+                ++loads;  // (not so below, where no lane may take part: such a load is awaited with those after it)
+                continue;
+            }
+            int l = lane;
+            asm volatile("" : "+v"(l));  // nothing of this rare branch is kept in registers across the main loop
+            const int p = ld * 64 + l, r = p / B::CH;
+            if (unit * MHA8_UNIT + r < S) {
+                const uint8_t* gl = g + r * rs + ((p % B::CH) ^ (is_v ? B::vswz(r) : B::kswz(r))) * 16;
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0), "v"(gl) : "memory", "m0");
+            } else {  // rows beyond the sequence are zero
+                *(mha8_lds_v4i*)(uintptr_t)(m0 + l * 16) = (v4i){l >> 6, l >> 6, l >> 6, l >> 6};
+            }
+        }
+    };
 
     // ---- addends (mask in the base-2 domain, -infinity beyond the sequence), what kind of group they make, which units count
-    mha8_lds_f32* const add = (mha8_lds_f32*)(lds + B::RING);
+    mha8_lds_f32* const add = (mha8_lds_f32*)(lds + ring + MHA8_VSLOTS * U);
     const int add_keys = n * MHA8_UNIT < MHA8_LDS_KEYS ? n * MHA8_UNIT : MHA8_LDS_KEYS;
     // per unit: bits 0, 1: groups with a nonzero addend; bit 2: an addend that counts beside one of 0 or more; bit 3: one of those
     mha8_lds_u32* const kinds = (mha8_lds_u32*)(add + add_keys);
     const float floor = a.c1 > 0.0f ? -(2.0f * 16384.0f * D * a.c1 + 16.0f) : -INFINITY;
     // a scale that is not positive does not keep the order of the scores, a large one not the precision of the short form
     const bool near = a.c1 > 0.0f && 16384.0f * D * a.c1 <= MHA8_NEAR;
-    auto fill = [&](int first, int count) {  // keys first .. first + count - 1 (whole units, at most MHA8_LDS_KEYS)
-        const float* mrow = a.mask + (long long)b * S;
+    auto fill = [&](int from, int count, float (&t)[4]) {  // keys from .. from + count - 1 (whole units, at most MHA8_LDS_KEYS); t: their first
 #pragma unroll 1
-        for (int j0 = first + tid; j0 < first + count; j0 += 1024) {  // a wavefront has one unit at a time
-            float t[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) t[i] = a.mask && j0 + 256 * i < S ? base2_mask(mrow[j0 + 256 * i]) : 0.0f;
+        for (int f = from; f < from + count; f += 4 * threads) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int j = j0 + 256 * i;
-                if (j >= first + count) break;
-                const float v = j < S ? t[i] : -INFINITY;
+                const int j = f + tid + threads * i;  // a wavefront has one unit at a time
+                if (j >= from + count) break;
+                const float v = j < S ? base2_mask(t[i]) : -INFINITY;
                 add[j & (MHA8_LDS_KEYS - 1)] = v;
                 const uint64_t nz = __builtin_amdgcn_ballot_w64(v != 0.0f), on = __builtin_amdgcn_ballot_w64(!(v < floor));
                 const uint64_t top = __builtin_amdgcn_ballot_w64(v >= 0.0f);
                 if (lane == 0)
                     kinds[(j / MHA8_UNIT) & 63] = ((uint32_t)nz ? 1u : 0u) | ((uint32_t)(nz >> 32) ? 2u : 0u) | (on ? 4u : 0u) | (top ? 8u : 0u);
             }
+            if (f + 4 * threads < from + count) read_mask(f + 4 * threads, t);
         }
         __syncthreads();
     };
@@ -367,87 +438,64 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
     };
     auto next_unit = [&](int u) { return whole ? u + 1 + __builtin_ctzll((counts >> u) >> 1 | 1ull << 63) : u + 1; };  // (past the last: unused)
 
-    // ---- direct loads: 2 * D32 of 1 KiB for a unit's keys, as many for its values, dealt round the wavefronts.  Load m
-    // covers the pieces 64 m + lane of the unit's LDS image.
-    uint32_t voff[D32];  // byte offset of the lane's piece from the unit's first row; !a.far: it fits 32 bits
-#pragma unroll
-    for (int i = 0; i < D32; ++i) {
-        const int ld = i * 4 + wave;
-        const bool is_v = ld >= 2 * D32;
-        const int p = (ld - (is_v ? 2 * D32 : 0)) * 64 + lane, r = p / B::CH;
-        voff[i] = (uint32_t)r * (uint32_t)(is_v ? vss : kss) + ((p % B::CH) ^ (is_v ? B::vswz(r) : B::kswz(r))) * 16;
-    }
-    int lu = 0, li = 0;                // next unit to load, and its number in the order of use (0 .. 2 total - 1)
-    uint32_t lslot = 0;
-    int newest = 0;                    // the newest issue(): 1 keys of a whole unit, 2 keys and values of one, 0 anything else
-    auto issue = [&]() {
-        newest = 0;
-        if (li >= 2 * total) return;
-        const bool with_v = li >= total, full = (lu + 1) * MHA8_UNIT <= S;
-#pragma unroll
-        for (int i = 0; i < D32; ++i) {
-            const int ld = i * 4 + wave;
-            const bool is_v = ld >= 2 * D32;
-            if (is_v && !with_v) continue;
-            const long long rs = is_v ? vss : kss;
-            const uint8_t* g = (is_v ? vbase : kbase) + (long long)(lu * MHA8_UNIT) * rs;
-            const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds0 + (is_v ? MHA8_SLOTS * U + (ld - 2 * D32) * 1024 : ld * 1024) + lslot);
-            if (full && !a.far) {
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0), "v"(voff[i]), "s"(g) : "memory", "m0");
-                continue;
-            }
-            int l = lane;
-            asm volatile("" : "+v"(l));  // nothing of this rare branch is kept in registers across the main loop
-            const int p = (ld - (is_v ? 2 * D32 : 0)) * 64 + l, r = p / B::CH;
-            if (lu * MHA8_UNIT + r < S) {
-                const uint8_t* gl = g + r * rs + ((p % B::CH) ^ (is_v ? B::vswz(r) : B::kswz(r))) * 16;
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0), "v"(gl) : "memory", "m0");
-            } else {  // rows beyond the sequence are zero
-                *(mha8_lds_v4i*)(uintptr_t)(m0 + l * 16) = (v4i){l >> 6, l >> 6, l >> 6, l >> 6};
-            }
-        }
-        if (full) newest = with_v ? 2 : 1;
-        lslot = lslot == 2 * U ? 0 : lslot + U;
-        ++li;
-        lu = li == total ? first_unit : next_unit(lu);
+    // ---- the order of use: the keys of the units that count, and once more if they do not all stay in LDS, then (with the
+    // second round) the values.  Use j of the keys is in slot j mod key_slots, use j of the values in slot j mod MHA8_VSLOTS.
+    int ku = 0, kj = 0, kuses = 1 << 30, vu = 0, vj = 0;  // next to load, its number in the order, and how many there are
+    uint32_t kslot = 0, vslot = 0;
+    int kstamp = 0, vstamp = 0;  // lane j mod 64: `loads` behind use j
+    auto load_keys = [&]() {
+        if (kj >= kuses) return;
+        load(0, ku, kslot);
+        kstamp = lane == (kj & 63) ? loads : kstamp;
+        kslot = kslot + U == ring ? 0 : kslot + U;
+        ++kj;
+        ku = kj == total ? first_unit : next_unit(ku);
     };
-    // Before unit i is used: its loads were issued two steps ago; those of the step before may still be under way, D32 per
-    // wavefront with values, at least D32 / 2 without.
-    auto arrive = [&]() {
-        if (newest == 2) mha8_wait_and_meet<D32>();
-        else if (newest == 1) mha8_wait_and_meet<D32 / 2>();
-        else mha8_wait_and_meet<0>();
+    auto load_values = [&]() {
+        if (vj >= total) return;
+        load(1, vu, ring + vslot);
+        vstamp = lane == (vj & 63) ? loads : vstamp;
+        vslot = vslot == (MHA8_VSLOTS - 1) * U ? 0 : vslot + U;
+        ++vj;
+        vu = next_unit(vu);
     };
-    // Units 0 and 1, which hardly ever turn out not to count, while the mask is looked at; once more if they do not.
-    // (The code is kept short here and below, one copy of each part: small calls wait for instructions more than for data.)
-    for (bool known = !whole;; known = true) {
+    // The first half of the units, which hardly ever turn out not to count, while the mask is on its way; once more if they do not.
+    // (One copy of each part: small calls wait for instructions more than for data.)
+    const int half = n < 3 ? n : (n + 1) / 2, ahead = half < a.key_slots ? half : a.key_slots;
 #pragma unroll 1
-        for (int i = 0; i < 2; ++i) issue();
-        if (known) break;
-        if (!a.mask && near) {  // every unit counts, and only the last can have addends (read behind later barriers)
-            odd0 = S - (n - 1) * MHA8_UNIT < 32 ? 1ull << (n - 1) : 0;
-            odd1 = S % MHA8_UNIT ? 1ull << (n - 1) : 0;
-            if (S % MHA8_UNIT && tid < MHA8_UNIT) add[(n - 1) * MHA8_UNIT + tid] = (n - 1) * MHA8_UNIT + tid < S ? 0.0f : -INFINITY;
-            break;
-        }
-        fill(0, add_keys);
+    for (int i = 0; i < ahead; ++i) load_keys();
+
+#pragma unroll
+    for (int i = 0; i < D32; ++i) asm volatile("" : "+v"(qreg[i]));  // (awaited here, not behind all loads below)
+    if (!a.mask && near && whole) {  // every unit counts, and only the last can have addends (read behind later barriers)
+        odd0 = S - (n - 1) * MHA8_UNIT < 32 ? 1ull << (n - 1) : 0;
+        odd1 = S % MHA8_UNIT ? 1ull << (n - 1) : 0;
+        if (S % MHA8_UNIT && tid < MHA8_UNIT) add[(n - 1) * MHA8_UNIT + tid] = (n - 1) * MHA8_UNIT + tid < S ? 0.0f : -INFINITY;
+    } else if (whole) {
+        fill(0, add_keys, mfirst);
         read_kinds();
         total = __builtin_popcountll(counts);
         first_unit = __builtin_ctzll(counts);
-        if ((counts & 3) == (n > 1 ? 3u : 1u)) {
-            lu = total > 2 ? next_unit(1) : first_unit;  // as issue() would have left it
-            break;
+        if ((~counts & ((2ull << (ahead - 1)) - 1)) == 0) {
+            ku = next_unit(ahead - 1);  // as load_keys() would have left it
+        } else {
+            mha8_wait_and_meet(0);
+            ku = first_unit, kj = 0, kslot = 0;
         }
-        mha8_wait_and_meet<0>();
-        lu = first_unit, li = 0, lslot = 0;
+        vu = first_unit;
     }
+    const bool stay = total <= a.key_slots;  // one round of loads for the keys
+    kuses = stay ? total : 2 * total;
+    if (kj >= total) ku = first_unit;
+#pragma unroll 1
+    while (kj < (kuses < a.key_slots ? kuses : a.key_slots)) load_keys();
 
     // ---- operand addresses in the first slot
     const uint32_t kaddr = lds0 + col * D;  // + the piece's position
     const int ksw = B::kswz(col), tr = (lane & 15) >> 1;
     // row that this lane supplies to the transposing read: key 8 (tr / 4) + 4 h + tr % 4 of a group (+ 16 in the second read)
     const int vrow = 8 * (tr >> 2) + 4 * h + (tr & 3);
-    const uint32_t vaddr = lds0 + MHA8_SLOTS * U + vrow * D + (lane & 1) * 8;
+    const uint32_t vaddr = lds0 + ring + vrow * D + (lane & 1) * 8;
     const int vpiece = ((lane >> 4) & 1) ^ B::vswz(vrow);
     auto scores = [&](uint32_t slot, int g) {  // rows = keys 32 g .. 32 g + 31 of the unit, columns = queries
         v16i s;
@@ -460,10 +508,8 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
         }
         return s;
     };
-    auto read_addends = [&](int u, int g, v4f (&mk)[4]) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            mk[q] = *(const mha8_lds_v4f*)(add + ((u * MHA8_UNIT & (MHA8_LDS_KEYS - 1)) + g * 32 + 8 * q + 4 * h));
+    auto read_addends = [&](int u, int g, int q) {  // of the keys 8 q + 4 h .. + 3 of the group
+        return *(const mha8_lds_v4f*)(add + ((u * MHA8_UNIT & (MHA8_LDS_KEYS - 1)) + g * 32 + 8 * q + 4 * h));
     };
     auto odd = [&](int u, int g) { return (((g ? odd1 : odd0) >> (u & 63)) & 1) != 0; };
 
@@ -471,37 +517,45 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
     auto turn = [&](int u) {
         if (whole || u % (MHA8_LDS_KEYS / MHA8_UNIT) != 0) return;
         const int left = (n - u) * MHA8_UNIT;
-        fill(u * MHA8_UNIT, left < MHA8_LDS_KEYS ? left : MHA8_LDS_KEYS);
+        float t[4];
+        read_mask(u * MHA8_UNIT, t);
+        fill(u * MHA8_UNIT, left < MHA8_LDS_KEYS ? left : MHA8_LDS_KEYS, t);
         read_kinds();
     };
 
-    // ---- pass 1: the row maximum
+    // ---- pass 1: the row maximum.  Behind the barrier no wavefront reads the use before any more: its slot is loaded again.
     uint32_t slot = 0;
     int imax = -2147483647 - 1;
     float fmx = -INFINITY;
     int u = first_unit;
 #pragma unroll 1
     for (int i = 0; i < total; ++i) {
-        arrive();
-        issue();
+        mha8_wait_and_meet(loads - __builtin_amdgcn_readlane(kstamp, i & 63));
+        if (i) load_keys();
+        if (i < MHA8_VSLOTS) load_values();
         turn(u);
+        const uint32_t at_k = slot;
+        const int at = u;
+        slot = slot + U == ring ? 0 : slot + U;
+        u = next_unit(u);
+        if (idle) continue;
         v16i s[2];
 #pragma unroll
-        for (int g = 0; g < 2; ++g) s[g] = scores(slot, g);
+        for (int g = 0; g < 2; ++g) s[g] = scores(at_k, g);
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
-            if (!odd(u, g)) {
+            if (!odd(at, g)) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) imax = s[g][r] > imax ? s[g][r] : imax;
             } else {
-                v4f mk[4];
-                read_addends(u, g, mk);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) fmx = fmaxf(fmx, __builtin_fmaf((float)s[g][r], a.c1, mk[r >> 2][r & 3]));
+                for (int q = 0; q < 4; ++q) {
+                    const v4f mk = read_addends(at, g, q);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) fmx = fmaxf(fmx, __builtin_fmaf((float)s[g][4 * q + e], a.c1, mk[e]));
+                }
             }
         }
-        slot = slot == 2 * U ? 0 : slot + U;
-        u = next_unit(u);
     }
     if (imax != -2147483647 - 1) fmx = fmaxf(fmx, (float)imax * a.c1);
     const float row_max = fmaxf(fmx, other_half_f(fmx));  // finite: key 0 exists
@@ -515,79 +569,111 @@ template <int D32> __global__ __launch_bounds__(256, D32 == 4 ? 2 : 3) void ogc_
         for (int r = 0; r < 16; ++r) oacc[d][r] = 0;
     uint32_t row_sum = 0;  // this lane's keys only; the halves are added at the end
     u = first_unit;
+    if (stay) slot = 0;
+    uint32_t vat = 0;
 #pragma unroll 1
     for (int i = 0; i < total; ++i) {
-        arrive();
-        issue();
+        const int kst = stay ? 0 : __builtin_amdgcn_readlane(kstamp, (total + i) & 63), vst = __builtin_amdgcn_readlane(vstamp, i & 63);
+        mha8_wait_and_meet(loads - (kst > vst ? kst : vst));
+        load_keys();
+        if (i) load_values();
         turn(u);
-        v16i s[2];
+        const uint32_t at_k = slot, at_v = vat;
+        const int at = u;
+        slot = slot + U == ring ? 0 : slot + U;
+        vat = vat == (MHA8_VSLOTS - 1) * U ? 0 : vat + U;
+        u = next_unit(u);
+        if (idle) continue;
+        auto numerators = [&](int g, const v16i& s, auto with_mask_c) {
+            constexpr int AT_ONCE = D32 == 4 ? 4 : D32 == 2 ? 1 : 2;  // quads of addends read together: as the registers allow
+            v4i w4;
+            v4f mk[AT_ONCE];
 #pragma unroll
-        for (int g = 0; g < 2; ++g) s[g] = scores(slot, g);
+            for (int q = 0; q < 4; ++q) {
+                uint32_t w = 0;
+                if constexpr (decltype(with_mask_c)::value) {
+                    if (q % AT_ONCE == 0)
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            v4i vf[D32];
+                        for (int x = 0; x < AT_ONCE; ++x) mk[x] = read_addends(at, g, q + x);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float x;  // in [0, 127]; a key past the end: 0
+                    if constexpr (decltype(with_mask_c)::value)
+                        x = __builtin_amdgcn_exp2f(__builtin_fmaf((float)s[4 * q + e], a.c1, mk[q % AT_ONCE][e]) - row_max) * 127.0f;
+                    else
+                        x = __builtin_amdgcn_exp2f(__builtin_fmaf((float)s[4 * q + e], a.c1, k0));
+                    w = __builtin_amdgcn_cvt_pk_u8_f32(x, e, w);  // round to nearest even
+                }
+                w4[q] = (int)w;
+                if constexpr (decltype(with_mask_c)::value && AT_ONCE < 4) __builtin_amdgcn_sched_barrier(0);
+                row_sum = __builtin_amdgcn_sad_u8(w, 0u, row_sum);  // + the four bytes
+            }
+            return w4;
+        };
+        auto second = [&](int g, const v4i& pw) {
 #pragma unroll
             for (int d = 0; d < D32; ++d) {
-                const uint32_t at = vaddr + slot + g * 32 * D + (((2 * d) ^ vpiece) * 16);
-                const v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((mha8_lds_v2i*)(uintptr_t)at);
-                const v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((mha8_lds_v2i*)(uintptr_t)(at + 16 * D));
-                vf[d] = (v4i){lo[0], lo[1], hi[0], hi[1]};
+                const uint32_t from = vaddr + at_v + g * 32 * D + (((2 * d) ^ vpiece) * 16);
+                const v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((mha8_lds_v2i*)(uintptr_t)from);
+                const v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((mha8_lds_v2i*)(uintptr_t)(from + 16 * D));
+                oacc[d] = __builtin_amdgcn_mfma_i32_32x32x32_i8((v4i){lo[0], lo[1], hi[0], hi[1]}, pw, oacc[d], 0, 0, 0);
             }
-            uint32_t dw[4];
-            auto numerators = [&](auto with_mask_c) {
-                v4f mk[4];
-                if constexpr (decltype(with_mask_c)::value) read_addends(u, g, mk);
+        };
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    uint32_t w = 0;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        float x;  // in [0, 127]; a key past the end: 0
-                        if constexpr (decltype(with_mask_c)::value)
-                            x = __builtin_amdgcn_exp2f(__builtin_fmaf((float)s[g][4 * q + e], a.c1, mk[q][e]) - row_max) * 127.0f;
-                        else
-                            x = __builtin_amdgcn_exp2f(__builtin_fmaf((float)s[g][4 * q + e], a.c1, k0));
-                        w = __builtin_amdgcn_cvt_pk_u8_f32(x, e, w);  // round to nearest even
-                    }
-                    dw[q] = w;
-                    row_sum = __builtin_amdgcn_sad_u8(w, 0u, row_sum);  // + the four bytes
-                }
-            };
-            if (!odd(u, g)) numerators(std::integral_constant<bool, false>{});
-            else numerators(std::integral_constant<bool, true>{});
-            const v4i pw = {(int)dw[0], (int)dw[1], (int)dw[2], (int)dw[3]};
-#pragma unroll
-            for (int d = 0; d < D32; ++d) oacc[d] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[d], pw, oacc[d], 0, 0, 0);
+        for (int g = 0; g < 2; ++g) {
+            const v16i s = scores(at_k, g);
+            v4i pw;
+            if (!odd(at, g)) pw = numerators(g, s, std::integral_constant<bool, false>{});
+            else pw = numerators(g, s, std::integral_constant<bool, true>{});
+            second(g, pw);
         }
-        slot = slot == 2 * U ? 0 : slot + U;
-        u = next_unit(u);
     }
+    if (idle) return;
 
-    // ---- normalise, requantize, store: after the half exchange a lane holds 16 consecutive channels of its query
+    // ---- normalise, requantize, store: after the half exchange a lane holds 16 consecutive channels of its query.
+    // float(A) / float(L) by the reciprocal: y = 1 / L rounded once, q = A y, q + (A - q L) y, the last two fused.  With L
+    // below 2^22 this is the quotient rounded once, the division's own result: q is within 1.5 units in the last place, so the
+    // remainder is exact and the sum before its rounding within 1.5 * 2^-24 units of A / L, which for such L is at least
+    // 2 * 2^-24 units away from any midpoint of two fp32 values.  As a division, 64 of them a lane, it was half of the vector
+    // ALU's work at 384 tokens.
     const int sum = (int)row_sum + other_half_i((int)row_sum);
-    const float lf = (float)sum;
+    const float lf = (float)sum, y = 1.0f / lf;
     uint8_t* op = a.o + b * a.so[0] + hd * a.so[1] + (long long)query * a.so[2];
+    auto finish = [&](auto quotient) {
 #pragma unroll
-    for (int d = 0; d < D32; ++d) {
-        uint32_t dw[4];
+        for (int d = 0; d < D32; ++d) {
+            uint32_t dw[4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            uint32_t w = 0;
+            for (int g = 0; g < 4; ++g) {
+                uint32_t w[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float tt = ((float)oacc[d][4 * g + e] / lf) * a.r;
-                const int qi = (int)__builtin_rintf(fminf(fmaxf(tt, -128.0f), 127.0f));
-                w |= ((uint32_t)qi & 0xffu) << (8 * e);
+                for (int e = 0; e < 4; ++e) {
+                    const float tt = quotient((float)oacc[d][4 * g + e]) * a.r;
+                    // + 1.5 * 2^23 rounds to an integer, to even at ties, whose low byte is that of the sum's bits
+                    w[e] = __builtin_bit_cast(uint32_t, fminf(fmaxf(tt, -128.0f), 127.0f) + 12582912.0f);
+                }
+                dw[g] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(w[3], w[2], 0x0c0c0400u), __builtin_amdgcn_perm(w[1], w[0], 0x0c0c0400u), 0x05040100u);
             }
-            dw[g] = w;
+            swap32_i8(dw[0], dw[2]);
+            swap32_i8(dw[1], dw[3]);
+            if (query < S) *(v4i*)(op + d * 32 + 16 * h) = (v4i){(int)dw[0], (int)dw[2], (int)dw[1], (int)dw[3]};
         }
-        swap32_i8(dw[0], dw[2]);
-        swap32_i8(dw[1], dw[3]);
-        if (query < S) *(v4i*)(op + d * 32 + 16 * h) = (v4i){(int)dw[0], (int)dw[2], (int)dw[1], (int)dw[3]};
+    };
+    if (S <= 32768) {
+        finish([&](float x) {
+            const float q = x * y;
+            return __builtin_fmaf(__builtin_fmaf(-q, lf, x), y, q);
+        });
+    } else {
+        finish([&](float x) { return x / lf; });
     }
 }
 
 namespace {
+
+// A number below 2^32 / v times this, shifted right by 32, is it divided by v (0: divide).
+uint32_t magic_i8(uint64_t m, uint64_t v) { return v == 1 || m * v >= 1ull << 32 ? 0u : (uint32_t)((1ull << 32) / v + 1); }
 
 bool stride_ok_i8(const int64_t s[3]) {
     for (int i = 0; i < 3; ++i)
@@ -595,30 +681,49 @@ bool stride_ok_i8(const int64_t s[3]) {
     return true;
 }
 
-// The ring, the addends, the units' kinds: at most 66 KiB (head_dim 128, 4096 keys and more).
-template <int D32> void launch_i8(const MhaI8Args& a, bool stream, dim3 grid, hipStream_t s) {
-    if (!stream) {
-        hipLaunchKernelGGL((ogc_mha_i8_kernel<D32>), grid, dim3(256), 0, s, a);
-        return;
+constexpr size_t MHA8_CU_LDS = 160 * 1024;
+
+// Bytes of LDS beside the keys' slots: the values' slots, the addends, the units' kinds.
+template <int D32> size_t side_lds(int seq) {
+    const int keys = (seq + MHA8_UNIT - 1) / MHA8_UNIT * MHA8_UNIT;
+    return MHA8_VSLOTS * Mha8<D32>::UNIT_BYTES + (size_t)(keys < MHA8_LDS_KEYS ? keys : MHA8_LDS_KEYS) * 4 + 64 * 4;
+}
+
+template <int D32> void launch_i8(MhaI8Args& a, bool stream, unsigned tiles, hipStream_t s) {
+    if constexpr (D32 <= 2) {
+        if (!stream) {
+            hipLaunchKernelGGL((ogc_mha_i8_kernel<D32>), dim3(tiles), dim3(256), 0, s, a);
+            return;
+        }
     }
-    const int keys = (a.seq + MHA8_UNIT - 1) / MHA8_UNIT * MHA8_UNIT;
-    const size_t lds = Mha8<D32>::RING + (size_t)(keys < MHA8_LDS_KEYS ? keys : MHA8_LDS_KEYS) * 4 + 64 * 4;
-    if (lds > 65536) {  // said at every such launch: the limit belongs to the current device
-        if (hipFuncSetAttribute((const void*)ogc_mha_i8_stream_kernel<D32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    // As many slots for keys, up to all units (60: their stamps are lanes), as leave the LDS of a compute unit to the
+    // workgroups that its registers hold, or to those that it gets if the launch has fewer; three at least.
+    const int units = (a.seq + MHA8_UNIT - 1) / MHA8_UNIT, all = units < 60 ? units : 60;
+    const size_t side = side_lds<D32>(a.seq);
+    unsigned each = (tiles + 255) / 256;
+    if (each > (unsigned)Mha8<D32>::RESIDENT) each = Mha8<D32>::RESIDENT;
+    auto fit = [&]() { return (int)(((long long)(MHA8_CU_LDS / each) - (long long)side) / Mha8<D32>::UNIT_BYTES); };
+    while (each > 1 && fit() < (all < 3 ? all : 3)) --each;
+    a.key_slots = fit() < all ? fit() : all;
+    const size_t lds = (size_t)a.key_slots * Mha8<D32>::UNIT_BYTES + side;
+    if (lds > 65536) {  // said at every such launch (the limit belongs to the current device), the same for all: threads do not disturb each other
+        if (hipFuncSetAttribute((const void*)ogc_mha_i8_stream_kernel<D32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MHA8_CU_LDS) != hipSuccess)
             return;  // reported by the caller
     }
-    hipLaunchKernelGGL((ogc_mha_i8_stream_kernel<D32>), grid, dim3(256), lds, s, a);
+    hipLaunchKernelGGL((ogc_mha_i8_stream_kernel<D32>), dim3(tiles), dim3(256), lds, s, a);
 }
 
 // The streaming kernel or the plain one.  The former does less per score and starts slower (three times the code, the
-// mask looked at before the first score), about 2 us on a launch that does not fill the chip.  Measured both ways, plain /
-// streaming, us, batch x heads x seq, padding mask:
-//   d = 64:  1x16x64 5.3 / 6.8;  64x12x64 8.9 / 9.6;  256x12x64 26.5 / 25.7;  32x12x128 9.2 / 9.9;  128x12x128 22.9 / 21.0;
-//            8x8x256 9.6 / 10.2;  32x12x197 18.5 / 15.1;  1x8x384 12.0 / 10.0;  8x8x384 12.6 / 12.5;  128x16x512 241 / 171
-//   d = 128: 8x12x64 7.8 / 8.3;  1x16x128 10.2 / 9.8;  32x12x128 15.5 / 14.2;  8x8x384 21.4 / 17.4;  128x8x384 167 / 105
+// mask looked at before the first score), half a microsecond on a launch that does not fill the chip; with 96 and 128 channels the
+// plain one's values, byte by byte into LDS, cost more than that in every launch.  Measured both ways, plain / streaming, us,
+// batch x heads x seq, padding mask:
+//   d = 32:  16x16x100 6.8 / 7.3;  8x8x256 9.2 / 9.4;  32x12x128 8.7 / 8.2;  128x16x60 16.1 / 12.1;  8x4x300 10.6 / 10.3;  4x8x700 19.9 / 17.3
+//   d = 64:  1x16x64 4.9 / 5.5;  32x8x48 5.5 / 6.1;  16x16x100 7.3 / 7.9;  8x8x256 9.8 / 10.2;  8x16x200 10.1 / 9.7;  32x12x128 10.6 / 9.8;
+//            64x12x64 10.1 / 8.0;  16x16x256 15.4 / 13.5;  1x4x300 10.7 / 9.8;  1x8x384 12.3 / 12.0;  8x8x384 12.8 / 13.2
+//   d = 96:  4x4x64 6.3 / 6.2;  1x4x100 7.9 / 7.5;  64x8x100 15.6 / 12.1;   d = 128:  1x4x48 7.0 / 6.6;  1x8x100 10.1 / 8.4;  8x8x384 22.8 / 16.8
 bool stream_case(const ogc_mha_desc* d) {
     const int64_t tiles = (int64_t)d->batch * d->heads * ((d->seq + 127) / 128);
-    return d->seq >= (d->head_dim >= 96 ? 128 : 320) || tiles * d->seq >= 128 * 1024;
+    return d->head_dim >= 96 || d->seq >= 320 || tiles * d->seq >= 40 * 1024;
 }
 
 }  // namespace
@@ -668,19 +773,19 @@ ogc_status ogc_mha_run_i8(const ogc_mha_desc* d, const ogc_mha_quant* qp, const 
     a.q_tiles = (d->seq + 127) / 128;
     const int bh = d->batch * d->heads;
     a.xcd_order = (bh % 8 == 0) ? 1 : 0;
-    auto magic = [](uint64_t m, uint64_t v) { return v == 1 || m * v >= 1ull << 32 ? 0u : (uint32_t)((1ull << 32) / v + 1); };  // exact there
-    a.tiles_magic = magic((uint64_t)bh * a.q_tiles, a.q_tiles);
-    a.heads_magic = magic(bh, d->heads);
+    a.key_slots = 0;
+    a.tiles_magic = magic_i8((uint64_t)bh * a.q_tiles, a.q_tiles);
+    a.heads_magic = magic_i8(bh, d->heads);
     a.far = a.sk[2] > (1ll << 31) / MHA8_UNIT || a.sv[2] > (1ll << 31) / MHA8_UNIT;
     a.c1 = ((qp->q_scale * qp->k_scale) * d->scale) * 1.44269504088896340736f;  // fp32 products, left to right
     a.r = qp->v_scale / qp->o_scale;                                             // one fp32 division
-    const dim3 grid((unsigned)(bh * a.q_tiles));
+    const unsigned tiles = (unsigned)(bh * a.q_tiles);
     hipStream_t s = (hipStream_t)stream;
     switch (d->head_dim / 32) {
-    case 1: launch_i8<1>(a, stream_case(d), grid, s); break;
-    case 2: launch_i8<2>(a, stream_case(d), grid, s); break;
-    case 3: launch_i8<3>(a, stream_case(d), grid, s); break;
-    default: launch_i8<4>(a, stream_case(d), grid, s); break;
+    case 1: launch_i8<1>(a, stream_case(d), tiles, s); break;
+    case 2: launch_i8<2>(a, stream_case(d), tiles, s); break;
+    case 3: launch_i8<3>(a, stream_case(d), tiles, s); break;
+    default: launch_i8<4>(a, stream_case(d), tiles, s); break;
     }
     return hipGetLastError() == hipSuccess ? OGC_OK : OGC_ERR_DEVICE;
 }
@@ -698,8 +803,6 @@ const char* ogc_mha_i8_kernel_name(const ogc_mha_desc* d) {
     switch (d->head_dim) {
     case 32: return "ogc_mha_i8_kernel<1>";
     case 64: return "ogc_mha_i8_kernel<2>";
-    case 96: return "ogc_mha_i8_kernel<3>";
-    case 128: return "ogc_mha_i8_kernel<4>";
     }
     return nullptr;
 }

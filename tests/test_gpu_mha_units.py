@@ -266,6 +266,54 @@ def test_i8_units_that_do_not_count(oracle_mod, head_dim):
     check_i8(oracle_mod, wl)
 
 
+@pytest.mark.parametrize("head_dim", [96, 128])
+def test_i8_short_sequences_of_wide_heads(oracle_mod, head_dim):
+    """One unit or part of one: heads of 96 and 128 channels stream at every length."""
+    for seq in (1, 2, 31, 32, 33, 63, 64, 65, 127):
+        wl = i8_case(3, seq, head_dim, 8200 + seq + head_dim, "i8 short S=%d d=%d" % (seq, head_dim))
+        check_i8(oracle_mod, wl)
+        check_i8(oracle_mod, wl, use_mask=False)
+
+
+@pytest.mark.parametrize("head_dim, batch, seq", [(32, 96, 1000), (64, 80, 1000), (96, 64, 1000), (128, 48, 1000), (128, 48, 384), (96, 2, 4096)])
+def test_i8_slots_of_keys(oracle_mod, head_dim, batch, seq):
+    """Launches that fill the chip hold some units of keys in LDS and load the others again for the second pass; what counts of a
+    masked entry may fit whole.  Entries without padding, masked in the first half (loaded before the mask is known) and
+    in between, to a few units, and to one key."""
+    wl = i8_case(batch, seq, head_dim, 8400 + head_dim, "i8 slots d=%d" % head_dim)
+    wl.mask[:] = 0.0
+    cuts = [(0, 0), (0, seq // 2), (70, 300), (130, seq), (1, seq)]
+    for e in range(batch):
+        wl.mask[e, cuts[e % 5][0]:cuts[e % 5][1]] = -10000.0
+    from paper_2301_01333_amd.harness import DeviceMHA
+
+    entries = sorted({e for e in (0, 1, 2, 3, 4, batch - 1) if e < batch})
+    for use_mask in (True, False):
+        dev = DeviceMHA(wl, STABLE, use_mask)
+        dev.run()
+        got = dev.result().astype(np.int32)
+        for e in entries if seq < 2000 else entries[1:]:
+            q, k, v = (heads_view(t, wl)[e:e + 1] for t in (wl.q, wl.k, wl.v))
+            ref = oracle_mod.attention_i8(q, k, v, wl.mask[e:e + 1] if use_mask else None, wl.scale, *wl.quant).transpose(0, 2, 1, 3)
+            diff = np.abs(got[e] - ref.reshape(got[e].shape).astype(np.int32))
+            assert diff.max() <= 1 and (diff > 0).mean() < 0.01, "entry %d: %d steps, %.3f %%" % (e, diff.max(), 100.0 * (diff > 0).mean())
+
+
+def test_i8_quotient_beyond_the_reciprocal():
+    """Row sums beyond 2^22 are divided by, not multiplied by the reciprocal: 33000 keys that all weigh 127."""
+    from paper_2301_01333_amd.harness import DeviceMHA
+
+    wl = synth.make_mha("i8", 1, 33000, 32, 1, 8450, name="i8 33000 keys")
+    wl.q = np.zeros_like(wl.q)
+    vs, os = np.float32(wl.quant[2]), np.float32(wl.quant[3])
+    dev = DeviceMHA(wl, STABLE, False)
+    dev.run()
+    got = dev.result().reshape(33000, 32).astype(np.int32)
+    a = 127 * wl.v.reshape(33000, 32).astype(np.int64).sum(0)
+    r = (a.astype(np.float32) / np.float32(127 * 33000)) * (vs / os)
+    assert (got == np.clip(np.rint(r), -128, 127).astype(np.int32)[None]).all()
+
+
 def i8_in_fp32(wl, use_mask=True):
     """The definition with its scores in fp32 and base 2, as every implementation here forms them: product, mask and maximum each
     rounded once.  Against float64 scores this matters where a row's largest addend is so low that fp32 spaces the scores."""

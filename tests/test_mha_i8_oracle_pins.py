@@ -149,3 +149,30 @@ def test_invariants(oracle_mod):
     got = o.astype(np.float64) * np.float64(np.float32(0.05))
     # half an output step, plus values up to 100 * 0.05 = 5 times the summed error of S weights, each within 1/127
     assert np.abs(got - ref).max() <= 0.05 * 0.5 + 5.0 * s_ * (1.0 / 127)
+
+
+def test_quotient_by_reciprocal_is_the_division():
+    """The streaming kernel's A / L: y = 1 / L rounded once, q = A y, q + (A - q L) y with fused operations.  For every L below 2^22 it is
+    the division's own result; here random pairs, small ones exhaustively, and quotients next to midpoints of two fp32 values."""
+    rng = np.random.default_rng(5700)
+    f = np.float32
+
+    def fused(x, y, z):
+        return (x.astype(np.longdouble) * y.astype(np.longdouble) + z.astype(np.longdouble)).astype(f)  # 64 bits hold the sums here
+
+    def check(a, l):
+        a, l = a.astype(f), l.astype(f)
+        y = f(1.0) / l
+        q = a * y
+        assert np.array_equal(fused(fused(-q, l, a), y, q), a / l)
+
+    small = np.arange(1, 700)
+    check(np.repeat(np.arange(-700, 700), small.size), np.tile(small, 1400))
+    for top in (1 << 10, 1 << 16, 1 << 22):
+        l = rng.integers(1, top, 500000)
+        check(rng.integers(-127 * 128 * 32768, 127 * 128 * 32768, l.size), l)
+        # A nearest to (a midpoint) * L: the quotient is as near to the midpoint as an integer A allows
+        q = rng.integers(1 << 23, 1 << 24, l.size)
+        e = rng.integers(0, 20, l.size)
+        a = np.rint((q.astype(np.longdouble) + 0.5) * l / (2.0 ** 23) * 2.0 ** (e - 12).astype(np.longdouble)).astype(np.int64)
+        check(a, l)
