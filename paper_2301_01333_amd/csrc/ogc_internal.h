@@ -77,6 +77,10 @@ struct OgcChainArgs {
     OgcLayerArgs layer[OGC_MAX_LAYERS];
 };
 
+struct OgcStreamArgs : OgcChainArgs {  // the fused kernel whose loads run on across blocks and layers
+    int32_t lds_params[OGC_MAX_LAYERS];  // byte of LDS where a layer's parameters begin; 0: they stay in global memory
+};
+
 #define OGC_CLOCK_WORDS_PER_LAUNCH 2048  // ogc_mlp_run_clocked: 64-bit words per launch (at most 512 workgroups x 4)
 #define OGC_STATIC_SCRATCH_BYTES (8u << 20)  // the library's own workspace for ogc_mlp_run_static, per GPU
 

@@ -532,7 +532,8 @@ OGC_DEV void epilogue_block(const typename AccT<DT>::type& acc, const OgcLayerAr
 // Loads one 16-byte chunk (row m, bytes kb..kb+15 of the row) of the caller's plain x, zero-filling
 // everything outside [0,M) x [0,K*elt) (pre-op reorder from the plain layout, Section IV, anchor #4).
 // u8 inputs are converted to the internal s8 form on the way.
-template <int DT> OGC_DEV v4i load_plain_chunk(const OgcLayerArgs& a, int m, int kb) {
+// FLAT: dwords of unaligned rows by flat loads (otherwise global ones, which the compiler's counts keep apart from LDS accesses).
+template <int DT, bool FLAT = true> OGC_DEV v4i load_plain_chunk(const OgcLayerArgs& a, int m, int kb) {
     const int kbytes = a.K * Elt<DT>::size;
     v4i v = {0, 0, 0, 0};
     if (m < a.M && kb < kbytes) {
@@ -546,7 +547,8 @@ template <int DT> OGC_DEV v4i load_plain_chunk(const OgcLayerArgs& a, int m, int
             const int n = kbytes - kb < 16 ? kbytes - kb : 16;
             const uintptr_t addr = (uintptr_t)p;
             const uint32_t sh = (uint32_t)(addr & 3);
-            const uint32_t* q = (const uint32_t*)(addr - sh);
+            typedef const __attribute__((address_space(1))) uint32_t* global_u32;
+            const std::conditional_t<FLAT, const uint32_t*, global_u32> q = (std::conditional_t<FLAT, const uint32_t*, global_u32>)(addr - sh);
             const int count = (int)(sh + n + 3) >> 2;
             uint32_t w[5];
 #pragma unroll
@@ -870,9 +872,218 @@ template <int DT, int DEEP> OGC_DEV void fused_chain(const OgcChainArgs& c, uint
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The fused chain's stream, for chains of a megabyte of weights and more (launch_fused_t).  One workgroup on a CU reads every weight
+// once, at 59 bytes a clock at best when all 256 CUs ask (64 alone); that, and the power of moving a gigabyte to the CUs, bounds
+// it.  So the loads never stop, and a wave's loads are consecutive: it takes one channel block at a time (a task) with
+// OGC_STREAM_STEPS k-steps in flight (two blocks step by step, as in fused_blocks: 74 instead of 134 GB/s a CU with nothing else to
+// do), and with a task's last steps a step's registers are loaded with the NEXT task's first, also where that belongs to the next
+// layer: weights wait for no activations, and epilogue, barrier and the next task's start run under their loads.  The channels'
+// parameters come from LDS: loads return in order, and one behind the weights would wait for all of them.
+// Measured, us, fused_blocks / this: int8 479-1024-1024-512-256-1 at batch 256 33.4 / 29.0, at 8191 36.5 / 32.6; four 1024-wide layers
+// at 8192 int8 59.4 / 52.8, E4M3 60.2 / 49.3; bf16 479-1024-1024-512-256-1 at 8192 57.0 / 52.2, 512 x 2 at 300 15.5 / 13.8.  Without matrix
+// instructions a 1024-wide int8 layer takes 10.0 us for 12.1 on all CUs, 9.0 for 9.6 on one: the clock gives way.  Tried: two blocks a
+// task (57 / 54, E4M3 59 / 51, but bf16 57 / 55); activations read a group of steps ahead, short tasks' weights too (registers
+// in scratch memory, 57 -> 76).
+// ------------------------------------------------------------------------------------------------
+#define OGC_STREAM_STEPS 8
+typedef __attribute__((address_space(3))) v4i ogc_lds_v4i;
+typedef __attribute__((address_space(3))) v4f ogc_lds_v4f;
+
+struct LdsY {  // a result that goes to LDS (see GlobalY)
+    ogc_lds_u8* p;
+    __device__ __forceinline__ LdsY operator+(size_t o) const { return LdsY{p + (uint32_t)o}; }
+};
+OGC_DEV void store16(LdsY y, const v4i& v) { *(ogc_lds_v4i*)y.p = v; }
+
+struct StreamTask {  // uniform over the wave
+    const uint8_t* w;   // weights of channel block nb
+    int steps;          // 32-byte k-steps (0: no task)
+    int layer, nb;
+};
+OGC_DEV int stream_blocks(const OgcChainArgs& c, int l) { return l + 1 == c.n_layers ? (c.layer[l].N + 31) >> 5 : c.layer[l].NB_out; }
+// the first task of this wave at block nb of layer l or behind
+OGC_DEV StreamTask stream_task(const OgcChainArgs& c, int l, int nb, int wave) {
+    StreamTask t = {nullptr, 0, 0, 0};
+    for (; l < c.n_layers; ++l, nb = wave) {
+        const int nblocks = stream_blocks(c, l);
+        if (nb >= nblocks) continue;
+        t.w = c.layer[l].w + (size_t)nb * c.layer[l].KC * 512;
+        t.steps = c.layer[l].KC >> 1;
+        t.layer = l;
+        t.nb = nb;
+        break;
+    }
+    return t;
+}
+
+template <int DT> OGC_DEV void fused_stream(const OgcStreamArgs& c, uint8_t* smem) {
+    constexpr int G = OGC_STREAM_STEPS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Workgroup b runs on XCD b%8.  A small batch is kept on few XCDs so that their L2s fetch the weights once
+    // for all of their workgroups; the workgroups dealt to the other XCDs leave at once.
+    const int xcd = blockIdx.x & 7;
+    const int tile = (blockIdx.x >> 3) * c.fused_xcds + xcd;
+    if (xcd >= c.fused_xcds || tile >= c.fused_tiles) return;
+    const int m0 = tile * 32;
+    ogc_lds_u8* const lds = (ogc_lds_u8*)smem;
+
+    const uint32_t at = lane * 16;
+    auto weights = [&](const uint8_t* base, uint32_t off) { return *(const v4i*)(base + off + at); };
+    v4i w[G];
+    StreamTask task = stream_task(c, 0, wave, wave);
+    auto first_steps = [&](const StreamTask& t) {  // of a task that has as many, in ascending order: the compiler's waits count on it
+#pragma unroll
+        for (int u = 0; u < G; ++u) w[u] = weights(t.w, u * 1024);
+    };
+    // Stage the plain input tile into LDS in operand layout (pre-op reorder fused at the chain entry): four lanes take 64
+    // consecutive bytes of a row, and a thread has up to four pieces on their way.  Before it the first weights, and the channels'
+    // parameters straight into LDS: scale and bias, or the bias alone, of a layer by one wave.
+    if (task.steps >= G) first_steps(task);
+    {
+        const OgcLayerArgs& a = c.layer[0];
+        const int pieces = a.KC * 32;
+        for (int l = wave; l < c.n_layers; l += OGC_FUSED_WAVES) {
+            const uint32_t bytes = stream_blocks(c, l) * 128, to0 = c.lds_params[l];
+            if (to0 == 0) break;
+            for (int which = Quant<DT>::yes ? 0 : 1; which < 2; ++which) {
+                const float* const from = which ? c.layer[l].bias : c.layer[l].scale;
+                for (uint32_t o = 0; o < bytes; o += 1024) {
+                    const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds + to0 + (Quant<DT>::yes && which ? bytes : 0) + o);
+                    if (o + at < bytes) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(o + at), "s"(from) : "memory", "m0");
+                }
+            }
+        }
+        auto row = [](int p) { return (p >> 2) & 31; };
+        auto chunk = [](int p) { return (p >> 7) * 4 + (p & 3); };
+        for (int p0 = tid; p0 < pieces; p0 += 4 * OGC_FUSED_THREADS) {
+            v4i v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int p = p0 + j * OGC_FUSED_THREADS;
+                if (p < pieces) v[j] = load_plain_chunk<DT, false>(a, m0 + row(p), chunk(p) * 16);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int p = p0 + j * OGC_FUSED_THREADS;
+                if (p < pieces) *(ogc_lds_v4i*)(lds + (chunk(p) * 32 + row(p)) * 16) = v[j];
+            }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+    for (int l = 0; l < c.n_layers; ++l) {
+        const OgcLayerArgs& a = c.layer[l];
+        const bool last = l + 1 == c.n_layers;
+        ogc_lds_u8* const xin = lds + (l & 1 ? c.lds_buf_bytes : 0);
+        ogc_lds_u8* const xout = lds + (l & 1 ? 0 : c.lds_buf_bytes);
+        const ogc_lds_u8* const params = lds + c.lds_params[l];
+        const bool in_lds = c.lds_params[l] != 0;
+        const uint32_t pbytes = Quant<DT>::yes ? stream_blocks(c, l) * 128 : 0;  // of the scales, before the biases
+        const ogc_lds_u8* const xp = xin + at;
+        while (task.steps && task.layer == l) {
+            const StreamTask next = stream_task(c, l, task.nb + OGC_FUSED_WAVES, wave);
+            typename AccT<DT>::type acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0;
+            const int full = task.steps / G, rest = task.steps % G;  // (an even number)
+            v4i xf[G];
+            auto read_x = [&](int u, int s) { xf[u] = *(const ogc_lds_v4i*)(xp + s * 1024); };
+            auto multiply = [&](int u) {  // steps u and u + 1 of the group
+                if constexpr (DT == OGC_F8) mma64(acc, w[u], w[u + 1], xf[u], xf[u + 1]);
+                else {
+                    mma32<DT>(acc, w[u], xf[u]);
+                    mma32<DT>(acc, w[u + 1], xf[u + 1]);
+                }
+            };
+            const bool more = next.steps >= G;
+            for (int g = 0; g + 1 < full; ++g) {
+#pragma unroll
+                for (int u = 0; u < G; ++u) read_x(u, g * G + u);
+#pragma unroll
+                for (int u = 0; u < G; u += 2) {
+                    multiply(u);
+                    w[u] = weights(task.w, ((g + 1) * G + u) * 1024);
+                    w[u + 1] = weights(task.w, ((g + 1) * G + u + 1) * 1024);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if (rest == 0 && more) {
+#pragma unroll
+                for (int u = 0; u < G; ++u) read_x(u, (full - 1) * G + u);
+#pragma unroll
+                for (int u = 0; u < G; u += 2) {
+                    multiply(u);
+                    w[u] = weights(next.w, u * 1024);
+                    w[u + 1] = weights(next.w, (u + 1) * 1024);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                if (full > 0) {
+#pragma unroll
+                    for (int u = 0; u < G; ++u) read_x(u, (full - 1) * G + u);
+#pragma unroll
+                    for (int u = 0; u < G; u += 2) multiply(u);
+                }
+#pragma unroll
+                for (int u = 0; u < G - 2; u += 2) {  // a few steps more, or a short task
+                    if (u < rest) {
+                        w[u] = weights(task.w, (full * G + u) * 1024);
+                        w[u + 1] = weights(task.w, (full * G + u + 1) * 1024);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < G - 2; u += 2) {
+                    if (u < rest) {
+                        read_x(u, full * G + u);
+                        read_x(u + 1, full * G + u + 1);
+                        multiply(u);
+                    }
+                }
+                if (more) first_steps(next);
+            }
+            const int n0 = task.nb * 32;
+            if constexpr (DT == OGC_I8) {
+                if (a.has_comp) {  // the compensation goes to the sums at once: no registers for it below
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const v4i comp = *(const v4i*)(a.ncomp + n0 + 8 * g + 4 * (lane >> 5));
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[4 * g + e] += comp[e];
+                    }
+                }
+            }
+            BlockParams p;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int n = n0 + 8 * g + 4 * (lane >> 5);
+                p.s[g] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+                p.c[g] = (v4i){0, 0, 0, 0};
+                if (in_lds) {
+                    if constexpr (Quant<DT>::yes) p.s[g] = *(const ogc_lds_v4f*)(params + n * 4);
+                    p.b[g] = *(const ogc_lds_v4f*)(params + pbytes + n * 4);
+                } else {
+                    if constexpr (Quant<DT>::yes) p.s[g] = *(const v4f*)(a.scale + n);
+                    p.b[g] = *(const v4f*)(a.bias + n);
+                }
+            }
+            if (last) epilogue_block<DT, 1>(acc, a, p, n0, m0, lane, (uint8_t*)nullptr);
+            else if (DT == OGC_F8 && a.act == OGC_ACT_RELU) epilogue_block<DT, 0, true, DT == OGC_F8 ? 1 : -1>(acc, a, p, n0, m0, lane, LdsY{xout});
+            else epilogue_block<DT, 0>(acc, a, p, n0, m0, lane, LdsY{xout});
+            task = next;
+        }
+        if (!last) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // (the weights' loads go on)
+    }
+}
+
 template <int DT> __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_fused_chain_kernel(const OgcChainArgs c) {
     extern __shared__ __align__(16) uint8_t smem[];
     fused_chain<DT, 8>(c, smem);
+}
+// The same for chains that take the stream (a kernel of its own: small chains lost 3 to 5 % to one that holds both bodies).
+template <int DT> __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_fused_chain_kernel(const OgcStreamArgs c) {
+    extern __shared__ __align__(1024) uint8_t smem[];
+    fused_stream<DT>(c, smem);
 }
 
 // For two workgroups on a CU: at most 128 registers (the loads of a few k-steps in flight, then none), and the one workgroup's
@@ -1649,21 +1860,66 @@ static bool fused_pairs(int dtype, int m_blocks, size_t lds) {
     return !(dtype == OGC_I8 && lds > 32 * 1024 && (m_blocks - 1) % 512 < 256);
 }
 
+// Does a chain take the stream?  Its start costs more (parameters to LDS, one more look at the layers: 13-512-256-128-64 in bf16 at batch
+// 128 10.5 us / 12.9 with it, 0.4 MB of weights; int8 333-777-555 at 4000 22.5 / 22.7, 0.7 MB), and layers of fewer than 8 k-steps
+// load without running ahead (int8 100-1500-100-1500-700 at 5000, a fifth of its weights in such layers, 40.2 / 41.1;
+// 1000-130-1000-1000, a seventh, 36.7 / 35.1): from a megabyte on, if no more than a sixth is in those.  Not in fp32, where the matrix
+// instruction is the bound (13-512-256-128 at batch 512 29.0 / 32.1).
+static bool fused_streams(const OgcChainArgs* c, int dtype) {
+    if (dtype == OGC_F32) return false;
+    size_t weights = 0, in_short = 0;
+    for (int l = 0; l < c->n_layers; ++l) {
+        const size_t w = (size_t)(l + 1 == c->n_layers ? (c->layer[l].N + 31) / 32 : c->layer[l].NB_out) * c->layer[l].KC * 512;
+        weights += w;
+        if (c->layer[l].KC < 2 * OGC_STREAM_STEPS) in_short += w;
+    }
+    return weights >= 1000000 && 6 * in_short <= weights;
+}
+
+// Up to 16 row tiles per XCD before the next XCD is used: every XCD that takes part fetches all the weights
+// into its own L2, so a small batch on one XCD asks the fabric for them once instead of eight times
+// (measured 1-4 % faster as well; beyond 16 workgroups on an XCD it turns slower).
+static int fused_grid(OgcChainArgs* args, int m_blocks) {
+    int xcds = 1;
+    while (xcds < 8 && m_blocks > 16 * xcds) xcds *= 2;
+    args->fused_xcds = xcds;
+    args->fused_tiles = m_blocks;
+    return (m_blocks - 1) / xcds * 8 + (m_blocks - 1) % xcds + 1;  // up to the last tile's workgroup
+}
+
+template <int DT> static int launch_fused_stream(const OgcChainArgs* c, int m_blocks, hipStream_t stream) {
+    OgcStreamArgs args;
+    (OgcChainArgs&)args = *c;
+    const size_t buffers = (size_t)2 * c->lds_buf_bytes;
+    size_t lds = buffers;
+    for (int l = 0; l < c->n_layers; ++l) {  // parameters behind the buffers, if they fit
+        args.lds_params[l] = (int32_t)lds;
+        lds += (size_t)(l + 1 == c->n_layers ? (c->layer[l].N + 31) / 32 : c->layer[l].NB_out) * (Quant<DT>::yes ? 256 : 128);
+    }
+    if (lds > ogc_fused_lds_limit()) {
+        lds = buffers;
+        for (int l = 0; l < c->n_layers; ++l) args.lds_params[l] = 0;
+    }
+    void (*const kern)(const OgcStreamArgs) = ogc_fused_chain_kernel<DT>;
+    static OgcLdsLimit limit;
+    if (const int rc = raise_lds(limit, (const void*)kern, lds)) return rc;
+    const int grid = fused_grid(&args, m_blocks);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(OGC_FUSED_THREADS), lds, stream, args);
+    return (int)hipGetLastError();
+}
+
 template <int DT> static int launch_fused_t(const OgcChainArgs* c, int m_blocks, hipStream_t stream) {
     const size_t lds = (size_t)2 * c->lds_buf_bytes;
     const bool pair = fused_pairs(DT, m_blocks, lds);
-    auto kern = pair ? ogc_fused_chain_pair_kernel<DT> : ogc_fused_chain_kernel<DT>;
+    if constexpr (DT != OGC_F32) {
+        if (!pair && fused_streams(c, DT)) return launch_fused_stream<DT>(c, m_blocks, stream);
+    }
+    void (*const deep)(const OgcChainArgs) = ogc_fused_chain_kernel<DT>;
+    auto kern = pair ? ogc_fused_chain_pair_kernel<DT> : deep;
     static OgcLdsLimit limit[2];
     if (const int rc = raise_lds(limit[pair], (const void*)kern, lds)) return rc;
     OgcChainArgs args = *c;
-    // Up to 16 row tiles per XCD before the next XCD is used: every XCD that takes part fetches all the weights
-    // into its own L2, so a small batch on one XCD asks the fabric for them once instead of eight times
-    // (measured 1-4 % faster as well; beyond 16 workgroups on an XCD it turns slower).
-    int xcds = 1;
-    while (xcds < 8 && m_blocks > 16 * xcds) xcds *= 2;
-    args.fused_xcds = xcds;
-    args.fused_tiles = m_blocks;
-    const int grid = (m_blocks - 1) / xcds * 8 + (m_blocks - 1) % xcds + 1;  // up to the last tile's workgroup
+    const int grid = fused_grid(&args, m_blocks);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(OGC_FUSED_THREADS), lds, stream, args);
     return (int)hipGetLastError();
 }

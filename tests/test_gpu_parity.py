@@ -135,6 +135,22 @@ def test_fused_k_steps_and_blocks(oracle_mod, dtype, dims):
 
 
 @pytest.mark.parametrize("dtype, dims, acts, more", [
+    ("i8", [31, 1100, 1090, 33], [RELU, GELU, RELU], dict(a_z=7, c_z=3)), ("i8", [1440, 1504, 1], [NONE, SIGM], dict(last_f32=True)),
+    ("i8", [2400, 1000, 64], [RELU, RELU], {}), ("bf16", [250, 1180, 940, 250], [GELU, RELU, NONE], dict(residual=True)),
+    ("bf16", [1020, 1000, 130], [RELU, RELU], {}), ("f8", [1100, 1090, 70, 33], [RELU, NONE, RELU], {})])
+def test_fused_stream_of_weights(oracle_mod, dtype, dims, acts, more):
+    """A megabyte of weights and more: loads run on from one channel block, and from one layer, to the next.  Whole groups of eight
+    k-steps and two, four and six more, short layers in between, one block to many, parameters that do not fit in LDS beside
+    2400-wide rows, zero points, residual, unaligned rows; on one row tile and a part of another."""
+    wl = synth.make_mlp(dtype, 45, dims, acts, seed=640 + dims[0], name="stream", ld_x=dims[0] + (0 if "residual" in more else 5), **more)
+    if dtype == "f8":
+        from test_gpu_f8 import check_chain
+        check_chain(oracle_mod, wl, "fused", layers_alone=False)
+    else:
+        check(wl, "fused", oracle_mod, ld_y=dims[-1] + 3)
+
+
+@pytest.mark.parametrize("dtype, dims, acts, more", [
     ("i8", [224, 1060, 608, 40], [RELU, NONE, SIGM], dict(last_f32=True)), ("i8", [31, 96, 544, 300], [GELU, RELU, RELU], {}),
     ("bf16", [160, 544, 608, 160], [GELU, RELU, NONE], dict(residual=True)), ("bf16", [31, 288, 640, 33], [RELU, SIGM, GELU], {}),
     ("f32", [96, 288, 160, 96], [GELU, RELU, NONE], dict(residual=True)), ("f32", [31, 320, 64, 7], [RELU, SIGM, RELU], {})])
