@@ -719,6 +719,33 @@ ogc_layer_kernel(const OgcLayerArgs a, int tiles_n, int tiles_total, int tiles_p
 #define OGC_FUSED_WAVES 8
 #define OGC_FUSED_THREADS (OGC_FUSED_WAVES * 64)
 
+// The 32 plain rows of an input tile from row m0 on, staged into LDS in operand layout by all threads of a chain kernel's workgroup
+// (pre-op reorder fused at the chain entry): four lanes take 64 consecutive bytes of a row, and a thread has four pieces on their
+// way.  Against one row a lane and one piece at a time: cluster kernels, 1024-wide rows of two layers, bf16 at batch 1000 21.8 -> 20.5 us, at
+// 128 11.9 -> 11.4 (with the first layer's first weights asked for before it), fp32 512 x 3 at 700 35.9 -> 34.7.  Rows that are not
+// 16-byte aligned (five dwords a piece) and the small chains of the fused kernels lost 1 to 3 % and keep the loop.
+template <int DT> OGC_DEV void stage_tile(const OgcLayerArgs& a, uint8_t* buf, int m0, int tid) {
+    typedef __attribute__((address_space(3))) uint8_t lds_u8;
+    typedef __attribute__((address_space(3))) v4i lds_v4i;
+    lds_u8* const lds = (lds_u8*)buf;
+    const int pieces = a.KC * 32;
+    auto row = [](int p) { return (p >> 2) & 31; };
+    auto chunk = [](int p) { return (p >> 7) * 4 + (p & 3); };
+    for (int p0 = tid; p0 < pieces; p0 += 4 * OGC_FUSED_THREADS) {
+        v4i v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int p = p0 + j * OGC_FUSED_THREADS;
+            if (p < pieces) v[j] = load_plain_chunk<DT, false>(a, m0 + row(p), chunk(p) * 16);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int p = p0 + j * OGC_FUSED_THREADS;
+            if (p < pieces) *(lds_v4i*)(lds + (chunk(p) * 32 + row(p)) * 16) = v[j];
+        }
+    }
+}
+
 // CNT output-channel blocks of one wave at a time: the activation operand read from LDS feeds CNT MFMAs, and
 // the CNT accumulator chains overlap (a single chain would wait out the full MFMA latency at every k-step).
 // stride: distance in channel blocks between a wave's consecutive blocks (the number of waves that share the layer).
@@ -942,7 +969,6 @@ template <int DT> OGC_DEV void fused_stream(const OgcStreamArgs& c, uint8_t* sme
     if (task.steps >= G) first_steps(task);
     {
         const OgcLayerArgs& a = c.layer[0];
-        const int pieces = a.KC * 32;
         for (int l = wave; l < c.n_layers; l += OGC_FUSED_WAVES) {
             const uint32_t bytes = stream_blocks(c, l) * 128, to0 = c.lds_params[l];
             if (to0 == 0) break;
@@ -954,21 +980,7 @@ template <int DT> OGC_DEV void fused_stream(const OgcStreamArgs& c, uint8_t* sme
                 }
             }
         }
-        auto row = [](int p) { return (p >> 2) & 31; };
-        auto chunk = [](int p) { return (p >> 7) * 4 + (p & 3); };
-        for (int p0 = tid; p0 < pieces; p0 += 4 * OGC_FUSED_THREADS) {
-            v4i v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int p = p0 + j * OGC_FUSED_THREADS;
-                if (p < pieces) v[j] = load_plain_chunk<DT, false>(a, m0 + row(p), chunk(p) * 16);
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int p = p0 + j * OGC_FUSED_THREADS;
-                if (p < pieces) *(ogc_lds_v4i*)(lds + (chunk(p) * 32 + row(p)) * 16) = v[j];
-            }
-        }
+        stage_tile<DT>(c.layer[0], smem, m0, tid);
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
@@ -1512,6 +1524,8 @@ __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_cluster_chain_kernel(co
     const int vwave = wave * S + member, vwaves = S * OGC_FUSED_WAVES;
     uint8_t* buf0 = smem;
     uint8_t* buf1 = smem + c.lds_buf_bytes;
+    if (c.layer[0].x_vec_ok) stage_tile<DT>(c.layer[0], buf0, m0, tid);
+    else
     {
         const OgcLayerArgs& a = c.layer[0];
         const int pieces = a.KC * 32;
@@ -1588,6 +1602,16 @@ __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_cluster_ksplit_chain_ke
     const int m0 = tile * 32;
     uint8_t* buf = smem;
     v4i(*red)[4][64] = (v4i(*)[4][64])(smem + c.lds_buf_bytes);
+    // the first weights of the first layer, which wait for no input
+    v4i wfirst[4];
+    bool have_first = member < (c.n_layers == 1 ? ((c.layer[0].N + 31) >> 5) : c.layer[0].NB_out) && wave + 3 * OGC_FUSED_WAVES < (c.layer[0].KC >> 1);
+    if (have_first) {
+        const uint8_t* wn = c.layer[0].w + (size_t)member * c.layer[0].KC * 512 + lane * 16;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) wfirst[u] = *(const v4i*)(wn + (size_t)(wave + u * OGC_FUSED_WAVES) * 1024);
+    }
+    if (c.layer[0].x_vec_ok) stage_tile<DT>(c.layer[0], buf, m0, tid);
+    else
     {
         const OgcLayerArgs& a = c.layer[0];
         const int pieces = a.KC * 32;
@@ -1599,8 +1623,6 @@ __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_cluster_ksplit_chain_ke
     __syncthreads();
     unsigned long long* ctr = sync + (size_t)tile * OGC_SYNC_STRIDE;  // [0] arrivals, [1] members finished
     int barriers = 0;
-    v4i wfirst[4];
-    bool have_first = false;
     for (int l = 0; l < c.n_layers; ++l) {
         const OgcLayerArgs& a = c.layer[l];
         const bool last = l + 1 == c.n_layers;
