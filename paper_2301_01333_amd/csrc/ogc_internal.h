@@ -79,6 +79,7 @@ struct OgcChainArgs {
 
 struct OgcStreamArgs : OgcChainArgs {  // the fused kernel whose loads run on across blocks and layers
     int32_t lds_params[OGC_MAX_LAYERS];  // byte of LDS where a layer's parameters begin; 0: they stay in global memory
+    int32_t rows_out;                    // the last layer's blocks are whole, its rows 16-byte aligned, and LDS holds its output
 };
 
 #define OGC_CLOCK_WORDS_PER_LAUNCH 2048  // ogc_mlp_run_clocked: 64-bit words per launch (at most 512 workgroups x 4)

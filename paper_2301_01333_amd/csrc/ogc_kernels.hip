@@ -907,11 +907,13 @@ template <int DT, int DEEP> OGC_DEV void fused_chain(const OgcChainArgs& c, uint
 // do), and with a task's last steps a step's registers are loaded with the NEXT task's first, also where that belongs to the next
 // layer: weights wait for no activations, and epilogue, barrier and the next task's start run under their loads.  The channels'
 // parameters come from LDS: loads return in order, and one behind the weights would wait for all of them.
-// Measured, us, fused_blocks / this: int8 479-1024-1024-512-256-1 at batch 256 33.4 / 29.0, at 8191 36.5 / 32.6; four 1024-wide layers
-// at 8192 int8 59.4 / 52.8, E4M3 60.2 / 49.3; bf16 479-1024-1024-512-256-1 at 8192 57.0 / 52.2, 512 x 2 at 300 15.5 / 13.8.  Without matrix
-// instructions a 1024-wide int8 layer takes 10.0 us for 12.1 on all CUs, 9.0 for 9.6 on one: the clock gives way.  Tried: two blocks a
-// task (57 / 54, E4M3 59 / 51, but bf16 57 / 55); activations read a group of steps ahead, short tasks' weights too (registers
-// in scratch memory, 57 -> 76).
+// The last layer's rows leave through LDS as 64-byte pieces (block by block, 16 bytes of a row by two lanes each, written through:
+// E4M3 49.3 instead of 45.8 us below).
+// Measured, us, fused_blocks / this: int8 479-1024-1024-512-256-1 at batch 256 33.4 / 29.0, at 8191 36.1 / 32.6; four 1024-wide layers
+// at 8192 int8 58.6 / 52.8, E4M3 60.4 / 45.8; two at 4001 28.4 / 24.6; bf16 479-1024-1024-512-256-1 at 2000 52.9 / 49.1, 512 x 2 at 300
+// 15.4 / 13.0.  A 1024-wide int8 layer takes 12.1 us, 10.0 without matrix instructions, 9.3 without its epilogue too (one CU alone: 9.6,
+// 9.0).  Tried: two blocks a task (57 / 54, E4M3 59 / 51, but bf16 57 / 55); activations read a group of steps ahead, short
+// tasks' weights too (registers in scratch memory, 57 -> 76).
 // ------------------------------------------------------------------------------------------------
 #define OGC_STREAM_STEPS 8
 typedef __attribute__((address_space(3))) v4i ogc_lds_v4i;
@@ -992,6 +994,9 @@ template <int DT> OGC_DEV void fused_stream(const OgcStreamArgs& c, uint8_t* sme
         const ogc_lds_u8* const params = lds + c.lds_params[l];
         const bool in_lds = c.lds_params[l] != 0;
         const uint32_t pbytes = Quant<DT>::yes ? stream_blocks(c, l) * 128 : 0;  // of the scales, before the biases
+        // The last layer's rows leave through LDS, 64 consecutive bytes of a row by four lanes, where its blocks are whole and lie in
+        // LDS as the caller wants them (the general int8 epilogue flips the bytes of blocked results); else each block by itself.
+        const bool rows = last && c.rows_out && (DT != OGC_I8 || a.act == OGC_ACT_RELU);
         const ogc_lds_u8* const xp = xin + at;
         while (task.steps && task.layer == l) {
             const StreamTask next = stream_task(c, l, task.nb + OGC_FUSED_WAVES, wave);
@@ -1079,12 +1084,20 @@ template <int DT> OGC_DEV void fused_stream(const OgcStreamArgs& c, uint8_t* sme
                     p.b[g] = *(const v4f*)(a.bias + n);
                 }
             }
-            if (last) epilogue_block<DT, 1>(acc, a, p, n0, m0, lane, (uint8_t*)nullptr);
+            if (last && !rows) epilogue_block<DT, 1>(acc, a, p, n0, m0, lane, (uint8_t*)nullptr);
             else if (DT == OGC_F8 && a.act == OGC_ACT_RELU) epilogue_block<DT, 0, true, DT == OGC_F8 ? 1 : -1>(acc, a, p, n0, m0, lane, LdsY{xout});
             else epilogue_block<DT, 0>(acc, a, p, n0, m0, lane, LdsY{xout});
             task = next;
         }
-        if (!last) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // (the weights' loads go on)
+        if (!last || rows) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // (the weights' loads go on)
+        if (rows) {
+            const int pieces = a.N * Elt<DT>::size * 2;
+            for (int p = tid; p < pieces; p += OGC_FUSED_THREADS) {
+                const int row = (p >> 2) & 31, chunk = (p >> 7) * 4 + (p & 3);
+                const v4i v = *(const ogc_lds_v4i*)(xout + (chunk * 32 + row) * 16);
+                if (m0 + row < a.M) store16_through(a.y + (long long)(m0 + row) * a.ldy_bytes + chunk * 16, v);
+            }
+        }
     }
 }
 
@@ -1922,6 +1935,9 @@ template <int DT> static int launch_fused_stream(const OgcChainArgs* c, int m_bl
         lds = buffers;
         for (int l = 0; l < c->n_layers; ++l) args.lds_params[l] = 0;
     }
+    const OgcLayerArgs& out = c->layer[c->n_layers - 1];
+    args.rows_out = out.y_vec_ok && !out.res && !out.out_f32 && out.N % 32 == 0 && out.N * (int)Elt<DT>::size % 64 == 0 &&
+                    (size_t)out.N * Elt<DT>::size * 32 <= (size_t)c->lds_buf_bytes;
     void (*const kern)(const OgcStreamArgs) = ogc_fused_chain_kernel<DT>;
     static OgcLdsLimit limit;
     if (const int rc = raise_lds(limit, (const void*)kern, lds)) return rc;

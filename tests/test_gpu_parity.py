@@ -150,6 +150,21 @@ def test_fused_stream_of_weights(oracle_mod, dtype, dims, acts, more):
         check(wl, "fused", oracle_mod, ld_y=dims[-1] + 3)
 
 
+@pytest.mark.parametrize("dtype, dims, acts", [
+    ("i8", [1100, 1000, 64], [RELU, RELU]), ("i8", [1100, 1000, 96], [RELU, RELU]), ("i8", [1024, 1024, 192], [NONE, GELU]),
+    ("i8", [700, 700, 1088], [RELU, RELU]), ("bf16", [640, 960, 32], [RELU, NONE]), ("bf16", [500, 900, 672], [RELU, GELU]),
+    ("f8", [1000, 1100, 128], [NONE, RELU]), ("f8", [1100, 1000, 64], [RELU, NONE])])
+def test_fused_stream_rows_out(oracle_mod, dtype, dims, acts):
+    """The last layer's rows by way of LDS (whole blocks, 16-byte aligned rows, and room for them), or each block by itself; rows
+    farther apart than their length; the second tile ends after 13 rows."""
+    wl = synth.make_mlp(dtype, 45, dims, acts, seed=660 + dims[0] + dims[-1], name="rows out")
+    if dtype == "f8":
+        from test_gpu_f8 import check_chain
+        check_chain(oracle_mod, wl, "fused", layers_alone=False)
+    else:
+        check(wl, "fused", oracle_mod, ld_y=dims[-1] + 16)
+
+
 @pytest.mark.parametrize("dtype, dims, acts, more", [
     ("i8", [224, 1060, 608, 40], [RELU, NONE, SIGM], dict(last_f32=True)), ("i8", [31, 96, 544, 300], [GELU, RELU, RELU], {}),
     ("bf16", [160, 544, 608, 160], [GELU, RELU, NONE], dict(residual=True)), ("bf16", [31, 288, 640, 33], [RELU, SIGM, GELU], {}),
