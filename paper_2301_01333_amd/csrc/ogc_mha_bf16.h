@@ -51,13 +51,11 @@ template <int D32> struct MhaB {
     static constexpr int D = D32 * 32, ROW = D * 2, CH = ROW / 16;  // bytes and 16-byte pieces per row
     static constexpr int UNIT_BYTES = MHA_UNIT * ROW, SLOTS = 4;
     static constexpr int RING = 2 * SLOTS * UNIT_BYTES;  // keys, then values
-    // Position of piece c of key row r inside the row: c ^ swz(r).  LDS takes a 16-byte read in groups of 16 lanes and has 64 banks:
-    // a read takes the same piece of sixteen consecutive keys (first product) or two neighbouring pieces of eight (second).
-    // With these, for rows of 64, 128 and 192 bytes, the former takes 4.1 clocks (8.0 with the pieces of eight keys apart): the split
-    // fp32 body, whose three planes are read for every six instructions, gains 1 to 2 % (32 x 16 x 512 x 64 191.9 -> 189.9 us, 8 x 16 x
-    // 512 x 96 80.3 -> 78.9), the bf16 one nothing.  256-byte rows stay at 8.0: sixteen pieces apart measured 1 % slower.
+    // Position of piece c of key row r inside the row.  A read takes the same piece of eight consecutive keys (first
+    // product) or two neighbouring pieces of four consecutive ones (second): with these the eight 16-byte pieces fall
+    // on distinct groups of four banks, for rows of 64, 128, 192 and 256 bytes.
     static constexpr bool WIDE_ROWS = CH % 8 == 0;
-    static __device__ __forceinline__ int kswz(int r) { return CH == 16 ? (r & 7) : CH == 8 ? ((r >> 1) & 7) : ((r >> 2) & 3); }
+    static __device__ __forceinline__ int kswz(int r) { return WIDE_ROWS ? (r & 7) : ((r >> 1) & 3); }
     static __device__ __forceinline__ int vswz(int r) { return WIDE_ROWS ? 2 * (r & 3) : 2 * ((r >> 1) & 1); }
 };
 
