@@ -722,7 +722,7 @@ ogc_layer_kernel(const OgcLayerArgs a, int tiles_n, int tiles_total, int tiles_p
 // The 32 plain rows of an input tile from row m0 on, staged into LDS in operand layout by all threads of a chain kernel's workgroup
 // (pre-op reorder fused at the chain entry): four lanes take 64 consecutive bytes of a row, and a thread has four pieces on their
 // way.  Against one row a lane and one piece at a time: cluster kernels, 1024-wide rows of two layers, bf16 at batch 1000 21.8 -> 20.5 us, at
-// 128 11.9 -> 11.4 (with the first layer's first weights asked for before it), fp32 512 x 3 at 700 35.9 -> 34.7.  Rows that are not
+// 128 11.9 -> 11.1 (with the first layer's first weights asked for before it), fp32 512 x 3 at 700 35.9 -> 34.8.  Rows that are not
 // 16-byte aligned (five dwords a piece) and the small chains of the fused kernels lost 1 to 3 % and keep the loop.
 template <int DT> OGC_DEV void stage_tile(const OgcLayerArgs& a, uint8_t* buf, int m0, int tid) {
     typedef __attribute__((address_space(3))) uint8_t lds_u8;
@@ -1517,8 +1517,11 @@ __global__ void ogc_zero_sync_kernel(unsigned long long* sync) {
 // runs on XCD b%8): their exchange stays in that XCD's L2.  Visibility does not depend on that placement: stores are
 // written through and the copy back uses system-scope loads, as in the cooperative kernel above, whose bounded
 // barrier wait and counter reset this kernel shares.  sync[1]: workgroups finished; sync[2 + tile]: arrivals.
+// ROWS: the tile is staged by stage_tile, of bf16 and E4M3 rows that are 16-byte aligned (1024 x 2: bf16 at batch 1000 21.5 -> 20.6 us,
+// E4M3 at 2000 13.6 -> 12.9; int8 14.4 / 14.5).  A kernel of its own: with both ways in one, unaligned bf16 rows took 0.8 % longer
+// (479-1024-1024-512-256-1 at 2960 46.6 / 47.2).
 // ------------------------------------------------------------------------------------------------
-template <int DT>
+template <int DT, bool ROWS>
 __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_cluster_chain_kernel(const OgcChainArgs c, unsigned long long* sync) {
     extern __shared__ __align__(16) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1537,9 +1540,9 @@ __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_cluster_chain_kernel(co
     const int vwave = wave * S + member, vwaves = S * OGC_FUSED_WAVES;
     uint8_t* buf0 = smem;
     uint8_t* buf1 = smem + c.lds_buf_bytes;
-    if (c.layer[0].x_vec_ok) stage_tile<DT>(c.layer[0], buf0, m0, tid);
-    else
-    {
+    if constexpr (ROWS) {
+        stage_tile<DT>(c.layer[0], buf0, m0, tid);
+    } else {
         const OgcLayerArgs& a = c.layer[0];
         const int pieces = a.KC * 32;
         for (int p = tid; p < pieces; p += OGC_FUSED_THREADS) {
@@ -2015,10 +2018,15 @@ extern "C" int ogc_cluster_xcds(int m_blocks, int split, int spread) {
 }
 
 template <int DT, int KSPLIT> static int launch_cluster_t(const OgcChainArgs* c, int m_blocks, int split, int spread, int cus, void* sync, hipStream_t stream) {
-    auto kern = KSPLIT ? ogc_cluster_ksplit_chain_kernel<DT> : ogc_cluster_chain_kernel<DT>;
+    auto kern = KSPLIT ? ogc_cluster_ksplit_chain_kernel<DT> : ogc_cluster_chain_kernel<DT, false>;
+    bool rows = false;
+    if constexpr (!KSPLIT && (DT == OGC_BF16 || DT == OGC_F8)) {
+        rows = c->layer[0].x_vec_ok;
+        if (rows) kern = ogc_cluster_chain_kernel<DT, true>;
+    }
     const size_t lds = KSPLIT ? (size_t)c->lds_buf_bytes + OGC_KS_RED_BYTES : (size_t)2 * c->lds_buf_bytes;
-    static OgcLdsLimit limit;
-    if (const int rc = raise_lds(limit, (const void*)kern, lds)) return rc;
+    static OgcLdsLimit limit[2];
+    if (const int rc = raise_lds(limit[rows], (const void*)kern, lds)) return rc;
     const int xcds = ogc_cluster_xcds(m_blocks, split, spread);
     // every member waits for the others of its tile: all of them need a CU at once (the plan assumed 256 CUs)
     if (xcds < 0 || (long)m_blocks * split > cus) return (int)hipErrorInvalidValue;
