@@ -293,7 +293,9 @@ ogc_status ogc_mlp_mode_estimates(ogc_mlp_plan_t plan, float us[3]);
 
 /* Name, with template arguments as a kernel trace prints them, of the kernel that ogc_mlp_run launches for
  * layer `layer` (fused mode: the same name for every layer; a split layer: its first kernel), for matching
- * profiler output.  Returns NULL on a bad argument. */
+ * profiler output.  Where the kernel depends on the address of x, the name is that for an x on a 16-byte boundary (in
+ * the cooperative mode ogc_cluster_rows_chain_kernel takes bf16 and E4M3 rows on such boundaries, ogc_cluster_chain_kernel
+ * all others).  Returns NULL on a bad argument. */
 const char* ogc_mlp_kernel_name(ogc_mlp_plan_t plan, int32_t layer);
 
 #ifdef __cplusplus

@@ -685,6 +685,12 @@ ogc_status ogc_mlp_prepack_weights(ogc_mlp_plan_t plan, const void* const* w, co
     return OGC_OK;
 }
 
+// Are the rows of a plain x whole 16-byte pieces on 16-byte boundaries?
+static int x_rows_aligned(ogc_mlp_plan_t plan, const void* x) {
+    const long long ldx_b = (long long)plan->desc.ld_x * plan->esz;
+    return ((uintptr_t)x % 16 == 0) && (ldx_b % 16 == 0) && (((long long)plan->layers[0].d.k * plan->esz) % 16 == 0);
+}
+
 // Shared body of ogc_mlp_run / ogc_mlp_run_profiled.  With ev != NULL, event ev[i] is recorded on the stream
 // before launch i and ev[n] after the last one.
 static ogc_status run_impl(ogc_mlp_plan_t plan, const void* x, void* y, const void* packed, void* workspace, void* stream,
@@ -704,7 +710,7 @@ static ogc_status run_impl(ogc_mlp_plan_t plan, const void* x, void* y, const vo
     }
     const uint8_t* blob = (const uint8_t*)packed;
     const long long ldx_b = (long long)plan->desc.ld_x * esz, ldy_b = (long long)plan->desc.ld_y * eo;
-    const int x_vec = ((uintptr_t)x % 16 == 0) && (ldx_b % 16 == 0) && (((long long)plan->layers[0].d.k * esz) % 16 == 0);
+    const int x_vec = x_rows_aligned(plan, x);
     const int y_vec = ((uintptr_t)y % 16 == 0) && (ldy_b % 16 == 0);
 
     auto finish_args = [&](int l, OgcLayerArgs* a) {
@@ -925,7 +931,8 @@ const char* ogc_mlp_kernel_name(ogc_mlp_plan_t plan, int32_t layer) {
     if (!plan || layer < 0 || layer >= (int)plan->layers.size()) return nullptr;
     if (plan->mode == OGC_MODE_FUSED) return ogc_fused_kernel_name(plan->desc.dtype, (plan->desc.m + 31) / 32, plan->lds_buf_bytes);
     if (plan->mode == OGC_MODE_COOP)
-        return plan->cluster_split > 0 ? ogc_cluster_kernel_name(plan->desc.dtype, plan->cluster_ksplit) : ogc_coop_kernel_name(plan->desc.dtype);
+        return plan->cluster_split > 0 ? ogc_cluster_kernel_name(plan->desc.dtype, plan->cluster_ksplit, x_rows_aligned(plan, nullptr))
+                                       : ogc_coop_kernel_name(plan->desc.dtype);
     const int L = (int)plan->layers.size();
     const ogc_layer_desc& d = plan->layers[layer].d;
     return ogc_layer_kernel_name(plan->desc.dtype, plan->layers[layer].tile,

@@ -114,7 +114,7 @@ size_t ogc_cluster_ksplit_lds_bytes(size_t lds_buf_bytes);
 int ogc_device_cu_count(void);
 int ogc_static_scratch(void** ptr);  // device address of the static workspace on the current device (asked once per device)
 const char* ogc_coop_kernel_name(int dtype);
-const char* ogc_cluster_kernel_name(int dtype, int ksplit);
+const char* ogc_cluster_kernel_name(int dtype, int ksplit, int x_vec_ok);
 int ogc_launch_prepack_weights(const void* w, void* out, int K, int N, int KC, int NPw, int esz, void* stream);
 int ogc_launch_prepack_params(int dtype, const void* w, const float* w_scale, const float* bias, float in_scale, int in_zp,
                               int K, int N, int NPw, float* scale_out, float* bias_out, int32_t* ncomp_out, void* stream);

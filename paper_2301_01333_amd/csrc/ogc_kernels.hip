@@ -1521,9 +1521,7 @@ __global__ void ogc_zero_sync_kernel(unsigned long long* sync) {
 // E4M3 at 2000 13.6 -> 12.9; int8 14.4 / 14.5).  A kernel of its own: with both ways in one, unaligned bf16 rows took 0.8 % longer
 // (479-1024-1024-512-256-1 at 2960 46.6 / 47.2).
 // ------------------------------------------------------------------------------------------------
-template <int DT, bool ROWS>
-__global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_cluster_chain_kernel(const OgcChainArgs c, unsigned long long* sync) {
-    extern __shared__ __align__(16) uint8_t smem[];
+template <int DT, bool ROWS> OGC_DEV void cluster_chain(const OgcChainArgs& c, unsigned long long* sync, uint8_t* smem) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int S = c.cluster_split;
     int tile, member;
@@ -1588,6 +1586,17 @@ __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_cluster_chain_kernel(co
             }
         }
     }
+}
+
+template <int DT>
+__global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_cluster_chain_kernel(const OgcChainArgs c, unsigned long long* sync) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    cluster_chain<DT, false>(c, sync, smem);
+}
+template <int DT>
+__global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_cluster_rows_chain_kernel(const OgcChainArgs c, unsigned long long* sync) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    cluster_chain<DT, true>(c, sync, smem);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2017,12 +2026,14 @@ extern "C" int ogc_cluster_xcds(int m_blocks, int split, int spread) {
     return -1;
 }
 
+// Does the channel-split cluster kernel stage the rows of x by stage_tile?
+static bool cluster_rows(int dtype, int x_vec_ok) { return x_vec_ok && (dtype == OGC_BF16 || dtype == OGC_F8); }
+
 template <int DT, int KSPLIT> static int launch_cluster_t(const OgcChainArgs* c, int m_blocks, int split, int spread, int cus, void* sync, hipStream_t stream) {
-    auto kern = KSPLIT ? ogc_cluster_ksplit_chain_kernel<DT> : ogc_cluster_chain_kernel<DT, false>;
-    bool rows = false;
+    auto kern = KSPLIT ? ogc_cluster_ksplit_chain_kernel<DT> : ogc_cluster_chain_kernel<DT>;
+    const bool rows = !KSPLIT && cluster_rows(DT, c->layer[0].x_vec_ok);
     if constexpr (!KSPLIT && (DT == OGC_BF16 || DT == OGC_F8)) {
-        rows = c->layer[0].x_vec_ok;
-        if (rows) kern = ogc_cluster_chain_kernel<DT, true>;
+        if (rows) kern = ogc_cluster_rows_chain_kernel<DT>;
     }
     const size_t lds = KSPLIT ? (size_t)c->lds_buf_bytes + OGC_KS_RED_BYTES : (size_t)2 * c->lds_buf_bytes;
     static OgcLdsLimit limit[2];
@@ -2103,12 +2114,14 @@ extern "C" const char* ogc_coop_kernel_name(int dtype) {
     static const char* const names[4] = {"ogc_coop_chain_kernel<0>", "ogc_coop_chain_kernel<1>", "ogc_coop_chain_kernel<2>", "ogc_coop_chain_kernel<3>"};
     return chain_kernel_name(names, dtype);
 }
-extern "C" const char* ogc_cluster_kernel_name(int dtype, int ksplit) {
+extern "C" const char* ogc_cluster_kernel_name(int dtype, int ksplit, int x_vec_ok) {
     static const char* const ks[4] = {"ogc_cluster_ksplit_chain_kernel<0>", "ogc_cluster_ksplit_chain_kernel<1>",
                                       "ogc_cluster_ksplit_chain_kernel<2>", "ogc_cluster_ksplit_chain_kernel<3>"};
     static const char* const plain[4] = {"ogc_cluster_chain_kernel<0>", "ogc_cluster_chain_kernel<1>", "ogc_cluster_chain_kernel<2>",
                                          "ogc_cluster_chain_kernel<3>"};
-    return ksplit ? chain_kernel_name(ks, dtype) : chain_kernel_name(plain, dtype);
+    static const char* const rows[4] = {"?", "ogc_cluster_rows_chain_kernel<1>", "?", "ogc_cluster_rows_chain_kernel<3>"};
+    if (ksplit) return chain_kernel_name(ks, dtype);
+    return cluster_rows(dtype, x_vec_ok) ? chain_kernel_name(rows, dtype) : chain_kernel_name(plain, dtype);
 }
 
 extern "C" int ogc_launch_prepack_weights(const void* w, void* out, int K, int N, int KC, int NPw, int esz, void* stream) {
