@@ -929,7 +929,17 @@ ogc_status ogc_mlp_mode_estimates(ogc_mlp_plan_t plan, float us[3]) {
 
 const char* ogc_mlp_kernel_name(ogc_mlp_plan_t plan, int32_t layer) {
     if (!plan || layer < 0 || layer >= (int)plan->layers.size()) return nullptr;
-    if (plan->mode == OGC_MODE_FUSED) return ogc_fused_kernel_name(plan->desc.dtype, (plan->desc.m + 31) / 32, plan->lds_buf_bytes);
+    if (plan->mode == OGC_MODE_FUSED) {
+        OgcChainArgs c;  // what the choice looks at: the layers' sizes
+        std::memset(&c, 0, sizeof(c));
+        c.n_layers = (int)plan->layers.size();
+        c.lds_buf_bytes = plan->lds_buf_bytes;
+        for (int l = 0; l < c.n_layers; ++l) {
+            const LayerPlan& lp = plan->layers[l];
+            c.layer[l].N = lp.d.n, c.layer[l].KC = lp.kc, c.layer[l].NB_out = lp.nb_out;
+        }
+        return ogc_fused_kernel_name(plan->desc.dtype, &c, (plan->desc.m + 31) / 32);
+    }
     if (plan->mode == OGC_MODE_COOP)
         return plan->cluster_split > 0 ? ogc_cluster_kernel_name(plan->desc.dtype, plan->cluster_ksplit, x_rows_aligned(plan, nullptr))
                                        : ogc_coop_kernel_name(plan->desc.dtype);

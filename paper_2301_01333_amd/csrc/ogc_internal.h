@@ -121,7 +121,7 @@ int ogc_launch_prepack_params(int dtype, const void* w, const float* w_scale, co
 int ogc_launch_quantize_e4m3(const float* x, uint8_t* out, size_t n, float inv_scale, void* stream);
 int ogc_launch_dequantize_e4m3(const uint8_t* x, float* out, size_t n, float scale, void* stream);
 const char* ogc_layer_kernel_name(int dtype, int tile, int x_plain, int out_plain, int act, int out_f32, int split);
-const char* ogc_fused_kernel_name(int dtype, int m_blocks, int lds_buf_bytes);
+const char* ogc_fused_kernel_name(int dtype, const OgcChainArgs* c, int m_blocks);
 size_t ogc_fused_lds_limit(void);
 int ogc_fused_threads(void);
 #ifdef __cplusplus

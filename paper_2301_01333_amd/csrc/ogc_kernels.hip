@@ -1106,7 +1106,7 @@ template <int DT> __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_fused
     fused_chain<DT, 8>(c, smem);
 }
 // The same for chains that take the stream (a kernel of its own: small chains lost 3 to 5 % to one that holds both bodies).
-template <int DT> __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_fused_chain_kernel(const OgcStreamArgs c) {
+template <int DT> __global__ void __launch_bounds__(OGC_FUSED_THREADS) ogc_fused_chain_stream_kernel(const OgcStreamArgs c) {
     extern __shared__ __align__(1024) uint8_t smem[];
     fused_stream<DT>(c, smem);
 }
@@ -1950,7 +1950,7 @@ template <int DT> static int launch_fused_stream(const OgcChainArgs* c, int m_bl
     const OgcLayerArgs& out = c->layer[c->n_layers - 1];
     args.rows_out = out.y_vec_ok && !out.res && !out.out_f32 && out.N % 32 == 0 && out.N * (int)Elt<DT>::size % 64 == 0 &&
                     (size_t)out.N * Elt<DT>::size * 32 <= (size_t)c->lds_buf_bytes;
-    void (*const kern)(const OgcStreamArgs) = ogc_fused_chain_kernel<DT>;
+    auto kern = ogc_fused_chain_stream_kernel<DT>;
     static OgcLdsLimit limit;
     if (const int rc = raise_lds(limit, (const void*)kern, lds)) return rc;
     const int grid = fused_grid(&args, m_blocks);
@@ -1964,8 +1964,7 @@ template <int DT> static int launch_fused_t(const OgcChainArgs* c, int m_blocks,
     if constexpr (DT != OGC_F32) {
         if (!pair && fused_streams(c, DT)) return launch_fused_stream<DT>(c, m_blocks, stream);
     }
-    void (*const deep)(const OgcChainArgs) = ogc_fused_chain_kernel<DT>;
-    auto kern = pair ? ogc_fused_chain_pair_kernel<DT> : deep;
+    auto kern = pair ? ogc_fused_chain_pair_kernel<DT> : ogc_fused_chain_kernel<DT>;
     static OgcLdsLimit limit[2];
     if (const int rc = raise_lds(limit[pair], (const void*)kern, lds)) return rc;
     OgcChainArgs args = *c;
@@ -2168,8 +2167,10 @@ extern "C" const char* ogc_layer_kernel_name(int dtype, int tile, int x_plain, i
     }
     return n;
 }
-extern "C" const char* ogc_fused_kernel_name(int dtype, int m_blocks, int lds_buf_bytes) {
+extern "C" const char* ogc_fused_kernel_name(int dtype, const OgcChainArgs* c, int m_blocks) {
     static const char* const names[4] = {"ogc_fused_chain_kernel<0>", "ogc_fused_chain_kernel<1>", "ogc_fused_chain_kernel<2>", "ogc_fused_chain_kernel<3>"};
     static const char* const pair[4] = {"ogc_fused_chain_pair_kernel<0>", "ogc_fused_chain_pair_kernel<1>", "ogc_fused_chain_pair_kernel<2>", "ogc_fused_chain_pair_kernel<3>"};
-    return fused_pairs(dtype, m_blocks, (size_t)2 * lds_buf_bytes) ? chain_kernel_name(pair, dtype) : chain_kernel_name(names, dtype);
+    static const char* const stream[4] = {"?", "ogc_fused_chain_stream_kernel<1>", "ogc_fused_chain_stream_kernel<2>", "ogc_fused_chain_stream_kernel<3>"};
+    if (fused_pairs(dtype, m_blocks, (size_t)2 * c->lds_buf_bytes)) return chain_kernel_name(pair, dtype);
+    return fused_streams(c, dtype) ? chain_kernel_name(stream, dtype) : chain_kernel_name(names, dtype);
 }

@@ -407,9 +407,9 @@ def test_auto_mode_choice_follows_the_cost_models():
 
 @pytest.mark.parametrize("dtype, width, m, name", [
     (b.OGC_BF16, 64, 8192, "kernel<1>"), (b.OGC_BF16, 64, 8193, "pair_kernel<1>"), (b.OGC_BF16, 640, 9000, "pair_kernel<1>"),
-    (b.OGC_BF16, 672, 9000, "kernel<1>"), (b.OGC_F32, 320, 9000, "pair_kernel<0>"), (b.OGC_F32, 352, 9000, "kernel<0>"),
-    (b.OGC_F8, 1280, 9000, "pair_kernel<3>"), (b.OGC_F8, 1344, 9000, "kernel<3>"), (b.OGC_I8, 512, 9000, "pair_kernel<2>"),
-    (b.OGC_I8, 512, 24576, "pair_kernel<2>"), (b.OGC_I8, 1024, 16384, "pair_kernel<2>"), (b.OGC_I8, 1024, 24576, "kernel<2>")])
+    (b.OGC_BF16, 672, 9000, "stream_kernel<1>"), (b.OGC_F32, 320, 9000, "pair_kernel<0>"), (b.OGC_F32, 352, 9000, "kernel<0>"),
+    (b.OGC_F8, 1280, 9000, "pair_kernel<3>"), (b.OGC_F8, 1344, 9000, "stream_kernel<3>"), (b.OGC_I8, 512, 9000, "pair_kernel<2>"),
+    (b.OGC_I8, 512, 24576, "pair_kernel<2>"), (b.OGC_I8, 1024, 16384, "pair_kernel<2>"), (b.OGC_I8, 1024, 24576, "stream_kernel<2>")])
 def test_fused_kernel_name_tells_the_one_that_runs(dtype, width, m, name):
     """Two workgroups to a CU from the 257th row tile on, where LDS holds the rows of both."""
     quant = dict(in_scale=0.05, in_zp=128 if dtype == b.OGC_I8 else 0, out_scale=0.1, out_zp=128 if dtype == b.OGC_I8 else 0) if dtype in (b.OGC_I8, b.OGC_F8) else {}

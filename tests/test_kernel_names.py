@@ -67,3 +67,19 @@ def test_cluster_kernel_name_tells_how_rows_are_staged(dtype, width, ld_x, name)
     """bf16 and E4M3 rows on 16-byte boundaries have a kernel of their own."""
     ov = {"cluster_split": 2, "cluster_ksplit": 0}
     assert chain_name(dtype, 100, [width, 96, 64], b.OGC_MODE_COOP, ov, ld_x) == {"ogc_cluster_" + name}
+
+
+@pytest.mark.parametrize("dtype, m, dims, name", [
+    # a megabyte (1000000 bytes) of packed weights, inner widths padded to 32 channels (bf16) or 64
+    (b.OGC_I8, 256, [1024, 960, 32], "stream_kernel<2>"), (b.OGC_I8, 256, [1024, 896, 32], "kernel<2>"), (b.OGC_BF16, 100, [512, 992], "stream_kernel<1>"),
+    (b.OGC_BF16, 100, [512, 960], "kernel<1>"), (b.OGC_F8, 100, [1000, 1000], "stream_kernel<3>"), (b.OGC_F8, 100, [960, 1024], "kernel<3>"),
+    (b.OGC_F32, 100, [512, 512], "kernel<0>"),
+    # at most a sixth of them in layers of fewer than eight k-steps
+    (b.OGC_I8, 100, [192, 1024, 1024], "stream_kernel<2>"), (b.OGC_I8, 100, [192, 1280, 960], "stream_kernel<2>"), (b.OGC_I8, 100, [192, 1280, 928], "kernel<2>"),
+    (b.OGC_BF16, 1, [96, 640, 800], "stream_kernel<1>"), (b.OGC_I8, 100, [1000, 130, 1000, 1000], "stream_kernel<2>"), (b.OGC_I8, 100, [100, 1500, 100, 1500, 700], "kernel<2>"),
+    # beyond 256 row tiles, where LDS holds two workgroups, the pair kernel comes first
+    (b.OGC_I8, 8192, [1024, 1024, 1024], "stream_kernel<2>"), (b.OGC_F8, 8193, [1024, 1024, 1024], "pair_kernel<3>")])
+def test_fused_kernel_name_tells_the_stream(kernels, dtype, m, dims, name):
+    """Which chains have their weights streamed across blocks and layers."""
+    assert chain_name(dtype, m, dims, b.OGC_MODE_FUSED) == {"ogc_fused_chain_" + name}
+    assert "ogc_fused_chain_" + name in kernels
