@@ -633,11 +633,14 @@ template <int D32> __global__ __launch_bounds__(256, Mha8<D32>::RESIDENT) void o
     if (idle) return;
 
     // ---- normalise, requantize, store: after the half exchange a lane holds 16 consecutive channels of its query.
-    // float(A) / float(L) by the reciprocal: y = 1 / L rounded once, q = A y, q + (A - q L) y, the last two fused.  With L
-    // below 2^22 this is the quotient rounded once, the division's own result: q is within 1.5 units in the last place, so the
-    // remainder is exact and the sum before its rounding within 1.5 * 2^-24 units of A / L, which for such L is at least
-    // 2 * 2^-24 units away from any midpoint of two fp32 values.  As a division, 64 of them a lane, it was half of the vector
-    // ALU's work at 384 tokens.
+    // float(A) / float(L) by the reciprocal: y = 1 / L rounded once, q = A y, q + (A - q L) y, the last two fused.  This is the
+    // quotient rounded once, the division's own result: with u the unit in the last place of A / L and y = (1 + e) / L, q is within
+    // 1.5 u, so the remainder is exact and the sum before its rounding is |A / L - q| |e| < 1.5 * 2^-24 u away from A / L, which
+    // is more than u / 2 L away from any midpoint of two fp32 values.  For L below 2^22 that is enough (and up to 2^23, beyond the
+    // longest sequence, it still holds: a q beside the midpoint leaves an error below 2^-24 u, and for one farther off |e| would
+    // have to pass (1 - 1.5 * 2^-24) 2^-24, which no such L reaches).  As a division, 64 of them a lane, it was half of the
+    // vector ALU's work at 384 tokens.  Longer sequences divide, with time to spare; without that second body the compiler of
+    // the 96-channel kernel reloads a spilled register in the loop over the keys.
     const int sum = (int)row_sum + other_half_i((int)row_sum);
     const float lf = (float)sum, y = 1.0f / lf;
     uint8_t* op = a.o + b * a.so[0] + hd * a.so[1] + (long long)query * a.so[2];

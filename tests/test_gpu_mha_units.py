@@ -299,19 +299,26 @@ def test_i8_slots_of_keys(oracle_mod, head_dim, batch, seq):
             assert diff.max() <= 1 and (diff > 0).mean() < 0.01, "entry %d: %d steps, %.3f %%" % (e, diff.max(), 100.0 * (diff > 0).mean())
 
 
-def test_i8_quotient_beyond_the_reciprocal():
-    """Row sums beyond 2^22 are divided by, not multiplied by the reciprocal: 33000 keys that all weigh 127."""
+@pytest.mark.parametrize("seq", [32768, 33100, 65536])
+def test_i8_quotient_beyond_the_reciprocal(seq):
+    """Keys that all weigh 127, on both sides of the rule: the largest row sum that the reciprocal serves, one beyond 2^22 = 4194304 (more
+    than 33026 keys) and the largest there is, which divide.  Channels of different means, so that outputs span the range."""
     from paper_2301_01333_amd.harness import DeviceMHA
 
-    wl = synth.make_mha("i8", 1, 33000, 32, 1, 8450, name="i8 33000 keys")
+    wl = synth.make_mha("i8", 1, seq, 128, 4, 8450, name="i8 %d keys" % seq)
+    assert (127 * seq < 1 << 22) == (seq == 32768)
     wl.q = np.zeros_like(wl.q)
+    base = np.linspace(-31, 31, 128)
+    wl.v = (base + np.random.default_rng(8451).integers(-40, 41, (seq, 128))).round().astype(np.int8).reshape(wl.v.shape)
     vs, os = np.float32(wl.quant[2]), np.float32(wl.quant[3])
     dev = DeviceMHA(wl, STABLE, False)
     dev.run()
-    got = dev.result().reshape(33000, 32).astype(np.int32)
-    a = 127 * wl.v.reshape(33000, 32).astype(np.int64).sum(0)
-    r = (a.astype(np.float32) / np.float32(127 * 33000)) * (vs / os)
-    assert (got == np.clip(np.rint(r), -128, 127).astype(np.int32)[None]).all()
+    got = dev.result().reshape(seq, 128).astype(np.int32)
+    a = 127 * wl.v.reshape(seq, 128).astype(np.int64).sum(0)
+    r = (a.astype(np.float32) / np.float32(127 * seq)) * (vs / os)
+    want = np.clip(np.rint(r), -128, 127).astype(np.int32)
+    assert want.min() < -100 and want.max() > 100
+    assert (got == want[None]).all()
 
 
 def i8_in_fp32(wl, use_mask=True):

@@ -151,28 +151,42 @@ def test_invariants(oracle_mod):
     assert np.abs(got - ref).max() <= 0.05 * 0.5 + 5.0 * s_ * (1.0 / 127)
 
 
-def test_quotient_by_reciprocal_is_the_division():
-    """The streaming kernel's A / L: y = 1 / L rounded once, q = A y, q + (A - q L) y with fused operations.  For every L below 2^22 it is
-    the division's own result; here random pairs, small ones exhaustively, and quotients next to midpoints of two fp32 values."""
-    rng = np.random.default_rng(5700)
+def reciprocal_quotient(a, l):
+    """The streaming kernel's A / L: y = 1 / L rounded once, q = A y, q + (A - q L) y with fused operations."""
     f = np.float32
 
     def fused(x, y, z):
         return (x.astype(np.longdouble) * y.astype(np.longdouble) + z.astype(np.longdouble)).astype(f)  # 64 bits hold the sums here
 
+    y = f(1.0) / l
+    q = a * y
+    return fused(fused(-q, l, a), y, q)
+
+
+def test_quotient_by_reciprocal_is_the_division():
+    """It is the division's own result for every L below 2^23, beyond 65536 keys of 127: random pairs, small ones exhaustively,
+    quotients next to midpoints of two fp32 values, and those at the top of a binade with the reciprocals that are rounded most."""
+    rng = np.random.default_rng(5700)
+    most = 127 * 128 * 65536
+
     def check(a, l):
-        a, l = a.astype(f), l.astype(f)
-        y = f(1.0) / l
-        q = a * y
-        assert np.array_equal(fused(fused(-q, l, a), y, q), a / l)
+        a, l = a.astype(np.float32), l.astype(np.float32)
+        assert np.array_equal(reciprocal_quotient(a, l), a / l)
+
+    def near_midpoints(q, e, l):  # A nearest to (a midpoint) * L: the quotient is as near to the midpoint as an integer A allows
+        a = np.rint((q.astype(np.longdouble) + 0.5) * l / (2.0 ** 23) * 2.0 ** (e - 12).astype(np.longdouble)).astype(np.int64)
+        check(a[a <= most], l[a <= most])
 
     small = np.arange(1, 700)
     check(np.repeat(np.arange(-700, 700), small.size), np.tile(small, 1400))
-    for top in (1 << 10, 1 << 16, 1 << 22):
-        l = rng.integers(1, top, 500000)
-        check(rng.integers(-127 * 128 * 32768, 127 * 128 * 32768, l.size), l)
-        # A nearest to (a midpoint) * L: the quotient is as near to the midpoint as an integer A allows
-        q = rng.integers(1 << 23, 1 << 24, l.size)
-        e = rng.integers(0, 20, l.size)
-        a = np.rint((q.astype(np.longdouble) + 0.5) * l / (2.0 ** 23) * 2.0 ** (e - 12).astype(np.longdouble)).astype(np.int64)
-        check(a, l)
+    for top in (1 << 10, 1 << 16, 1 << 22, 1 << 23):
+        l = rng.integers(max(1, top >> 1 if top > 1 << 21 else 1), top, 500000)
+        check(rng.integers(-most, most, l.size), l)
+        near_midpoints(rng.integers(1 << 23, 1 << 24, l.size), rng.integers(0, 20, l.size), l)
+    # the proof's last step: how far from 1 / L its rounded value is, relatively, for every L there is
+    l = np.arange(1, 1 << 23)
+    e = np.abs(1.0 - l * (np.float32(1.0) / l.astype(np.float32)).astype(np.float64)) * 2.0 ** 24  # (exact: 47 bits)
+    assert e.max() < 1.0 - 1.5 * 2.0 ** -24
+    worst = np.argsort(e)[-20000:]
+    for q in range((1 << 24) - 8, 1 << 24):
+        near_midpoints(np.full(worst.size, q), rng.integers(0, 20, worst.size), l[worst])
