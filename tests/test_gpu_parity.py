@@ -134,6 +134,14 @@ def test_fused_k_steps_and_blocks(oracle_mod, dtype, dims):
         check(synth.make_mlp(dtype, 8192 + 33, dims, [RELU] * (len(dims) - 1), seed=621, name="pairs"), "fused", oracle_mod)
 
 
+def kernel_name(wl, mode, ld_x=None, overrides=None):
+    """The kernel of the workload's first layer."""
+    mlp = binding.FusedMLP(wl.dtype, wl.m, wl.layers, ld_x, None, wl.residual, MODES[mode], overrides=overrides)
+    name = binding.ogc_mlp_kernel_name(mlp.plan, 0)
+    mlp.close()
+    return name
+
+
 @pytest.mark.parametrize("dtype, dims, acts, more", [
     ("i8", [31, 1100, 1090, 33], [RELU, GELU, RELU], dict(a_z=7, c_z=3)), ("i8", [1440, 1504, 1], [NONE, SIGM], dict(last_f32=True)),
     ("i8", [2400, 1000, 64], [RELU, RELU], {}), ("bf16", [250, 1180, 940, 250], [GELU, RELU, NONE], dict(residual=True)),
@@ -143,6 +151,7 @@ def test_fused_stream_of_weights(oracle_mod, dtype, dims, acts, more):
     k-steps and two, four and six more, short layers in between, one block to many, parameters that do not fit in LDS beside
     2400-wide rows, zero points, residual, unaligned rows; on one row tile and a part of another."""
     wl = synth.make_mlp(dtype, 45, dims, acts, seed=640 + dims[0], name="stream", ld_x=dims[0] + (0 if "residual" in more else 5), **more)
+    assert kernel_name(wl, "fused").startswith("ogc_fused_chain_stream_kernel")
     if dtype == "f8":
         from test_gpu_f8 import check_chain
         check_chain(oracle_mod, wl, "fused", layers_alone=False)
@@ -158,11 +167,27 @@ def test_fused_stream_rows_out(oracle_mod, dtype, dims, acts):
     """The last layer's rows by way of LDS (whole blocks, 16-byte aligned rows, and room for them), or each block by itself; rows
     farther apart than their length; the second tile ends after 13 rows."""
     wl = synth.make_mlp(dtype, 45, dims, acts, seed=660 + dims[0] + dims[-1], name="rows out")
+    assert kernel_name(wl, "fused").startswith("ogc_fused_chain_stream_kernel")
     if dtype == "f8":
         from test_gpu_f8 import check_chain
         check_chain(oracle_mod, wl, "fused", layers_alone=False)
     else:
         check(wl, "fused", oracle_mod, ld_y=dims[-1] + 16)
+
+
+@pytest.mark.parametrize("m", [545, 3001])
+@pytest.mark.parametrize("dtype, dims, has_bias", [("i8", [1024, 960, 64], False), ("bf16", [520, 960, 33], False), ("f8", [1000, 1000, 40], False),
+                                                   ("i8", [479, 1024, 640, 7], True)])
+def test_fused_stream_over_xcds(oracle_mod, dtype, dims, has_bias, m):
+    """Row tiles on two XCDs and on all eight, the last one ragged; chains without a bias, whose place in LDS is filled all the same."""
+    acts = [RELU] * (len(dims) - 1)
+    wl = synth.make_mlp(dtype, m if dtype != "f8" else min(m, 1111), dims, acts, seed=680 + dims[0] + m, name="stream on XCDs", has_bias=has_bias)
+    assert kernel_name(wl, "fused").startswith("ogc_fused_chain_stream_kernel")
+    if dtype == "f8":
+        from test_gpu_f8 import check_chain
+        check_chain(oracle_mod, wl, "fused", layers_alone=False)
+    else:
+        check(wl, "fused", oracle_mod, rows=[slice(0, 300), slice(wl.m - 300, wl.m)])
 
 
 @pytest.mark.parametrize("dtype, dims, acts, more", [
@@ -577,6 +602,26 @@ def test_cluster_kernel_ragged_and_edges(oracle_mod, dtype, split):
         check(synth.make_mlp("i8", 19, [70, 64, 5], [RELU, SIGM], seed=5, last_f32=True), "coop", oracle_mod, overrides=ov)
     else:
         check(synth.make_mlp(dtype, 70, [40, 64, 40], [GELU, NONE], seed=13, residual=True), "coop", oracle_mod, overrides=ov)
+
+
+@pytest.mark.parametrize("width", [72, 264, 520, 1024])
+@pytest.mark.parametrize("dtype", ["bf16", "f8", "i8", "f32"])
+@pytest.mark.parametrize("ksplit", [0, 1])
+def test_cluster_kernel_wide_aligned_rows(oracle_mod, dtype, width, ksplit):
+    """Rows on 16-byte boundaries, staged with four pieces of a thread on their way: less than one piece a thread, several, turns that end
+    within the four, and a ragged last tile; as they are, and farther apart than their length.  A misaligned x takes the other way."""
+    width = {"bf16": width, "f8": 2 * width, "i8": 2 * width, "f32": width // 2}[dtype]   # 144, 528, 1040 and 2048 bytes
+    ov = {"cluster_split": 2, "cluster_ksplit": ksplit, "cluster_whole": 0}
+    want = "ogc_cluster_" + ("ksplit_" if ksplit else "rows_" if dtype in ("bf16", "f8") else "") + "chain_kernel"
+    esz = {"bf16": 2, "f8": 1, "i8": 1, "f32": 4}[dtype]
+    for ld_x, offset in ((width, 0), (width + 16 // esz, 0), (width, esz)):
+        wl = synth.make_mlp(dtype, 77, [width, 100, 64], [RELU, RELU], seed=690 + width, name="wide rows", ld_x=ld_x)
+        assert kernel_name(wl, "coop", ld_x, ov).startswith(want)
+        if dtype == "f8":
+            from test_gpu_f8 import check_chain
+            check_chain(oracle_mod, wl, "coop", layers_alone=False, overrides=ov, x_byte_offset=offset)
+        else:
+            check(wl, "coop", oracle_mod, overrides=ov, x_byte_offset=offset)
 
 
 @pytest.mark.parametrize("dtype,m,split", [("i8", 256, 4), ("i8", 520, 8), ("bf16", 200, 4), ("bf16", 64, 16), ("i8", 2048, 4),
