@@ -125,9 +125,48 @@ def check_stream_kernel_registers(verbose: bool = True) -> None:
     pairs = re.findall(r"\.name:\s+(_Z\d+ogc_fused_chain_pair_kernel\w+)\s*\n\s+\.private_segment_fixed_size:\s+(\d+)", text)
     if len(pairs) != 4 or any(int(scratch) for _, scratch in pairs):
         raise RuntimeError("fused pair kernels (name, bytes of scratch memory per lane): %s" % pairs)
+    # Its streaming kernel counts on weights that arrive in order: a reload of a spilled register would wait for all of them.
+    streams = re.findall(r"\.name:\s+(_Z\d+ogc_fused_chain_stream_kernel\w+)\s*\n\s+\.private_segment_fixed_size:\s+(\d+)", text)
+    if len(streams) != 3 or any(int(scratch) for _, scratch in streams):
+        raise RuntimeError("fused streaming kernels (name, bytes of scratch memory per lane): %s" % streams)
     if verbose:
         print("stream kernels checked: %d (compiler writes nothing at or above v80, no calls; %d kernels of the general "
               "epilogue use scratch memory)" % (checked, spilling), flush=True)
+
+
+def _loops(lines):
+    """(first, last) line of every loop: from a label to a branch back to it."""
+    import re
+
+    at, found = {}, []
+    for i, line in enumerate(lines):
+        label, branch = re.match(r"(\.LBB\w+):", line), re.match(r"\s+s_c?branch\w*\s+(\.LBB\w+)", line)
+        if label:
+            at[label.group(1)] = i
+        if branch and branch.group(1) in at:
+            found.append((at[branch.group(1)], i))
+    return found
+
+
+def check_int8_attention_loops(verbose: bool = True) -> None:
+    """The streaming Int8 attention kernels hold the registers of three to six workgroups on a CU; 96 channels do not quite fit and
+    spill a few between the two passes over the keys.  Inside the passes a reload would wait for every direct load on its
+    way: this compiles the kernels to assembly and fails if a loop with matrix instructions touches scratch memory."""
+    import re
+
+    text, checked = _device_assembly("ogc_mha_i8.hip"), 0
+    for m in re.finditer(r"^(_Z24ogc_mha_i8_stream_kernel\w*):[^\n]*\n(.*?)\n\.Lfunc_end", text, re.S | re.M):
+        lines = [l.split(";")[0] for l in m.group(2).splitlines()]
+        loops = [lines[a:b] for a, b in _loops(lines) if any("v_mfma" in l for l in lines[a:b])]
+        if len(loops) < 2:
+            raise RuntimeError("%s: the two passes over the keys were not found in the assembly" % m.group(1))
+        if any("scratch_" in l for body in loops for l in body):
+            raise RuntimeError("%s spills registers in a loop over the keys" % m.group(1))
+        checked += 1
+    if checked != 4:
+        raise RuntimeError("streaming Int8 attention kernels found in the assembly: %d of 4" % checked)
+    if verbose:
+        print("streaming Int8 attention kernels checked: %d (no spills in the loops over the keys)" % checked, flush=True)
 
 
 def check_split_attention_loops(verbose: bool = True) -> None:
@@ -140,14 +179,9 @@ def check_split_attention_loops(verbose: bool = True) -> None:
     text = _device_assembly("ogc_mha.hip")
     checked = 0
     for m in re.finditer(r"^(_Z14ogc_mha_kernelILi0ELi([123])E\w*):[^\n]*\n(.*?)\n\.Lfunc_end", text, re.S | re.M):
-        name, lines, at, found = m.group(1), [l.split(";")[0] for l in m.group(3).splitlines()], {}, 0
-        for i, line in enumerate(lines):
-            label, branch = re.match(r"(\.LBB\w+):", line), re.match(r"\s+s_c?branch\w*\s+(\.LBB\w+)", line)
-            if label:
-                at[label.group(1)] = i
-            if not branch or branch.group(1) not in at:
-                continue
-            body = lines[at[branch.group(1)]:i]
+        name, lines, found = m.group(1), [l.split(";")[0] for l in m.group(3).splitlines()], 0
+        for first, last in _loops(lines):
+            body = lines[first:last]
             if sum("v_mfma_f32_32x32x16_bf16" in l for l in body) != 48 * int(m.group(2)):
                 continue
             found += 1
@@ -166,4 +200,5 @@ if __name__ == "__main__":
     print(build_library())
     check_stream_kernel_registers()
     check_split_attention_loops()
+    check_int8_attention_loops()
     sys.exit(0)
