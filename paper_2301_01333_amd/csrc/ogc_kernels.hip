@@ -722,8 +722,9 @@ ogc_layer_kernel(const OgcLayerArgs a, int tiles_n, int tiles_total, int tiles_p
 // The 32 plain rows of an input tile from row m0 on, staged into LDS in operand layout by all threads of a chain kernel's workgroup
 // (pre-op reorder fused at the chain entry): four lanes take 64 consecutive bytes of a row, and a thread has four pieces on their
 // way.  Against one row a lane and one piece at a time: cluster kernels, 1024-wide rows of two layers, bf16 at batch 1000 21.8 -> 20.5 us, at
-// 128 11.9 -> 11.1 (with the first layer's first weights asked for before it), fp32 512 x 3 at 700 35.9 -> 34.8.  Rows that are not
-// 16-byte aligned (five dwords a piece) and the small chains of the fused kernels lost 1 to 3 % and keep the loop.
+// 128 11.9 -> 11.1 (with the first layer's first weights asked for before it), fp32 512 x 3 at 700 35.9 -> 34.8.  In the cluster kernels
+// rows that are not 16-byte aligned (five dwords a piece) lost 1 to 2 %, in the deep and pair kernels small chains 2 to 4 %: these keep
+// the loop.  The streaming kernel stages all rows this way, by global loads, as its first weights are on their way meanwhile.
 template <int DT> OGC_DEV void stage_tile(const OgcLayerArgs& a, uint8_t* buf, int m0, int tid) {
     typedef __attribute__((address_space(3))) uint8_t lds_u8;
     typedef __attribute__((address_space(3))) v4i lds_v4i;
@@ -970,7 +971,6 @@ template <int DT> OGC_DEV void fused_stream(const OgcStreamArgs& c, uint8_t* sme
     // parameters straight into LDS: scale and bias, or the bias alone, of a layer by one wave.
     if (task.steps >= G) first_steps(task);
     {
-        const OgcLayerArgs& a = c.layer[0];
         for (int l = wave; l < c.n_layers; l += OGC_FUSED_WAVES) {
             const uint32_t bytes = stream_blocks(c, l) * 128, to0 = c.lds_params[l];
             if (to0 == 0) break;
@@ -1901,7 +1901,11 @@ extern "C" int ogc_fused_threads(void) { return OGC_FUSED_THREADS; }
 //   24576   18.1/14.3 27.5/24.7 18.6/17.3 29.2/26.1 19.1/13.8 30.2/24.2 41.4/37.4 93.7/93.7
 //   32768   23.2/16.2 35.5/25.8 23.8/18.9 37.5/27.4 24.4/14.1 39.2/26.5 53.8/45.6 123/123
 // Wide int8 rows leave a workgroup that ends up alone on its CU with too few loads in flight: two layers of 1024 at batch 24576
-// 104 / 113 (16384: 63 / 58; 32768: 139 / 127; E4M3 at 24576: 114 / 106).
+// 104 / 113 (16384: 63 / 58; 32768: 139 / 127; E4M3 at 24576: 114 / 106).  The line was drawn against the deep kernel.  Against the
+// streaming one, which chains of a megabyte and more take where this says no, pair / stream, us: int8 1024 x 2 at 9000 46.5 / 49.6, at
+// 16384 59.6 / 56.6, at 24576 93.2 / 85.8, 479-1024-1024-512-256-1 at 16384 59.6 / 65.4, at 24576 94.4 / 96.7; E4M3 1024 x 2 at 9000 45.9 / 44.3,
+// at 16384 53.6 / 48.8, at 24576 80.3 / 71.7; bf16 640 x 2 at 9000 37.9 / 38.0, at 16384 54.4 / 45.4: right for int8, up to 16 % short of the
+// better one for wide E4M3 and bf16 chains.
 static bool fused_pairs(int dtype, int m_blocks, size_t lds) {
     if (m_blocks <= 256 || 2 * lds > ogc_fused_lds_limit()) return false;
     return !(dtype == OGC_I8 && lds > 32 * 1024 && (m_blocks - 1) % 512 < 256);

@@ -299,10 +299,12 @@ MHA8_DEV void mha8_wait_and_meet(int n) {
 //   * Keys and values go from global memory straight into LDS; V^T leaves it through the transposing read
 //     (ds_read_b64_tr_b8: 8 keys x 16 channels per 16 lanes, the keys' rows chosen by the lanes' addresses).
 //   * The first half of the keys, the queries and the mask are asked for at once; then all keys for which LDS has slots.
-//     Where that is all that count (up to 384 keys of 128 channels), the second pass finds them there and loads values only.
+//     Where that is all that count, the second pass finds them there and loads values only.  Slots for 128 channels and 384 tokens: three
+//     workgroups on a compute unit 192 keys each, two 384, one 1024.
 //   * Registers are kept to 80 / 96 / 128 / 168 (32 / 64 / 96 / 128 channels) for 6 / 5 / 4 / 3 workgroups on a compute unit
 //     (Mha8::RESIDENT): one group of 32 keys at a time in the second pass, one place where its product is taken, so that the
-//     accumulators stay in place.  128 channels in 128 registers for four: 88 -> 103 us, slots for two units of keys only.
+//     accumulators stay in place.  96 channels miss their 128 by three registers, spilled between the passes; the build sees to it
+//     that no loop reloads one.  128 channels in 128 registers for four: 88 -> 103 us, slots for two units of keys only.
 //     Workgroups of six or eight wavefronts share their loads among more queries and are slower all the same: six leave two
 //     SIMDs with a wavefront too many for a second workgroup (131 us), eight of 128 channels spill (109).
 //   * A group of 32 keys whose mask entries are all zero (most of them) takes its maximum over the integer scores, two
@@ -722,8 +724,9 @@ template <int D32> void launch_i8(MhaI8Args& a, bool stream, unsigned tiles, hip
 
 // The streaming kernel or the plain one.  The former does less per score and starts slower (three times the code, the
 // mask looked at before the first score), half a microsecond on a launch that does not fill the chip; with 96 and 128 channels the
-// plain one's values, byte by byte into LDS, cost more than that in every launch.  Measured both ways, plain / streaming, us,
-// batch x heads x seq, padding mask:
+// plain one's values, byte by byte into LDS, cost more than that in every launch.  With 32 and 64 channels one line through the
+// sizes: near it either kernel is up to 8 % the better one (1x4x300 of 64 channels, 8x4x300 of 32 and 8x8x384 of 64 below are on the wrong
+// side).  Measured both ways, plain / streaming, us, batch x heads x seq, padding mask:
 //   d = 32:  16x16x100 6.8 / 7.3;  8x8x256 9.2 / 9.4;  32x12x128 8.7 / 8.2;  128x16x60 16.1 / 12.1;  8x4x300 10.6 / 10.3;  4x8x700 19.9 / 17.3
 //   d = 64:  1x16x64 4.9 / 5.5;  32x8x48 5.5 / 6.1;  16x16x100 7.3 / 7.9;  8x8x256 9.8 / 10.2;  8x16x200 10.1 / 9.7;  32x12x128 10.6 / 9.8;
 //            64x12x64 10.1 / 8.0;  16x16x256 15.4 / 13.5;  1x4x300 10.7 / 9.8;  1x8x384 12.3 / 12.0;  8x8x384 12.8 / 13.2
